@@ -183,9 +183,9 @@ tnt_status tnt_mem_bwd(const tnt_config* cfg, const void* q, const void* k, cons
  * of tnt_mem_fwd with no workspace and no saved buffer arguments.  Its
  * workspace is a device array of TNT_NOALLOC_WORKSPACE_BYTES that the library
  * holds on each GPU it runs on from the first call there until the process
- * ends; configurations whose smallest forward workspace (tnt_mem_workspace_size(cfg,
- * TNT_WS_FWD_MIN)) is larger get TNT_ERR_WORKSPACE (the forward takes the faster
- * two-pass local path when TNT_WS_FWD also fits).  The call allocates nothing
+ * ends; configurations whose forward without a saved buffer needs more (at most
+ * tnt_mem_workspace_size(cfg, TNT_WS_FWD_MIN)) get TNT_ERR_WORKSPACE (the forward takes
+ * the faster two-pass local path when TNT_WS_FWD also fits).  The call allocates nothing
  * (no hipMalloc / hipFree, no helper stream: every launch is on `stream`), and
  * the forward writes every part of that array it reads, so the previous
  * call's contents do not matter.  All calls on one GPU share the array: calls
@@ -216,9 +216,9 @@ tnt_status tnt_mem_fwd_noalloc(const tnt_config* cfg, const void* q, const void*
  * blocks ordered [M][B][H], followed by a scratch area of M*B*H blocks of
  * 2*hid + d + 3*G*d floats (G = hid / min(64, hid)), each rounded up to a
  * multiple of 64 floats, whose contents are undefined between calls.  Calls
- * on one state must be serialised (same stream).  Each token takes three
- * launches over (hidden-unit slice, chain, memory) workgroups; the work is
- * matrix-vector products and rank-one updates of the fp32 state. */
+ * on one state must be serialised (same stream).  Up to 16 tokens between two
+ * chunk boundaries take two launches over (hidden-unit slice, chain, memory)
+ * workgroups, a boundary one more. */
 
 /* Bytes of the carried state (0 if the config is invalid). */
 size_t tnt_mem_state_size(const tnt_config* cfg);

@@ -256,9 +256,10 @@ struct StepArgs {
   float* state;
   void* o;                                    // [B][H][T][d]
   size_t mem_stride;
-  // per-token launches: hidden units split into G slices of HS; the scratch
-  // area (after every state block) holds sc_stride floats per (memory, chain)
-  int G, HS, t;
+  // hidden units split into G slices of HS; the scratch area (after every state
+  // block) holds sc_stride floats per (memory, chain); a launch takes tokens
+  // t0 .. t0 + n - 1
+  int G, HS, t0, n;
   float* scratch;
   size_t sc_stride;
 };

@@ -14,399 +14,473 @@
 // o_i = f(W_t, M q_t) (Sec. 4.1.1 local update, Sec. 4.1.2; App. C).
 //
 // The state of every (memory, chain) is split by hidden unit into G slices of
-// HS = min(64, hid): slice g owns rows [g HS, (g+1) HS) of W^1, W1, S1 and the
-// same columns of W^2, W2, S2, and one workgroup per (slice, chain, memory)
-// touches nothing else of the state.  Each token takes three launches:
-//   K1: chunk / shard boundary of the slice; z = W^1 k (and the global
-//       retrieval's W^1 q) for the slice's rows; s(z), s'(z) to scratch; the
-//       slice's share of W^2 s(z) (and W^2 s(W^1 q)); a local memory's query
-//       x = M_t q (slice 0);
-//   K2: r = (2/d)(sum of the shares - v); the slice's delta = (W^2^T r) s'(z);
-//       the gated update of the slice; a local memory's W1_t x on the fresh
-//       rows and its share of W2_t s(W1_t x); M += k k^T / ||k||^2 (slice 0);
-//   K3: o = sum of the retrieval shares (global memory first, fixed order).
-// The work is matrix-vector products and rank-one updates of the fp32 state
-// (HBM-bound), with 16-byte loads issued in batches; there is no contraction
-// long enough for MFMA tiles.
+// HS = min(64, hid): slice g owns rows [g HS, (g+1) HS) of W1, S1 and the same
+// columns of W2, S2.  Everything that is taken at the entry weights (z = W^1 k,
+// y = W^2 s(z), the residual r, delta = (W^2^T r) s'(z), the global retrieval) is
+// independent from token to token until the next chunk boundary, and a slice's
+// running weights depend on r and its own rows only.  So up to STEP_N tokens that
+// no memory's chunk boundary divides take two launches:
+//   tokens  one workgroup per (slice, chain, memory): y of every token over all
+//           hidden units (each slice forms it for itself: no exchange between
+//           workgroups), r, the slice's delta; then, token by token with the
+//           slice's W1, S1, W2, S2 in registers, the gated update and a local
+//           memory's share of W2_t s(W1_t x).  A local memory's queries
+//           x = M_t q come from a private copy of its Q-K sum.
+//   out     o = the sum of the retrieval shares (global memory first, fixed
+//           order); M += k k^T / ||k||^2 of every token.
+// A third launch, before them, where a memory's chunk or shard begins: W^ <- W,
+// or the reset.  The products at the entry weights are fp32 MFMA tiles of 16
+// tokens (rows past the call's tokens zero); a token's row does not depend on the
+// other rows, so every cut of a sequence gives bitwise the same results.
+//
+// Bound by latency at few tokens and by the state's bytes (read and written once a
+// launch, W^ read once per slice through L2) at one token: the slice's whole state
+// is requested before the first product.  B 4, H 8, d 64, hid 256, global + one
+// local: one token 22.9 us (31.1 with three launches per token, which also read every
+// weight once more); 77 tokens at B 2 336 us (2104: three launches per token).
 #include "tnt_device.h"
 #include "tnt_kernels.h"
+
+#include <algorithm>
+#include <type_traits>
 
 namespace tnt {
 
 namespace {
 
 constexpr int STEP_THREADS = 256;
+// threads of a token launch: 512 at d = 128, where a slice's state, M and the weights
+// in flight would not fit the registers of 256
+constexpr int step_threads(int d) { return d == 128 ? 512 : STEP_THREADS; }
 constexpr int STEP_MAX_D = 128, STEP_MAX_H = 512;
-constexpr int SEG4 = 16;                  // 16-byte loads a thread issues before reducing
-constexpr int STEP_PART = 4096;           // LDS floats of the partial sums
+constexpr int STEP_N = 16;  // tokens of one launch at most: the rows of an MFMA tile
 
-// One row-dot job: y[r] = A[r] . x (and y2[r] = A[r] . x2 when x2 is set) for r < R.
-struct RowJob {
-  const float* A;
-  int R, N, lda;  // rows, row length, row stride (floats)
-  const float *x, *x2;
-  float *y, *y2;
+// LDS of the token launch (floats; rows padded by 16 bytes)
+struct StepLds {
+  int ld, lh, ls;                           // row strides: d, hid, HS
+  int k, q, r, x, a, aq, sp, g, z, kk, kq, gt;  // offsets
+  int total;
 };
-
-// Runs up to two jobs in one pass.  Each row is cut into segments of up to
-// SEG4 float4; a thread loads a whole segment, then forms its dots with the
-// job's vectors; the segment sums meet in `part` (at most STEP_PART floats:
-// R * segments * vectors summed over the jobs).
-__device__ __forceinline__ void row_dots_2(const RowJob j0, const RowJob j1, float* part) {
-  const int s0 = (j0.N / 4) < SEG4 ? 1 : (j0.N / 4) / SEG4;
-  const int s1 = (j1.N / 4) < SEG4 ? 1 : (j1.N / 4) / SEG4;
-  const int n0 = j0.R * s0, n1 = j1.R * s1;
-  const int v0 = j0.x2 ? 2 : 1;
-  float* part1 = part + v0 * n0;
-  for (int it = threadIdx.x; it < n0 + n1; it += blockDim.x) {
-    const bool first = it < n0;
-    // the job's fields picked by value (a reference would put the jobs in scratch)
-    const float* jA = first ? j0.A : j1.A;
-    const float* jx = first ? j0.x : j1.x;
-    const float* jx2 = first ? j0.x2 : j1.x2;
-    const int jN = first ? j0.N : j1.N, jld = first ? j0.lda : j1.lda;
-    const int S = first ? s0 : s1, ii = first ? it : it - n0;
-    const int n4 = jN / 4, seg4 = n4 < SEG4 ? n4 : SEG4;
-    const int r = ii / S, sg = ii - r * S;
-    const f4* row = reinterpret_cast<const f4*>(jA + (size_t)r * jld) + sg * seg4;
-    f4 buf[SEG4];
-#pragma unroll
-    for (int c = 0; c < SEG4; ++c)
-      if (c < seg4) buf[c] = row[c];
-    const f4* x4 = reinterpret_cast<const f4*>(jx) + sg * seg4;
-    float acc = 0.f;
-#pragma unroll
-    for (int c = 0; c < SEG4; ++c)
-      if (c < seg4) {
-        const f4 xv = x4[c];
-        acc += buf[c][0] * xv[0] + buf[c][1] * xv[1] + buf[c][2] * xv[2] + buf[c][3] * xv[3];
-      }
-    (first ? part : part1)[ii] = acc;
-    if (jx2) {
-      const f4* y4 = reinterpret_cast<const f4*>(jx2) + sg * seg4;
-      float acc2 = 0.f;
-#pragma unroll
-      for (int c = 0; c < SEG4; ++c)
-        if (c < seg4) {
-          const f4 xv = y4[c];
-          acc2 += buf[c][0] * xv[0] + buf[c][1] * xv[1] + buf[c][2] * xv[2] + buf[c][3] * xv[3];
-        }
-      (first ? part + n0 : part1 + n1)[ii] = acc2;
-    }
-  }
-  __syncthreads();
-  for (int r = threadIdx.x; r < j0.R + j1.R; r += blockDim.x) {
-    const bool first = r < j0.R;
-    float* jy = first ? j0.y : j1.y;
-    float* jy2 = first ? j0.y2 : j1.y2;
-    const bool two = first ? j0.x2 != nullptr : j1.x2 != nullptr;
-    const int S = first ? s0 : s1, rr = first ? r : r - j0.R, n = first ? n0 : n1;
-    const float* pp = first ? part : part1;
-    float acc = 0.f;
-    for (int sg = 0; sg < S; ++sg) acc += pp[rr * S + sg];
-    jy[rr] = acc;
-    if (two) {
-      float acc2 = 0.f;
-      for (int sg = 0; sg < S; ++sg) acc2 += pp[n + rr * S + sg];
-      jy2[rr] = acc2;
-    }
-  }
+__host__ __device__ inline StepLds step_lds(int d, int hid, int HS) {
+  StepLds y;
+  y.ld = d + 4; y.lh = hid + 4; y.ls = HS + 4;
+  int o = 0;
+  y.k = o; o += STEP_N * y.ld;
+  y.q = o; o += STEP_N * y.ld;
+  y.r = o; o += STEP_N * y.ld;
+  y.x = o; o += STEP_N * y.ld;
+  y.a = o; o += STEP_N * y.lh;   // s(z)
+  y.aq = o; o += STEP_N * y.lh;  // s(W^1 q) (global memory)
+  y.sp = o; o += STEP_N * y.ls;  // s'(z) of the slice
+  y.g = o; o += STEP_N * y.ls;   // delta of the slice
+  y.z = o; o += 2 * HS;          // s(W1_t x) of the slice, two tokens in turn
+  y.kk = o; o += STEP_N;         // 1 / ||k||^2 (0 for a zero key)
+  y.kq = o; o += STEP_N;         // k . q
+  y.gt = o; o += 3 * STEP_N;     // lr, mom, decay
+  y.total = o;
+  return y;
 }
 
-__device__ __forceinline__ void row_dots(const float* A, int R, int N, const float* x, float* y,
-                                         float* part) {
-  const RowJob j0{A, R, N, N, x, nullptr, y, nullptr}, none{A, 0, N, N, x, nullptr, y, nullptr};
-  row_dots_2(j0, none, part);
+// One 16-byte piece of a lane's row of B in the product acc(t, j) += sum_k A[t][k] B[j][k]
+// (16 rows t of A in LDS, 16 rows j of B, both contraction-contiguous): the piece at
+// contraction offset k0 + 4 (lane / 16) holds four consecutive k, one per MFMA step
+// (the steps sum the same k on both sides).
+__device__ __forceinline__ void row_piece(f4& acc, const float* A, int lda, int k0, const f4& b) {
+  const int l = lane_id();
+  const f4 x = *reinterpret_cast<const f4*>(A + (l & 15) * lda + k0 + 4 * (l >> 4));
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r], b[r], acc, 0, 0, 0);
 }
 
-// y[c] = sum_r A[r][c] x[r] for c < N.  A thread takes four columns (one
-// float4) over a run of up to SEG4 rows, loading the run first; the run sums
-// meet in `part` (N/4 * runs * 4 <= STEP_PART here).
-__device__ __forceinline__ void col_dots(const float* A, int R, int N, int lda, const float* x,
-                                         float* y, float* part) {
-  const int n4 = N / 4, ld4 = lda / 4;
-  const int run = R < SEG4 ? R : SEG4;
-  const int nr = R / run;
-  const f4* A4 = reinterpret_cast<const f4*>(A);
-  f4* p4 = reinterpret_cast<f4*>(part);
-  for (int it = threadIdx.x; it < n4 * nr; it += blockDim.x) {
-    const int c4 = it % n4, rr = it / n4;
-    const int r0 = rr * run;
-    f4 buf[SEG4];
+// Sums over groups of W consecutive lanes (4, 8, 16 or 32, aligned), every lane of a
+// group getting the sum, for NU values at once: exchanges inside the quads, then
+// mirrors of 8 and 16 lanes (whose quads / halves hold equal values by then).
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
+}
+template <int NU>
+__device__ __forceinline__ void group_sums(float (&x)[NU], int W) {
 #pragma unroll
-    for (int i = 0; i < SEG4; ++i)
-      if (i < run) buf[i] = A4[(size_t)(r0 + i) * ld4 + c4];
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int u = 0; u < NU; ++u) x[u] += dpp_f<0xB1>(x[u]);  // quad_perm [1, 0, 3, 2]
 #pragma unroll
-    for (int i = 0; i < SEG4; ++i)
-      if (i < run) acc += buf[i] * x[r0 + i];
-    p4[it] = acc;
-  }
-  __syncthreads();
-  for (int c = threadIdx.x; c < N; c += blockDim.x) {
-    const int c4 = c >> 2, e = c & 3;
-    float acc = 0.f;
-    for (int rr = 0; rr < nr; ++rr) acc += part[(size_t)(rr * n4 + c4) * 4 + e];
-    y[c] = acc;
-  }
+  for (int u = 0; u < NU; ++u) x[u] += dpp_f<0x4E>(x[u]);  // quad_perm [2, 3, 0, 1]
+  if (W >= 8)
+#pragma unroll
+    for (int u = 0; u < NU; ++u) x[u] += dpp_f<0x141>(x[u]);  // row_half_mirror
+  if (W >= 16)
+#pragma unroll
+    for (int u = 0; u < NU; ++u) x[u] += dpp_f<0x140>(x[u]);  // row_mirror
+  if (W >= 32)
+#pragma unroll
+    for (int u = 0; u < NU; ++u) x[u] += __shfl_xor(x[u], 16, WAVE);
+}
+
+// 1 / ||k||^2 (0 for a zero key) of one LDS row, the same in every launch
+__device__ __forceinline__ float inv_norm2(const float* k, int d) {
+  float s = 0.f;
+  for (int i = lane_id(); i < d; i += WAVE) s = __builtin_fmaf(k[i], k[i], s);
+  s = wave_sum(s);
+  return s > 0.f ? 1.0f / s : 0.f;
+}
+
+// the retrieval shares of a launch's tokens, per chain: [n][d] of the global memory
+// (if any), then [n][G][d] of every local memory
+__device__ __forceinline__ float* step_share(const StepArgs& a, int chain, int m) {
+  float* b = a.scratch + (size_t)chain * a.M * a.sc_stride;
+  const size_t nd = (size_t)a.n * a.d;
+  if (a.has_global && m == 0) return b;
+  return b + (a.has_global ? nd : 0) + (size_t)(m - a.has_global) * a.G * nd;
 }
 
 }  // namespace
 
-// scratch of one (memory, chain), floats: s(z) [hid], s'(z) [hid], x [d],
-// then per slice the shares W^2 s(z) [G][d], global W^2 s(W^1 q) [G][d] and
-// local W2_t s(W1_t x) [G][d]
-struct StepScr {
-  float *a, *sp, *x, *yp, *yq, *y2;
-};
-__device__ __forceinline__ StepScr step_scr(const StepArgs& a, int m, int chain) {
-  float* b = a.scratch + ((size_t)m * a.B * a.H + chain) * a.sc_stride;
-  StepScr s;
-  s.a = b;
-  s.sp = b + a.hid;
-  s.x = b + 2 * a.hid;
-  s.yp = s.x + a.d;
-  s.yq = s.yp + (size_t)a.G * a.d;
-  s.y2 = s.yq + (size_t)a.G * a.d;
-  return s;
-}
-
-template <typename IO, int ACT>
-__global__ void __launch_bounds__(STEP_THREADS) step_k1(StepArgs a) {
-  __shared__ __align__(16) float sq[STEP_MAX_D], sk[STEP_MAX_D], sx[STEP_MAX_D], sy[STEP_MAX_D],
-      syq[STEP_MAX_D];
-  __shared__ __align__(16) float sz[64], sa[64], szq[64], saq[64];
-  __shared__ __align__(16) float part[STEP_PART];
-  __shared__ float red[STEP_THREADS / WAVE];
-  const int g = blockIdx.x, chain = blockIdx.y, m = blockIdx.z;
-  const int H = a.H, d = a.d, hid = a.hid, HS = a.HS, j0 = g * HS;
-  const int b = chain / H, h = chain - b * H, t = a.t;
-  const long long p = a.pos + t;
+// A chunk or shard begins at position pos + t0: W^ <- W, or the reset.
+__global__ void __launch_bounds__(256) step_boundary_kernel(StepArgs a) {
+  const int chain = blockIdx.y, m = blockIdx.z;
+  const long long p = a.pos + a.t0;
   const bool global = a.has_global && m == 0;
-  const size_t hd = (size_t)hid * d;
-  float* base = a.state + ((size_t)m * a.B * H + chain) * a.mem_stride;
-  float *Wh1 = base, *Wh2 = base + hd, *W1 = base + 2 * hd, *W2 = base + 3 * hd,
-        *S1 = base + 4 * hd, *S2 = base + 5 * hd, *Mq = base + 6 * hd;
-  const StepScr sc = step_scr(a, m, chain);
-  const size_t tok = ((size_t)chain * a.T + t) * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    sq[i] = to_f(((const IO*)a.q)[tok + i]);
-    sk[i] = to_f(((const IO*)a.k)[tok + i]);
-  }
-
-  // chunk / shard boundary, restricted to the slice (and M on slice 0)
   const bool reset = !global && p % a.S[m] == 0;
-  if (reset || p % a.C[m] == 0) {
-    const float* W1i = a.W1i + ((size_t)m * H + h) * hd;
-    const float* W2i = a.W2i + ((size_t)m * H + h) * hd;
-    for (int e = threadIdx.x; e < HS * d; e += blockDim.x) {  // rows of W^1, W1, S1
-      const size_t i1 = (size_t)j0 * d + e;
-      if (reset) {
-        Wh1[i1] = W1[i1] = W1i[i1];
-        S1[i1] = 0.f;
-      } else {
-        Wh1[i1] = W1[i1];
-      }
-    }
-    for (int e = threadIdx.x; e < HS * d; e += blockDim.x) {  // columns of W^2, W2, S2
-      const int i = e / HS, jj = e - i * HS;
-      const size_t i2 = (size_t)i * hid + j0 + jj;
-      if (reset) {
-        Wh2[i2] = W2[i2] = W2i[i2];
-        S2[i2] = 0.f;
-      } else {
-        Wh2[i2] = W2[i2];
-      }
-    }
-    if (!global && g == 0 && (reset || a.qk_scope == 1))
-      for (int e = threadIdx.x; e < d * d; e += blockDim.x) Mq[e] = 0.f;
-  }
-  __syncthreads();
-
-  // z = W^1 k on the slice's rows (and the global retrieval's W^1 q); a local
-  // memory's M_{t-1} q on slice 0
-  const bool proj = !global && a.qk_proj && g == 0;
-  {
-    const RowJob r1{Wh1 + (size_t)j0 * d, HS, d, d, sk, global ? sq : nullptr, sz,
-                    global ? szq : nullptr};
-    const RowJob r2{Mq, proj ? d : 0, d, d, sq, nullptr, sx, nullptr};
-    row_dots_2(r1, r2, part);
-  }
-  __syncthreads();
-  for (int jj = threadIdx.x; jj < HS; jj += blockDim.x) {
-    const ActVals av = act_all<ACT>(sz[jj]);
-    sa[jj] = av.s;
-    sc.a[j0 + jj] = av.s;
-    sc.sp[j0 + jj] = av.d1;
-    if (global) saq[jj] = act_f<ACT>(szq[jj]);
-  }
-  __syncthreads();
-  // the slice's share of W^2 s(z) (and of W^2 s(W^1 q))
-  {
-    const RowJob r1{Wh2 + j0, d, HS, hid, sa, global ? saq : nullptr, sy, global ? syq : nullptr};
-    const RowJob none{Wh2, 0, HS, hid, sa, nullptr, sy, nullptr};
-    row_dots_2(r1, none, part);
-  }
-  float kk = 0.f, kq = 0.f;
-  if (!global && g == 0) {
-    for (int i = threadIdx.x; i < d; i += blockDim.x) {
-      kk += sk[i] * sk[i];
-      kq += sk[i] * sq[i];
+  if (!reset && p % a.C[m] != 0) return;
+  const int h = chain % a.H;
+  const size_t hd4 = (size_t)a.hid * a.d / 4, dd4 = (size_t)a.d * a.d / 4;
+  f4* base = reinterpret_cast<f4*>(a.state + ((size_t)m * a.B * a.H + chain) * a.mem_stride);
+  const f4* W1i = reinterpret_cast<const f4*>(a.W1i) + ((size_t)m * a.H + h) * hd4;
+  const f4* W2i = reinterpret_cast<const f4*>(a.W2i) + ((size_t)m * a.H + h) * hd4;
+  const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, st = (size_t)gridDim.x * blockDim.x;
+  for (size_t e = i0; e < hd4; e += st) {
+    if (reset) {
+      base[e] = base[2 * hd4 + e] = W1i[e];
+      base[hd4 + e] = base[3 * hd4 + e] = W2i[e];
+      base[4 * hd4 + e] = base[5 * hd4 + e] = zero4();
+    } else {
+      base[e] = base[2 * hd4 + e];
+      base[hd4 + e] = base[3 * hd4 + e];
     }
   }
-  kk = block_sum(kk, red);  // (barrier inside: the shares are complete)
-  kq = block_sum(kq, red);
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    sc.yp[(size_t)g * d + i] = sy[i];
-    if (global) sc.yq[(size_t)g * d + i] = syq[i];
-    // local query x = M_t q = M_{t-1} q + k (k . q) / ||k||^2, or q
-    if (!global && g == 0) {
-      const float ikk = kk > 0.f ? 1.0f / kk : 0.f;
-      sc.x[i] = a.qk_proj ? sx[i] + sk[i] * (kq * ikk) : sq[i];
-    }
-  }
+  if (!global && (reset || a.qk_scope == 1))
+    for (size_t e = i0; e < dd4; e += st) base[6 * hd4 + e] = zero4();
 }
 
-template <typename IO, int ACT>
-__global__ void __launch_bounds__(STEP_THREADS) step_k2(StepArgs a) {
-  __shared__ __align__(16) float sk[STEP_MAX_D], sr[STEP_MAX_D], sx[STEP_MAX_D], sy[STEP_MAX_D];
-  __shared__ __align__(16) float sa[64], sp[64], sg[64], sz[64];
-  __shared__ __align__(16) float part[STEP_PART];
-  __shared__ float red[STEP_THREADS / WAVE];
+// Tokens t0 .. t0 + n - 1.  Every weight a workgroup reads is requested before the
+// first barrier (hid up to 256; the rest of a larger one in a second round).
+template <typename IO, int ACT, int D>
+__global__ void __launch_bounds__(step_threads(D)) step_tokens_kernel(StepArgs a) {
+  extern __shared__ __align__(16) float sm[];
+  constexpr int d = D, NT = step_threads(D), NW = NT / WAVE;
+  constexpr int g4 = D / 4;                    // 16-byte pieces of a row of W1, S1, M
+  constexpr int NU = D <= 32 ? 2 : 16 * D / NT;  // pieces of each of the slice's arrays a thread holds
+  constexpr int NM = (D * g4 + NT - 1) / NT;  // and of M
+  constexpr int ND = D / 16;                   // tiles of d, pieces of a row of W^1
+  constexpr int GZ = D == 128 ? 2 : 4;         // row tiles of W^1 a wave requests at a time
+  constexpr int GY = D == 128 ? 8 : 16;        // pieces of a row of W^2 likewise
   const int g = blockIdx.x, chain = blockIdx.y, m = blockIdx.z;
-  const int B = a.B, H = a.H, d = a.d, hid = a.hid, HS = a.HS, G = a.G, j0 = g * HS;
-  const int b = chain / H, h = chain - b * H, t = a.t;
+  const int H = a.H, hid = a.hid, HS = a.HS, G = a.G, j0 = g * HS, n = a.n;
+  const int tid = threadIdx.x, l = lane_id(), w = wave_id(), lg = l >> 4, lc = l & 15;
   const bool global = a.has_global && m == 0;
+  const bool proj = !global && a.qk_proj;
   const size_t hd = (size_t)hid * d;
-  float* base = a.state + ((size_t)m * B * H + chain) * a.mem_stride;
-  float *Wh2 = base + hd, *W1 = base + 2 * hd, *W2 = base + 3 * hd, *S1 = base + 4 * hd,
-        *S2 = base + 5 * hd, *Mq = base + 6 * hd;
-  const StepScr sc = step_scr(a, m, chain);
-  const size_t tok = ((size_t)chain * a.T + t) * d;
-  const size_t gi = (((size_t)m * B + b) * H + h) * a.T + t;
-  const float eta = a.lr[gi], beta = a.mom[gi], alpha = a.decay[gi];
-  const float rs = 2.0f / (float)d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    sk[i] = to_f(((const IO*)a.k)[tok + i]);
-    float y = 0.f;
-    for (int gg = 0; gg < G; ++gg) y += sc.yp[(size_t)gg * d + i];
-    sr[i] = rs * (y - to_f(((const IO*)a.v)[tok + i]));
-    if (!global) sx[i] = sc.x[i];
+  float* const base = a.state + ((size_t)m * a.B * H + chain) * a.mem_stride;
+  const float *Wh1 = base, *Wh2 = base + hd, *Mq = base + 6 * hd;
+  float *W1 = base + 2 * hd + (size_t)j0 * d, *W2 = base + 3 * hd + j0;
+  float *S1 = base + 4 * hd + (size_t)j0 * d, *S2 = base + 5 * hd + j0;
+  const StepLds Y = step_lds(d, hid, HS);
+  float *sk = sm + Y.k, *sq = sm + Y.q, *sr = sm + Y.r, *sx = sm + Y.x, *sa = sm + Y.a,
+        *saq = sm + Y.aq, *ssp = sm + Y.sp, *sg = sm + Y.g, *sz = sm + Y.z, *skk = sm + Y.kk,
+        *skq = sm + Y.kq, *sgt = sm + Y.gt;
+  const size_t tok = ((size_t)chain * a.T + a.t0) * d;
+  const IO *q = (const IO*)a.q + tok, *k = (const IO*)a.k + tok, *v = (const IO*)a.v + tok;
+  const size_t gi = ((size_t)m * a.B * H + chain) * a.T + a.t0;
+
+  for (int e = tid; e < STEP_N * d; e += NT) {
+    const int t = e / d, i = e - t * d;
+    sk[t * Y.ld + i] = t < n ? to_f(k[e]) : 0.f;
+    sq[t * Y.ld + i] = t < n ? to_f(q[e]) : 0.f;
   }
-  for (int jj = threadIdx.x; jj < HS; jj += blockDim.x) {
-    sa[jj] = sc.a[j0 + jj];
-    sp[jj] = sc.sp[j0 + jj];
+  if (tid < 3 * STEP_N) {
+    const int t = tid & (STEP_N - 1);
+    const float* p = tid < STEP_N ? a.lr : tid < 2 * STEP_N ? a.mom : a.decay;
+    if (t < n) sgt[tid] = p[gi + t];
   }
-  __syncthreads();
-  // delta = (W^2^T r) * s'(z) on the slice
-  col_dots(Wh2 + j0, d, HS, hid, sr, sg, part);
-  __syncthreads();
-  for (int jj = threadIdx.x; jj < HS; jj += blockDim.x) sg[jj] *= sp[jj];
+  // W^1 rows of the wave's first tiles, W^2 rows of its tile, the slice's W^2 columns
+  f4 bz[GZ][ND], by[GY], bd[ND];
+  auto load_z = [&](int x0) {
+#pragma unroll
+    for (int x = 0; x < GZ; ++x) {
+      const int jt = w + NW * (x0 + x);
+      if (jt < hid / 16)
+#pragma unroll
+        for (int s = 0; s < ND; ++s)
+          bz[x][s] = *reinterpret_cast<const f4*>(Wh1 + (size_t)(jt * 16 + lc) * d + 16 * s + 4 * lg);
+    }
+  };
+  auto load_y = [&](int it, int k0) {
+#pragma unroll
+    for (int s = 0; s < GY; ++s)
+      if (k0 + 16 * s < hid)
+        by[s] = *reinterpret_cast<const f4*>(Wh2 + (size_t)(it * 16 + lc) * hid + k0 + 16 * s + 4 * lg);
+  };
+  load_z(0);
+  if (w < ND) load_y(w, 0);
+  if (w < HS / 16)
+#pragma unroll
+    for (int s = 0; s < ND; ++s)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        bd[s][r] = Wh2[(size_t)(16 * s + 4 * lg + r) * hid + j0 + w * 16 + lc];
+  // the slice's state and M
+  const int h4 = HS / 4, n4 = HS * g4;
+  constexpr int m4 = D * g4;
+  f4 w1[NU], s1[NU], w2[NU], s2[NU], mq[NM];
+  if (proj)
+#pragma unroll
+    for (int u = 0; u < NM; ++u) {
+      const int e = tid + u * NT;
+      if (e < m4) mq[u] = reinterpret_cast<const f4*>(Mq)[e];
+    }
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int e = tid + u * NT;
+    w1[u] = s1[u] = w2[u] = s2[u] = zero4();
+    if (e < n4) {
+      const size_t o2 = (size_t)(e / h4) * hid + 4 * (e % h4);
+      w1[u] = reinterpret_cast<const f4*>(W1)[e];
+      s1[u] = reinterpret_cast<const f4*>(S1)[e];
+      w2[u] = *reinterpret_cast<const f4*>(W2 + o2);
+      s2[u] = *reinterpret_cast<const f4*>(S2 + o2);
+    }
+  }
   __syncthreads();
 
-  // gated update of the slice (16-byte accesses, UNR per array in flight);
-  // a local memory also forms z'[j] = W1_t[j] . x from the fresh rows (the
-  // d/4 lanes of a row are adjacent in a wave and sum by shuffles)
-  const float keep = 1.0f - alpha;
-  constexpr int UNR = 4;
-  const int g4 = d / 4, h4 = HS / 4, n4 = HS * d / 4;  // n4: a multiple of 64
-  const f4* k4 = reinterpret_cast<const f4*>(sk);
-  const f4* x4 = reinterpret_cast<const f4*>(sx);
-  const f4* a4 = reinterpret_cast<const f4*>(sa);
-  {
-    f4 *S14 = reinterpret_cast<f4*>(S1 + (size_t)j0 * d), *W14 = reinterpret_cast<f4*>(W1 + (size_t)j0 * d);
-    for (int e0 = threadIdx.x; e0 < n4; e0 += UNR * blockDim.x) {
-      f4 s1[UNR], w1[UNR];
+  // z = W^1 k of every hidden unit (and the global retrieval's W^1 q).  A product and
+  // the reads of its accumulator stay in one basic block here and below: where a
+  // branch between them joined, the compiler (ROCm 7.2) left out the wait for the
+  // last MFMA on the path that skips it.
+  auto z_phase = [&](auto two) {
+    constexpr bool TWO = decltype(two)::value;
+    for (int x0 = 0; w + NW * x0 < hid / 16; x0 += GZ) {
+      if (x0) load_z(x0);
 #pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int e = e0 + u * blockDim.x;
-        if (e < n4) {
-          s1[u] = S14[e];
-          w1[u] = W14[e];
+      for (int x = 0; x < GZ; ++x) {
+        const int jt = w + NW * (x0 + x);
+        if (jt >= hid / 16) continue;
+        f4 z = zero4(), zq = zero4();
+#pragma unroll
+        for (int s = 0; s < ND; ++s) {
+          row_piece(z, sk, Y.ld, 16 * s, bz[x][s]);
+          if constexpr (TWO) row_piece(zq, sq, Y.ld, 16 * s, bz[x][s]);
         }
-      }
+        const int j = jt * 16 + lc;
+        const bool mine = j >= j0 && j < j0 + HS;
 #pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int e = e0 + u * blockDim.x;
-        if (e < n4) {  // whole waves take this branch
-          const int jj = e / g4, l4 = e - jj * g4;
-          const f4 n1 = beta * s1[u] - (eta * sg[jj]) * k4[l4];
-          const f4 nw = keep * w1[u] + n1;
-          S14[e] = n1;
-          W14[e] = nw;
-          if (!global) {
-            const f4 xv = x4[l4];
-            float zp = nw[0] * xv[0] + nw[1] * xv[1] + nw[2] * xv[2] + nw[3] * xv[3];
-            for (int o_ = 1; o_ < g4; o_ <<= 1) zp += __shfl_xor(zp, o_, WAVE);
-            if (l4 == 0) sz[jj] = zp;
-          }
+        for (int r = 0; r < 4; ++r) {
+          const int t = 4 * lg + r;
+          const ActVals av = act_all<ACT>(z[r]);
+          sa[t * Y.lh + j] = av.s;
+          if (mine) ssp[t * Y.ls + j - j0] = av.d1;
+          if constexpr (TWO) saq[t * Y.lh + j] = act_f<ACT>(zq[r]);
         }
       }
     }
-  }
-  {
-    for (int e0 = threadIdx.x; e0 < n4; e0 += UNR * blockDim.x) {
-      f4 s2[UNR], w2[UNR];
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int e = e0 + u * blockDim.x;
-        if (e < n4) {
-          const int i = e / h4, c4 = e - i * h4;
-          const size_t ofs = (size_t)i * hid + j0 + 4 * c4;
-          s2[u] = *reinterpret_cast<const f4*>(S2 + ofs);
-          w2[u] = *reinterpret_cast<const f4*>(W2 + ofs);
-        }
+  };
+  if (global)
+    z_phase(std::true_type{});
+  else
+    z_phase(std::false_type{});
+  if (proj)  // 1 / ||k||^2, k . q
+    for (int t = w; t < n; t += NW) {
+      const float ik = inv_norm2(sk + t * Y.ld, d);
+      float s = 0.f;
+      for (int i = l; i < d; i += WAVE) s = __builtin_fmaf(sk[t * Y.ld + i], sq[t * Y.ld + i], s);
+      s = wave_sum(s);
+      if (l == 0) {
+        skk[t] = ik;
+        skq[t] = s;
       }
+    }
+  __syncthreads();
+  // r = (2/d) (W^2 s(z) - v); the global retrieval's columns dealt to the slices
+  const float rs = 2.0f / (float)d;
+  auto y_tile = [&](int it, auto pieces, auto two) {
+    constexpr int P = decltype(pieces)::value;  // pieces of a row of W^2 a round
+    constexpr bool TWO = decltype(two)::value;
+    f4 y = zero4(), yq = zero4();
+    for (int k0 = 0; k0 < hid; k0 += 16 * P) {
+      if (it != w || k0) load_y(it, k0);
 #pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int e = e0 + u * blockDim.x;
-        if (e < n4) {
-          const int i = e / h4, c4 = e - i * h4;
-          const size_t ofs = (size_t)i * hid + j0 + 4 * c4;
-          const f4 n2 = beta * s2[u] - (eta * sr[i]) * a4[c4];
-          *reinterpret_cast<f4*>(S2 + ofs) = n2;
-          *reinterpret_cast<f4*>(W2 + ofs) = keep * w2[u] + n2;
+      for (int s = 0; s < P; ++s) {
+        row_piece(y, sa, Y.lh, k0 + 16 * s, by[s]);
+        if constexpr (TWO) row_piece(yq, saq, Y.lh, k0 + 16 * s, by[s]);
+      }
+    }
+    const int i = it * 16 + lc;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int t = 4 * lg + r;
+      sr[t * Y.ld + i] = t < n ? rs * (y[r] - to_f(v[(size_t)t * d + i])) : 0.f;
+      if (TWO && t < n) step_share(a, chain, m)[(size_t)t * d + i] = yq[r];
+    }
+  };
+  auto y_rows = [&](auto pieces) {
+    for (int it = w; it < ND; it += NW) {
+      if (global && it % G == g)
+        y_tile(it, pieces, std::true_type{});
+      else
+        y_tile(it, pieces, std::false_type{});
+    }
+  };
+  switch (hid / 16) {  // a power of two
+    case 1: y_rows(std::integral_constant<int, 1>{}); break;
+    case 2: y_rows(std::integral_constant<int, 2>{}); break;
+    case 4: y_rows(std::integral_constant<int, 4>{}); break;
+    case 8: y_rows(std::integral_constant<int, 8>{}); break;
+    default: y_rows(std::integral_constant<int, GY>{}); break;
+  }
+  // a local memory's queries, token by token: x = M_{t-1} q + k (k . q) / ||k||^2,
+  // M_t = M_{t-1} + k k^T / ||k||^2 (or q itself)
+  if (proj) {
+    for (int t = 0; t < n; ++t) {
+      const f4 *k4 = reinterpret_cast<const f4*>(sk + t * Y.ld), *q4 = reinterpret_cast<const f4*>(sq + t * Y.ld);
+      const float ik = skk[t], c = skq[t] * ik;
+      const f4 qv = q4[tid % g4], kv = k4[tid % g4];  // a thread's pieces share their column
+      static_assert(NT % g4 == 0, "one column of pieces per thread");
+      float s[NM];
+#pragma unroll
+      for (int u = 0; u < NM; ++u)
+        s[u] = mq[u][0] * qv[0] + mq[u][1] * qv[1] + mq[u][2] * qv[2] + mq[u][3] * qv[3];
+      group_sums<NM>(s, g4);
+#pragma unroll
+      for (int u = 0; u < NM; ++u) {
+        const int e = tid + u * NT;
+        if (e < m4) {
+          const int i = e / g4;
+          const float ki = sk[t * Y.ld + i];
+          if (e % g4 == 0) sx[t * Y.ld + i] = s[u] + ki * c;
+          const float kn = ki * ik;
+#pragma unroll
+          for (int x = 0; x < 4; ++x) mq[u][x] = __builtin_fmaf(kn, kv[x], mq[u][x]);
         }
       }
     }
+  } else if (!global) {
+    for (int e = tid; e < n * d; e += NT) sx[(e / d) * Y.ld + e % d] = sq[(e / d) * Y.ld + e % d];
   }
-  if (!global && g == 0) {
-    float kk = 0.f;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) kk += sk[i] * sk[i];
-    kk = block_sum(kk, red);
-    const float ikk = kk > 0.f ? 1.0f / kk : 0.f;
-    for (int e = threadIdx.x; e < d * d; e += blockDim.x) {
-      const int i = e / d, j = e - i * d;
-      Mq[e] += sk[i] * sk[j] * ikk;
+  __syncthreads();
+  // delta = (W^2^T r) s'(z) on the slice's columns (HS / 16 <= 4 tiles, one per wave)
+  if (w < HS / 16) {
+    f4 acc = zero4();
+#pragma unroll
+    for (int s = 0; s < ND; ++s) row_piece(acc, sr, Y.ld, 16 * s, bd[s]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int t = 4 * lg + r, j = w * 16 + lc;
+      sg[t * Y.ls + j] = acc[r] * ssp[t * Y.ls + j];
     }
   }
-  if (global) return;
   __syncthreads();
-  // the slice's share of the local retrieval W2_t s(W1_t x)
-  for (int jj = threadIdx.x; jj < HS; jj += blockDim.x) sa[jj] = act_f<ACT>(sz[jj]);
-  __syncthreads();
-  {
-    const RowJob r1{W2 + j0, d, HS, hid, sa, nullptr, sy, nullptr};
-    const RowJob none{W2, 0, HS, hid, sa, nullptr, sy, nullptr};
-    row_dots_2(r1, none, part);
+
+  // token by token: the gated update, and a local memory's share of W2_t s(W1_t x)
+  float* const share = step_share(a, chain, m);
+  for (int t = 0; t < n; ++t) {
+    const float eta = sgt[t], beta = sgt[STEP_N + t], keep = 1.0f - sgt[2 * STEP_N + t];
+    const f4 kv = reinterpret_cast<const f4*>(sk + t * Y.ld)[tid % g4];
+    const f4 av = reinterpret_cast<const f4*>(sa + t * Y.lh + j0)[tid % h4];
+    float* const zt = sz + (t & 1) * HS;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int jj = (tid + u * NT) / g4;
+      s1[u] = beta * s1[u] - (eta * sg[t * Y.ls + (jj < HS ? jj : 0)]) * kv;
+      w1[u] = keep * w1[u] + s1[u];
+    }
+    if (!global) {
+      const f4 xv = reinterpret_cast<const f4*>(sx + t * Y.ld)[tid % g4];
+      float zp[NU];
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+        zp[u] = w1[u][0] * xv[0] + w1[u][1] * xv[1] + w1[u][2] * xv[2] + w1[u][3] * xv[3];
+      group_sums<NU>(zp, g4);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int e = tid + u * NT;
+        if (e < n4 && e % g4 == 0) zt[e / g4] = act_f<ACT>(zp[u]);
+      }
+      __syncthreads();  // (the other token's sz was last read before this barrier)
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int i = (tid + u * NT) / h4;
+      s2[u] = beta * s2[u] - (eta * sr[t * Y.ld + (i < d ? i : 0)]) * av;
+      w2[u] = keep * w2[u] + s2[u];
+    }
+    if (!global) {
+      const f4 zv = reinterpret_cast<const f4*>(zt)[tid % h4];
+      float y[NU];
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+        y[u] = w2[u][0] * zv[0] + w2[u][1] * zv[1] + w2[u][2] * zv[2] + w2[u][3] * zv[3];
+      group_sums<NU>(y, h4);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int e = tid + u * NT;
+        if (e < n4 && e % h4 == 0) share[((size_t)t * G + g) * d + e / h4] = y[u];
+      }
+    }
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < d; i += blockDim.x) sc.y2[(size_t)g * d + i] = sy[i];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int e = tid + u * NT;
+    if (e < n4) {
+      const size_t o2 = (size_t)(e / h4) * hid + 4 * (e % h4);
+      reinterpret_cast<f4*>(W1)[e] = w1[u];
+      reinterpret_cast<f4*>(S1)[e] = s1[u];
+      *reinterpret_cast<f4*>(W2 + o2) = w2[u];
+      *reinterpret_cast<f4*>(S2 + o2) = s2[u];
+    }
+  }
 }
 
-// o = the global retrieval's shares, then each local memory's (fixed order)
+// blockIdx.y = 0: o = the global retrieval, then each local memory's shares (fixed
+// order); blockIdx.y = 1 + i: local memory i's Q-K sum after the launch's tokens
 template <typename IO>
-__global__ void __launch_bounds__(128) step_k3(StepArgs a) {
-  const int chain = blockIdx.x, d = a.d, G = a.G;
-  IO* o = (IO*)a.o + ((size_t)chain * a.T + a.t) * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    float acc = 0.f;
-    for (int m = 0; m < a.M; ++m) {
-      const StepScr sc = step_scr(a, m, chain);
-      const float* sh = (a.has_global && m == 0) ? sc.yq : sc.y2;
-      for (int gg = 0; gg < G; ++gg) acc += sh[(size_t)gg * d + i];
+__global__ void __launch_bounds__(STEP_THREADS) step_out_kernel(StepArgs a) {
+  __shared__ __align__(16) float sk[STEP_N * STEP_MAX_D];
+  __shared__ float skk[STEP_N];
+  const int chain = blockIdx.x, d = a.d, G = a.G, n = a.n;
+  const size_t tok = ((size_t)chain * a.T + a.t0) * d;
+  if (blockIdx.y == 0) {
+    IO* o = (IO*)a.o + tok;
+    for (int e = threadIdx.x; e < n * d; e += STEP_THREADS) {
+      const int t = e / d, i = e - t * d;
+      float acc = a.has_global ? step_share(a, chain, 0)[e] : 0.f;
+      for (int m = a.has_global; m < a.M; ++m) {
+        const float* sh = step_share(a, chain, m) + (size_t)t * G * d + i;
+        for (int gg = 0; gg < G; ++gg) acc += sh[(size_t)gg * d];
+      }
+      o[e] = from_f<IO>(acc);
     }
-    o[i] = from_f<IO>(acc);
+    return;
+  }
+  const int m = a.has_global + (int)blockIdx.y - 1;
+  f4* M4 = reinterpret_cast<f4*>(a.state + ((size_t)m * a.B * a.H + chain) * a.mem_stride +
+                                 6 * (size_t)a.hid * d);
+  for (int e = threadIdx.x; e < n * d; e += STEP_THREADS) sk[e] = to_f(((const IO*)a.k)[tok + e]);
+  __syncthreads();
+  for (int t = wave_id(); t < n; t += STEP_THREADS / WAVE) {
+    const float ik = inv_norm2(sk + t * d, d);
+    if (lane_id() == 0) skk[t] = ik;
+  }
+  __syncthreads();
+  const int g4 = d / 4;
+  for (int e = threadIdx.x; e < d * g4; e += STEP_THREADS) {
+    const int i = e / g4, c4 = e - i * g4;
+    f4 x = M4[e];
+    for (int t = 0; t < n; ++t) {
+      const f4 kv = reinterpret_cast<const f4*>(sk + t * d)[c4];
+      const float kn = sk[t * d + i] * skk[t];
+#pragma unroll
+      for (int y = 0; y < 4; ++y) x[y] = __builtin_fmaf(kn, kv[y], x[y]);
+    }
+    M4[e] = x;
   }
 }
 
@@ -463,24 +537,46 @@ hipError_t launch_step_init(const StepArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <typename IO, int ACT>
-static hipError_t step_tokens(StepArgs a, hipStream_t st) {
-  const dim3 grid(a.G, a.B * a.H, a.M), block(STEP_THREADS);
-  for (int t = 0; t < a.T; ++t) {
-    a.t = t;
-    hipLaunchKernelGGL((step_k1<IO, ACT>), grid, block, 0, st, a);
-    hipLaunchKernelGGL((step_k2<IO, ACT>), grid, block, 0, st, a);
-    hipLaunchKernelGGL((step_k3<IO>), dim3(a.B * a.H), dim3(128), 0, st, a);
+template <typename IO, int ACT, int D>
+static hipError_t step_run(StepArgs a, hipStream_t st) {
+  const size_t lds = (size_t)step_lds(a.d, a.hid, a.HS).total * sizeof(float);
+  auto kern = step_tokens_kernel<IO, ACT, D>;
+  if (a.d != D || !lds_fits((const void*)kern, lds)) return hipErrorInvalidConfiguration;
+  set_lds_limit((const void*)kern);
+  const int BH = a.B * a.H, nloc = a.M - a.has_global;
+  // tokens whose shares fit a chain's scratch blocks
+  const size_t per = (size_t)a.d * (a.has_global + nloc * a.G);
+  const int most = std::min<int>(STEP_N, (int)((size_t)a.M * a.sc_stride / per));
+  for (int t = 0; t < a.T; t += a.n) {
+    a.t0 = t;
+    a.n = std::min(most, a.T - t);
+    bool bound = false;
+    for (int m = 0; m < a.M; ++m) {  // (a shard starts only where a chunk does)
+      const long long in = (a.pos + t) % a.C[m];
+      bound |= in == 0;
+      a.n = (int)std::min<long long>(a.n, a.C[m] - in);
+    }
+    if (bound) hipLaunchKernelGGL(step_boundary_kernel, dim3(16, BH, a.M), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(kern, dim3(a.G, BH, a.M), dim3(step_threads(D)), lds, st, a);
+    hipLaunchKernelGGL(step_out_kernel<IO>, dim3(BH, 1 + nloc), dim3(STEP_THREADS), 0, st, a);
   }
   return hipGetLastError();
+}
+
+template <typename IO, int ACT>
+static hipError_t step_sizes(const StepArgs& a, hipStream_t st) {
+  return a.d == 16   ? step_run<IO, ACT, 16>(a, st)
+         : a.d == 32 ? step_run<IO, ACT, 32>(a, st)
+         : a.d == 64 ? step_run<IO, ACT, 64>(a, st)
+                     : step_run<IO, ACT, 128>(a, st);
 }
 
 hipError_t launch_step(const StepArgs& a, hipStream_t st) {
   if (a.d > STEP_MAX_D || a.hid > STEP_MAX_H || a.HS > 64 || a.G * a.HS != a.hid || !a.scratch)
     return hipErrorInvalidValue;
   if (a.bf16)
-    return a.act == ACT_SILU ? step_tokens<__bf16, ACT_SILU>(a, st) : step_tokens<__bf16, ACT_GELU>(a, st);
-  return a.act == ACT_SILU ? step_tokens<float, ACT_SILU>(a, st) : step_tokens<float, ACT_GELU>(a, st);
+    return a.act == ACT_SILU ? step_sizes<__bf16, ACT_SILU>(a, st) : step_sizes<__bf16, ACT_GELU>(a, st);
+  return a.act == ACT_SILU ? step_sizes<float, ACT_SILU>(a, st) : step_sizes<float, ACT_GELU>(a, st);
 }
 
 }  // namespace tnt
