@@ -112,7 +112,7 @@ struct Layout {
   // forward workspace
   size_t w_opart, w_tokc, w_chunkc, w_R, w_part, w_gpack, w_gop, w_scr[TNT_MAX_LOCAL],
       w_fsplit[TNT_MAX_LOCAL], w_ring,
-      fwd_bytes;
+      fwd_bytes, fwd_saved_bytes;
   // without a saved buffer, the two-pass local forward's every-slot compute-type
   // state copies and fp32 Q-K states (SIZE_MAX: that memory walks in one pass)
   size_t w_nt[TNT_MAX_LOCAL], w_nm[TNT_MAX_LOCAL], fwd_two_bytes;
@@ -140,8 +140,23 @@ Dims mem_dims(const tnt_config* c, int gsub0, int i) {
     D.qk_proj = 0;
     D.qk_scope = 0;
     D.gsub = gsub0;
+  } else if (D.bf16 && D.d == 64 && D.hid == 256 && D.Cp == 48 && !generic_only()) {
+    // chunks of 33 to 48 rows run on the 64-row instances of the fixed-size kernels
+    // (rows past the chunk are masked): their walks are bound by latency, not by the
+    // rows they multiply.  Forward without saving + recomputing backward at B3 H5
+    // L6144, C_L 48 (GELU): 24.4 ms on the runtime-sized kernels, 4.4 ms here.
+    D.Cp = 64;
   }
   return D;
+}
+
+// Whether the two-pass forward's per-chunk buffer is part of the smallest forward
+// workspace.  Only for the shapes listed here: every other shape's lies past it and
+// is asked for with a saved buffer only, so that a forward without one (the
+// no-allocation call's fixed array above all) needs no more than the one-walk mode.
+bool fsplit_in_min(const Dims& D) {
+  if (!D.bf16 || D.d != 64 || D.hid != 256 || D.Cp - D.C >= 16) return false;
+  return D.act == 1 ? one_of(D.Cp, {16, 32, 64}) : one_of(D.Cp, {16, 64});
 }
 
 Layout layout_of(const tnt_config* c, int gsub0 = 0) {
@@ -213,9 +228,8 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
     y.w_scr[i] = off; off += up((size_t)y.l_units[i] * y.lplan[i].elems * cts);
     const size_t fb = local_fwd_split_bytes(D, y.l_units[i]);
     y.w_fsplit[i] = fb ? off : SIZE_MAX;
-    off += up(fb);
+    if (fsplit_in_min(D)) off += up(fb);
   }
-  const size_t fwd_core = off;
   // two-slot state rings, used when no saved buffer is given
   y.w_ring = off;
   if (c->has_global) { y.ring_g = off; off += up((size_t)y.BH * 2 * 4 * y.hd * f); }
@@ -226,7 +240,13 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
     y.ring_m[i] = off; off += up((size_t)y.l_units[i] * ns * dd * f);
   }
   y.fwd_bytes = off;
-  (void)fwd_core;
+  for (int i = 0; i < c->n_local; ++i) {
+    const Dims D = mem_dims(c, gsub0, i);
+    if (y.w_fsplit[i] == SIZE_MAX || fsplit_in_min(D)) continue;
+    y.w_fsplit[i] = off;
+    off += up(local_fwd_split_bytes(D, y.l_units[i]));
+  }
+  y.fwd_saved_bytes = off;
   // the two-pass local forward without a saved buffer: past the smallest forward
   // workspace (the backward workspace may reuse this space: it never runs a
   // forward without saving)
@@ -239,7 +259,7 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
   y.fwd_two_bytes = off;
 
   // backward workspace (shares the forward's front part for recomputation)
-  off = y.fwd_bytes;
+  off = y.fwd_saved_bytes;
   y.b_dparts = off; off += up(3 * (size_t)y.M * y.io_elems * f);
   if (c->has_global) {
     y.b_adj_g = off; off += up((size_t)y.BH * 2 * 4 * y.hd * f);
@@ -457,7 +477,7 @@ tnt_status run_forward(const tnt_config* c, const Layout& y, const void* q, cons
     a.nslots = (sv || grouped || two_i) ? y.l_chunks[i] + 1 : 2;
     a.fslots = sv ? y.l_fslots[i] : two_i ? 2 : 0;  // two_i: the two-slot fp32 ring
     a.scratch = ws + y.w_scr[i];
-    a.fsplit = y.w_fsplit[i] != SIZE_MAX ? (void*)(ws + y.w_fsplit[i]) : nullptr;
+    a.fsplit = (sv || two_i) && y.w_fsplit[i] != SIZE_MAX ? (void*)(ws + y.w_fsplit[i]) : nullptr;
     a.plan = y.lplan[i];
     a.D = mem_dims(c, y.gsub0, i);
     a.force_generic = generic_only() || grouped;
@@ -778,7 +798,7 @@ size_t tnt_mem_workspace_size(const tnt_config* cfg, int kind) {
   const Eff E = effective(cfg);
   const Layout y = layout_of(&E.c, E.gsub);
   if (kind == TNT_WS_FWD) return y.fwd_two_bytes;
-  if (kind == TNT_WS_FWD_MIN) return y.fwd_bytes;
+  if (kind == TNT_WS_FWD_MIN) return y.fwd_saved_bytes;
   if (kind == TNT_WS_BWD) return y.bwd_bytes;
   if (kind == TNT_WS_BWD_RECOMPUTE) return y.bwd_re_bytes;
   return 0;
@@ -801,6 +821,12 @@ tnt_status tnt_mem_fwd(const tnt_config* cfg, const void* q, const void* k, cons
 }  // extern "C"
 
 namespace tnt {
+size_t forward_unsaved_min(const tnt_config* cfg) {
+  if (validate(cfg) != TNT_OK) return 0;
+  const Eff E = effective(cfg);
+  return layout_of(&E.c, E.gsub).fwd_bytes;
+}
+
 tnt_status forward_entry(const tnt_config* cfg, const void* q, const void* k, const void* v,
                          const float* lr, const float* mom, const float* decay,
                          const float* W1_init, const float* W2_init, void* o,
@@ -818,7 +844,7 @@ tnt_status forward_entry(const tnt_config* cfg, const void* q, const void* k, co
     if (p && misaligned(p)) return TNT_ERR_ALIGN;
   const Eff E = effective(cfg);
   const Layout y = layout_of(&E.c, E.gsub);
-  if (ws_bytes < y.fwd_bytes) return TNT_ERR_WORKSPACE;
+  if (ws_bytes < (saved ? y.fwd_saved_bytes : y.fwd_bytes)) return TNT_ERR_WORKSPACE;
   if (saved && saved_bytes < y.saved_bytes) return TNT_ERR_WORKSPACE;
   const SavedHeader hdr = header_of(cfg, y);
   s = run_forward(&E.c, y, q, k, v, lr, mom, decay, W1_init, W2_init, o, final_state,

@@ -13,4 +13,6 @@ tnt_status forward_entry(const tnt_config* cfg, const void* q, const void* k, co
                          const float* W1_init, const float* W2_init, void* o,
                          float* final_state, void* saved, size_t saved_bytes, void* workspace,
                          size_t ws_bytes, bool fork, hipStream_t stream);
+// Least workspace of a forward without a saved buffer (0: invalid configuration).
+size_t forward_unsaved_min(const tnt_config* cfg);
 }  // namespace tnt

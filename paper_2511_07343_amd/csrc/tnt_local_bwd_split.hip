@@ -1303,7 +1303,9 @@ bool dispatch_split(const LocalBwdArgs* a, const Dims& Dm, int units, void* ws, 
   return try_split<__bf16, __bf16, ACT_SILU, 64, 256, 64>(a, Dm, units, ws, st, err, bytes) ||
          try_split<__bf16, __bf16, ACT_SILU, 64, 256, 32>(a, Dm, units, ws, st, err, bytes) ||
          try_split<__bf16, __bf16, ACT_SILU, 64, 256, 16>(a, Dm, units, ws, st, err, bytes) ||
-         try_split<__bf16, __bf16, ACT_GELU, 64, 256, 64>(a, Dm, units, ws, st, err, bytes);
+         try_split<__bf16, __bf16, ACT_GELU, 64, 256, 64>(a, Dm, units, ws, st, err, bytes) ||
+         try_split<__bf16, __bf16, ACT_GELU, 64, 256, 32>(a, Dm, units, ws, st, err, bytes) ||
+         try_split<__bf16, __bf16, ACT_GELU, 64, 256, 16>(a, Dm, units, ws, st, err, bytes);
 }
 
 bool dispatch_gate(const LocalBwdArgs& a, int units, hipStream_t st, hipError_t* err) {
@@ -1312,7 +1314,9 @@ bool dispatch_gate(const LocalBwdArgs& a, int units, hipStream_t st, hipError_t*
   return try_gate<__bf16, __bf16, ACT_SILU, 64, 256, 64>(a, Dm, units, st, err) ||
          try_gate<__bf16, __bf16, ACT_SILU, 64, 256, 32>(a, Dm, units, st, err) ||
          try_gate<__bf16, __bf16, ACT_SILU, 64, 256, 16>(a, Dm, units, st, err) ||
-         try_gate<__bf16, __bf16, ACT_GELU, 64, 256, 64>(a, Dm, units, st, err);
+         try_gate<__bf16, __bf16, ACT_GELU, 64, 256, 64>(a, Dm, units, st, err) ||
+         try_gate<__bf16, __bf16, ACT_GELU, 64, 256, 32>(a, Dm, units, st, err) ||
+         try_gate<__bf16, __bf16, ACT_GELU, 64, 256, 16>(a, Dm, units, st, err);
 }
 
 }  // namespace

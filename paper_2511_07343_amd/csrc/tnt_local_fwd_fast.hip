@@ -740,6 +740,7 @@ static bool dispatch_fast(const LocalFwdArgs& a, int units, hipStream_t st, hipE
            try_fast<__bf16, __bf16, ACT_SILU, 64, 256, 32>(a, units, st, err, bytes) ||
            try_fast<__bf16, __bf16, ACT_SILU, 64, 256, 16>(a, units, st, err, bytes) ||
            try_fast<__bf16, __bf16, ACT_GELU, 64, 256, 64>(a, units, st, err, bytes) ||
+           try_fast<__bf16, __bf16, ACT_GELU, 64, 256, 32>(a, units, st, err, bytes) ||
            try_fast<__bf16, __bf16, ACT_GELU, 64, 256, 16>(a, units, st, err, bytes);
   }
   return false;  // fp32 shapes (the tiny smoke workload) take the runtime-sized kernel

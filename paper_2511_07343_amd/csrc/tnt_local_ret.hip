@@ -471,6 +471,7 @@ bool launch_local_ret(const LocalFwdArgs& a, int units, hipStream_t st, hipError
          try_ret<__bf16, ACT_SILU, 64, 256, 32>(a, units, st, err) ||
          try_ret<__bf16, ACT_SILU, 64, 256, 16>(a, units, st, err) ||
          try_ret<__bf16, ACT_GELU, 64, 256, 64>(a, units, st, err) ||
+         try_ret<__bf16, ACT_GELU, 64, 256, 32>(a, units, st, err) ||
          try_ret<__bf16, ACT_GELU, 64, 256, 16>(a, units, st, err);
 }
 

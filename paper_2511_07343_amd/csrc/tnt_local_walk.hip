@@ -519,6 +519,7 @@ bool launch_local_walk(const LocalFwdArgs& a, int units, hipStream_t st, hipErro
          try_walk<__bf16, ACT_SILU, 64, 256, 32>(a, units, st, err) ||
          try_walk<__bf16, ACT_SILU, 64, 256, 16>(a, units, st, err) ||
          try_walk<__bf16, ACT_GELU, 64, 256, 64>(a, units, st, err) ||
+         try_walk<__bf16, ACT_GELU, 64, 256, 32>(a, units, st, err) ||
          try_walk<__bf16, ACT_GELU, 64, 256, 16>(a, units, st, err);
 }
 
