@@ -113,6 +113,7 @@ struct Layout {
   size_t w_opart, w_tokc, w_chunkc, w_R, w_part, w_gpack, w_gop, w_scr[TNT_MAX_LOCAL],
       w_fsplit[TNT_MAX_LOCAL], w_ring,
       fwd_bytes, fwd_saved_bytes;
+  bool gop_late;  // w_gop lies past fwd_bytes
   // without a saved buffer, the two-pass local forward's every-slot compute-type
   // state copies and fp32 Q-K states (SIZE_MAX: that memory walks in one pass)
   size_t w_nt[TNT_MAX_LOCAL], w_nm[TNT_MAX_LOCAL], fwd_two_bytes;
@@ -216,7 +217,8 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
     y.w_chunkc = off; off += up((size_t)y.BH * y.g_chunks * 4 * f);
     y.w_R = off; off += up((size_t)y.BH * c->C_G * c->d * f);
     const Dims D = dims_of(c, c->C_G, c->L);
-    const int ns = std::max({global_fwd_splits(D), global_bwd_splits(D), global_blk_splits(D), 1});
+    // (the fixed-size kernels take at most one split per 1024 tokens)
+    const int ns = std::max({global_fwd_splits(D), global_bwd_splits(D), c->C_G / 256, 1});
     y.w_part = off; off += up((size_t)y.BH * ns * 4 * y.hd * f);
     // transposed state copies and the chunk operands of the fixed-size global kernels
     y.w_gpack = off; off += up((size_t)y.BH * 4 * y.hd * cts);
@@ -246,6 +248,13 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
     y.w_fsplit[i] = off;
     off += up(local_fwd_split_bytes(D, y.l_units[i]));
   }
+  // the fixed-size global kernels' chunk operands, padded to whole K slabs: where the
+  // chunk is padded they lie past the smallest forward workspace, too
+  if (c->has_global && global_blk_pad(c->C_G) != c->C_G) {
+    y.w_gop = off;
+    off += up((size_t)y.BH * (2 * (size_t)c->hid + 4 * (size_t)c->d) * global_blk_pad(c->C_G) * cts);
+    y.gop_late = true;
+  }
   y.fwd_saved_bytes = off;
   // the two-pass local forward without a saved buffer: past the smallest forward
   // workspace (the backward workspace may reuse this space: it never runs a
@@ -271,7 +280,7 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
     y.b_gscr = off;
     off += up(global_bwd_scratch_bytes(D, &y.b_gscr_f32));
     y.b_gpackA = off; off += up((size_t)y.BH * 8 * y.hd * cts);  // transposed and as they are
-    y.b_gop = off; off += up((size_t)y.BH * 5 * ((size_t)c->hid + c->d) * c->C_G * cts);
+    y.b_gop = off; off += up((size_t)y.BH * 5 * ((size_t)c->hid + c->d) * global_blk_pad(c->C_G) * cts);
   }
   for (int i = 0; i < c->n_local; ++i) {
     const Dims D = mem_dims(c, gsub0, i);
@@ -511,7 +520,8 @@ tnt_status run_forward(const tnt_config* c, const Layout& y, const void* q, cons
     g.Rbuf = (float*)(ws + y.w_R);
     g.part = (float*)(ws + y.w_part);
     g.packT = ws + y.w_gpack;
-    g.opT = ws + y.w_gop;
+    // without the workspace for padded chunk operands: the runtime-sized kernels
+    g.opT = (!y.gop_late || sv || ws_bytes >= y.fwd_saved_bytes) ? (void*)(ws + y.w_gop) : nullptr;
     g.D = dims_of(c, c->C_G, c->L);
     g.force_generic = generic_only();
     g.skip_final_carry = final_state == nullptr;

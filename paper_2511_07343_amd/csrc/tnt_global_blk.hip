@@ -27,12 +27,23 @@ namespace tnt {
 
 namespace {
 
-// tokens per split of the carry / state GEMMs: GTK_LONG where the chunk length
-// allows (fewer fp32 partials written and read back)
-constexpr int GTK = 256, GTK_LONG = 1024;
 // K slab of the LDS-staged carry GEMMs (tokens per round trip)
 constexpr int GCARRY_KT = 128;
-inline int gtk_of(int C) { return C % GTK_LONG == 0 ? GTK_LONG : GTK; }
+// A chunk's operand rows (opT) are padded to whole slabs: the token tiles write zeros
+// past the chunk, so every chunk length takes these kernels.
+__host__ __device__ inline int gpad(int C) { return (C + GCARRY_KT - 1) / GCARRY_KT * GCARRY_KT; }
+// tokens per split of the carry / state GEMMs: at most 1024 (fewer fp32 partials
+// written and read back than with short splits), whole slabs, the splits even
+inline int gtk_of(int C) {
+  const int slabs = gpad(C) / GCARRY_KT, ns = (slabs + 7) / 8;
+  return (slabs + ns - 1) / ns * GCARRY_KT;
+}
+// rows (hidden units) of a state matrix that one workgroup of those GEMMs takes: all
+// of them up to 256 x 64 outputs, 128 of them at 512 x 128 (the wave's accumulators)
+template <int D, int H>
+constexpr int gpiece() {
+  return H * D > 16384 ? 128 : H;
+}
 
 template <int H>
 constexpr int gtile_rows() {
@@ -54,6 +65,15 @@ __device__ __forceinline__ void gload8<float>(const float* p, float (&x)[8]) {
   for (int t = 0; t < 4; ++t) {
     x[t] = u[t];
     x[t + 4] = v[t];
+  }
+}
+template <typename IO>
+__device__ __forceinline__ void gload8_or0(const IO* p, float (&x)[8], bool in) {
+  if (in) {
+    gload8(p, x);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) x[t] = 0.f;
   }
 }
 template <typename CT>
@@ -175,7 +195,7 @@ constexpr size_t gfwd_tile_lds() {  // padded rows, compute type (2 bytes)
              : (size_t)gtile_rows<H>() * (D + 8) + (size_t)gtile_rows<H>() * (H + 8)) * 2;
 }
 
-template <typename IO, typename CT, int ACT, int D, int H, bool KS>
+template <typename IO, typename CT, int ACT, int D, int H, bool KS, bool PAD>
 __global__ void __launch_bounds__(512) gfwd_tile_kernel(GlobalArgs a, int n) {
   constexpr int TT = gtile_rows<H>();
   // rows padded by 16 bytes: the 16-byte operand reads of consecutive rows do
@@ -189,8 +209,10 @@ __global__ void __launch_bounds__(512) gfwd_tile_kernel(GlobalArgs a, int n) {
   CT* sSp = sHk + TT * LH;               // [TT][LH]  s'(Zk)   (KS only)
   __shared__ float cC[TT], bb[TT];
   const Dims Dm = a.D;
-  const int C = Dm.C;
+  const int Ct = Dm.C, C = PAD ? gpad(Ct) : Ct;  // tokens of the chunk, its padded rows
   const int chain = blockIdx.y, r0 = blockIdx.x * TT;
+  // tokens of this tile (none in a tile of padding); PAD = false: whole tiles only
+  const int rows = PAD ? min(TT, Ct - r0) : TT;
   constexpr size_t hd = (size_t)H * D;
   // the chunk-entry state in bf16: V1^T [D][H], V2^T [H][D], V1 [H][D], V2 [D][H]
   const CT* pS = (const CT*)a.packT + (size_t)chain * 4 * hd;
@@ -198,7 +220,7 @@ __global__ void __launch_bounds__(512) gfwd_tile_kernel(GlobalArgs a, int n) {
   CT* op = (CT*)a.opT + (size_t)chain * (2 * (size_t)H + 4 * (size_t)D) * C;
   CT *D1T = op, *HkT = D1T + (size_t)H * C, *KcT = HkT + (size_t)H * C, *KbT = KcT + (size_t)D * C,
      *RcT = KbT + (size_t)D * C, *RbT = RcT + (size_t)D * C;
-  const size_t tok0 = (size_t)n * C + r0;
+  const size_t tok0 = (size_t)n * Ct + r0;
   const size_t cb = (size_t)chain * Dm.L + tok0;
   const IO* q = (const IO*)a.q + cb * D;
   const IO* k = (const IO*)a.k + cb * D;
@@ -208,18 +230,19 @@ __global__ void __launch_bounds__(512) gfwd_tile_kernel(GlobalArgs a, int n) {
   const float rscale = 2.0f / (float)D;
 
   if (threadIdx.x < TT) {
-    cC[threadIdx.x] = tk[(size_t)threadIdx.x * TKS + 0];
-    bb[threadIdx.x] = tk[(size_t)threadIdx.x * TKS + 1];
+    const bool in = !PAD || (int)threadIdx.x < rows;
+    cC[threadIdx.x] = in ? tk[(size_t)threadIdx.x * TKS + 0] : 0.f;
+    bb[threadIdx.x] = in ? tk[(size_t)threadIdx.x * TKS + 1] : 0.f;
   }
   __syncthreads();
   for (int e = threadIdx.x; e < TT * (D / 8); e += blockDim.x) {
     const int i = e % TT, j0 = (e / TT) * 8;
     float qx[8];
-    gload8(q + (size_t)i * D + j0, qx);
+    gload8_or0(q + (size_t)i * D + j0, qx, !PAD || i < rows);
     gstore8<CT>(sQ + (size_t)i * LD + j0, qx);
     if constexpr (KS) {
       float kx[8];
-      gload8(k + (size_t)i * D + j0, kx);
+      gload8_or0(k + (size_t)i * D + j0, kx, !PAD || i < rows);
       gstore8<CT>(sK + (size_t)i * LD + j0, kx);
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
@@ -274,15 +297,16 @@ __global__ void __launch_bounds__(512) gfwd_tile_kernel(GlobalArgs a, int n) {
       for (int r = 0; r < 4; ++r) {
         const int ii = i + r;
         const size_t e = (size_t)ii * D + j;
+        const bool in = !PAD || ii < rows;
         if (KS || !a.o_final) {
-          o[e] = ao[rb][cb_][r];
-        } else {  // the layer output: every memory's part in the fixed order
+          if (in) o[e] = ao[rb][cb_][r];
+        } else if (in) {  // the layer output: every memory's part in the fixed order
           float sv = ao[rb][cb_][r];
           for (int p = 1; p < a.o_nparts; ++p) sv += o[p * a.o_stride + e];
           reinterpret_cast<IO*>(a.o_final)[cb * D + e] = from_f<IO>(sv);
         }
         if constexpr (KS) {
-          const float rv = rscale * (ay[rb][cb_][r] - to_f(v[e]));
+          const float rv = in ? rscale * (ay[rb][cb_][r] - to_f(v[e])) : 0.f;
           sR[(size_t)ii * LD + j] = from_f<CT>(rv);
           rc[r] = cC[ii] * rv;
           rbv[r] = bb[ii] * rv;
@@ -395,42 +419,45 @@ __device__ __forceinline__ void lds_gemm_nt(f4 (&acc)[RB][CB], int i0, int j0,
 //   m = 0: D1^T (cC K) -> V1 slot,  m = 1: D1^T (b K) -> S1 slot   (hid x d)
 //   m = 2: (cC R)^T Hk -> V2 slot,  m = 3: (b R)^T Hk -> S2 slot   (d x hid)
 // ---------------------------------------------------------------------------
-template <typename CT, int D, int H, int TK>
-__global__ void __launch_bounds__(512) gfwd_carry_kernel(GlobalArgs a) {
+template <typename CT, int D, int H>
+__global__ void __launch_bounds__(512) gfwd_carry_kernel(GlobalArgs a, int TK) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int split = blockIdx.x, m = blockIdx.y, chain = blockIdx.z, ns = gridDim.x;
-  const int C = a.D.C;
+  constexpr int MP = gpiece<D, H>(), NP = H / MP;
+  const int split = blockIdx.x, m = blockIdx.y / NP, h0 = (blockIdx.y % NP) * MP;
+  const int chain = blockIdx.z, ns = gridDim.x;
+  const int C = gpad(a.D.C);
   constexpr size_t hd = (size_t)H * D;
   const CT* op = (const CT*)a.opT + (size_t)chain * (2 * (size_t)H + 4 * (size_t)D) * C;
   const CT *D1T = op, *HkT = D1T + (size_t)H * C, *KcT = HkT + (size_t)H * C,
            *KbT = KcT + (size_t)D * C, *RcT = KbT + (size_t)D * C, *RbT = RcT + (size_t)D * C;
   const size_t k0 = (size_t)split * TK;
+  const int K = min(TK, C - split * TK);
   float* P = a.part + ((size_t)chain * ns + split) * 4 * hd;
   CT* lds = reinterpret_cast<CT*>(smem);
   if (m < 2) {
-    using BK = Blk<H, D>;
+    using BK = Blk<MP, D>;
     static_assert(BK::NB == 8, "one block per wave");
-    const CT* const As[1] = {D1T + k0};
+    const CT* const As[1] = {D1T + (size_t)h0 * C + k0};
     const CT* const Bs[1] = {(m == 0 ? KcT : KbT) + k0};
-    float* out = P + (m == 0 ? 0 : 2 * hd);
+    float* out = P + (m == 0 ? 0 : 2 * hd) + (size_t)h0 * D;
     const int i0 = (wave_id() / BK::NBN) * BK::RB * 16, j0 = (wave_id() % BK::NBN) * BK::CB * 16;
     f4 acc[BK::RB][BK::CB];
     zero_blk(acc);
-    lds_gemm_nt<CT, H, D, GCARRY_KT, 1>(acc, i0, j0, As, Bs, C, TK, lds);
+    lds_gemm_nt<CT, MP, D, GCARRY_KT, 1>(acc, i0, j0, As, Bs, C, K, lds);
     blk_each4<BK::RB, BK::CB>(i0, j0, [&](int rb, int cb_, int i, int j) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) out[(size_t)(i + r) * D + j] = acc[rb][cb_][r];
     });
   } else {
-    using BK = Blk<D, H>;
+    using BK = Blk<D, MP>;
     static_assert(BK::NB == 8, "one block per wave");
     const CT* const As[1] = {(m == 2 ? RcT : RbT) + k0};
-    const CT* const Bs[1] = {HkT + k0};
-    float* out = P + (m == 2 ? hd : 3 * hd);
+    const CT* const Bs[1] = {HkT + (size_t)h0 * C + k0};
+    float* out = P + (m == 2 ? hd : 3 * hd) + h0;
     const int i0 = (wave_id() / BK::NBN) * BK::RB * 16, j0 = (wave_id() % BK::NBN) * BK::CB * 16;
     f4 acc[BK::RB][BK::CB];
     zero_blk(acc);
-    lds_gemm_nt<CT, D, H, GCARRY_KT, 1>(acc, i0, j0, As, Bs, C, TK, lds);
+    lds_gemm_nt<CT, D, MP, GCARRY_KT, 1>(acc, i0, j0, As, Bs, C, K, lds);
     blk_each4<BK::RB, BK::CB>(i0, j0, [&](int rb, int cb_, int i, int j) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) out[(size_t)(i + r) * H + j] = acc[rb][cb_][r];
@@ -441,7 +468,7 @@ __global__ void __launch_bounds__(512) gfwd_carry_kernel(GlobalArgs a) {
 // ---------------------------------------------------------------------------
 // backward, token tiles of TT rows of chunk n (exit adjoint in slot (n+1)&1)
 // ---------------------------------------------------------------------------
-template <typename IO, typename CT, int ACT, int D, int H>
+template <typename IO, typename CT, int ACT, int D, int H, bool PAD>
 __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
   constexpr int TT = gtile_rows<H>();
   constexpr int TN = D / 16;
@@ -458,8 +485,10 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
   __shared__ float cC[TT], bb[TT];
   __shared__ float gp[2][TN][TT];
   const Dims Dm = a.D;
-  const int C = Dm.C;
+  const int Ct = Dm.C, C = PAD ? gpad(Ct) : Ct;  // tokens of the chunk, its padded rows
   const int chain = blockIdx.y, r0 = blockIdx.x * TT;
+  // tokens of this tile (none in a tile of padding); PAD = false: whole tiles only
+  const int rows = PAD ? min(TT, Ct - r0) : TT;
   constexpr size_t hd = (size_t)H * D;
   // bf16 copies of the chunk-entry state and the exit adjoint, transposed and as they are
   const CT* pS = (const CT*)a.packT + (size_t)chain * 4 * hd;
@@ -472,7 +501,7 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
      *HkT = GbT + (size_t)H * C, *HqT = HkT + (size_t)H * C, *KT = HqT + (size_t)H * C,
      *QT = KT + (size_t)D * C, *RT = QT + (size_t)D * C, *YkbT = RT + (size_t)D * C,
      *dOT = YkbT + (size_t)D * C;
-  const size_t tok0 = (size_t)n * C + r0;
+  const size_t tok0 = (size_t)n * Ct + r0;
   const size_t cb = (size_t)chain * Dm.L + tok0;
   const IO* q = (const IO*)a.q + cb * D;
   const IO* k = (const IO*)a.k + cb * D;
@@ -487,15 +516,16 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
   const int l = lane_id();
 
   if (threadIdx.x < TT) {
-    cC[threadIdx.x] = tk[(size_t)threadIdx.x * TKS + 0];
-    bb[threadIdx.x] = tk[(size_t)threadIdx.x * TKS + 1];
+    const bool in = !PAD || (int)threadIdx.x < rows;
+    cC[threadIdx.x] = in ? tk[(size_t)threadIdx.x * TKS + 0] : 0.f;
+    bb[threadIdx.x] = in ? tk[(size_t)threadIdx.x * TKS + 1] : 0.f;
   }
   for (int e = threadIdx.x; e < TT * (D / 8); e += blockDim.x) {
     const int i = e % TT, j0 = (e / TT) * 8;
     float qx[8], kx[8], ox[8];
-    gload8(q + (size_t)i * D + j0, qx);
-    gload8(k + (size_t)i * D + j0, kx);
-    gload8(dO + (size_t)i * D + j0, ox);
+    gload8_or0(q + (size_t)i * D + j0, qx, !PAD || i < rows);
+    gload8_or0(k + (size_t)i * D + j0, kx, !PAD || i < rows);
+    gload8_or0(dO + (size_t)i * D + j0, ox, !PAD || i < rows);
     gstore8<CT>(sQ + (size_t)i * D + j0, qx);
     gstore8<CT>(sK + (size_t)i * D + j0, kx);
     gstore8<CT>(sdO + (size_t)i * D + j0, ox);
@@ -560,8 +590,9 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const size_t e = (size_t)(i + r) * D + j;
-        rv[r] = rscale * (ay[rb][cb_][r] - to_f(v[e]));
-        dqp[e] = aq[rb][cb_][r];
+        const bool in = !PAD || i + r < rows;
+        rv[r] = in ? rscale * (ay[rb][cb_][r] - to_f(v[e])) : 0.f;
+        if (in) dqp[e] = aq[rb][cb_][r];
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) sR[(size_t)(i + r) * D + j] = from_f<CT>(rv[r]);  // Q is dead
@@ -615,7 +646,7 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
         const float rbv = -cC[ii] * t5[rb][cb_][r] - bb[ii] * t6[rb][cb_][r] + ag[rb][cb_][r];
         yv[r] = rscale * rbv;
         sYkb[e] = from_f<CT>(yv[r]);
-        dvp[e] = -yv[r];
+        if (!PAD || ii < rows) dvp[e] = -yv[r];
         const float kx = to_f(sK[e]), rx = to_f(sR[e]);
         const float s1 = gsum16(kx * t3[rb][cb_][r] + rx * t5[rb][cb_][r]);
         const float s2 = gsum16(kx * t4[rb][cb_][r] + rx * t6[rb][cb_][r]);
@@ -628,7 +659,7 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
     });
   }
   __syncthreads();
-  if (threadIdx.x < TT) {
+  if ((int)threadIdx.x < rows) {
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int t = 0; t < TN; ++t) {
@@ -671,7 +702,7 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int ii = i + r;
-        dkp[(size_t)ii * D + j] =
+        if (!PAD || ii < rows) dkp[(size_t)ii * D + j] =
             -cC[ii] * t3[rb][cb_][r] - bb[ii] * t4[rb][cb_][r] + ak[rb][cb_][r];
       }
     });
@@ -685,7 +716,7 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
 // Zqbar = (dO V2) * s'(Zq), dq = Zqbar V1, with the operands of the entry-adjoint
 // products that do not vanish (Zqbar^T Q, dO^T Hq)
 // ---------------------------------------------------------------------------
-template <typename IO, typename CT, int ACT, int D, int H>
+template <typename IO, typename CT, int ACT, int D, int H, bool PAD>
 __global__ void __launch_bounds__(512) gbwd_tile_last_kernel(GlobalArgs a, int n) {
   constexpr int TT = gtile_rows<H>();
   extern __shared__ __align__(16) unsigned char smem[];
@@ -693,15 +724,17 @@ __global__ void __launch_bounds__(512) gbwd_tile_last_kernel(GlobalArgs a, int n
   CT* sdO = sQ + TT * D;                 // [TT][D]
   CT* sZqb = sdO + TT * D;               // [TT][H]
   const Dims Dm = a.D;
-  const int C = Dm.C;
+  const int Ct = Dm.C, C = PAD ? gpad(Ct) : Ct;  // tokens of the chunk, its padded rows
   const int chain = blockIdx.y, r0 = blockIdx.x * TT;
+  // tokens of this tile (none in a tile of padding); PAD = false: whole tiles only
+  const int rows = PAD ? min(TT, Ct - r0) : TT;
   constexpr size_t hd = (size_t)H * D;
   const CT* pS = (const CT*)a.packT + (size_t)chain * 4 * hd;
   const CT *V1T = pS, *V2T = pS + hd, *V1 = pS + 2 * hd;
   CT* op = (CT*)a.opT + (size_t)chain * 5 * ((size_t)H + D) * C;
   CT *ZqbT = op + (size_t)H * C, *HqT = op + 4 * (size_t)H * C, *QT = op + 5 * (size_t)H * C + (size_t)D * C,
      *dOT = op + 5 * (size_t)H * C + 4 * (size_t)D * C;
-  const size_t tok0 = (size_t)n * C + r0;
+  const size_t tok0 = (size_t)n * Ct + r0;
   const size_t cb = (size_t)chain * Dm.L + tok0;
   const IO* q = (const IO*)a.q + cb * D;
   const IO* dO = (const IO*)a.dO + cb * D;
@@ -713,8 +746,8 @@ __global__ void __launch_bounds__(512) gbwd_tile_last_kernel(GlobalArgs a, int n
   for (int e = threadIdx.x; e < TT * (D / 8); e += blockDim.x) {
     const int i = e % TT, j0 = (e / TT) * 8;
     float qx[8], ox[8];
-    gload8(q + (size_t)i * D + j0, qx);
-    gload8(dO + (size_t)i * D + j0, ox);
+    gload8_or0(q + (size_t)i * D + j0, qx, !PAD || i < rows);
+    gload8_or0(dO + (size_t)i * D + j0, ox, !PAD || i < rows);
     gstore8<CT>(sQ + (size_t)i * D + j0, qx);
     gstore8<CT>(sdO + (size_t)i * D + j0, ox);
 #pragma unroll
@@ -724,11 +757,11 @@ __global__ void __launch_bounds__(512) gbwd_tile_last_kernel(GlobalArgs a, int n
       dOT[et] = from_f<CT>(ox[t]);
     }
   }
-  for (int e = threadIdx.x * 4; e < TT * D; e += blockDim.x * 4) {
+  for (int e = threadIdx.x * 4; e < rows * D; e += blockDim.x * 4) {
     *reinterpret_cast<f32x4*>(dkp + e) = f32x4{0.f, 0.f, 0.f, 0.f};
     *reinterpret_cast<f32x4*>(dvp + e) = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  if (threadIdx.x < TT) {
+  if ((int)threadIdx.x < rows) {
     dtk[(size_t)threadIdx.x * 4 + 0] = 0.f;
     dtk[(size_t)threadIdx.x * 4 + 1] = 0.f;
   }
@@ -764,7 +797,8 @@ __global__ void __launch_bounds__(512) gbwd_tile_last_kernel(GlobalArgs a, int n
     mma_blk<CT, KC, KC, BD::RB, BD::CB, H>(aq, sZqb, H, i0, V1T, H, j0);
     blk_each4<BD::RB, BD::CB>(i0, j0, [&](int rb, int cb_, int i, int j) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) dqp[(size_t)(i + r) * D + j] = aq[rb][cb_][r];
+      for (int r = 0; r < 4; ++r)
+        if (!PAD || i + r < rows) dqp[(size_t)(i + r) * D + j] = aq[rb][cb_][r];
     });
   });
 }
@@ -776,57 +810,60 @@ __global__ void __launch_bounds__(512) gbwd_tile_last_kernel(GlobalArgs a, int n
 // ---------------------------------------------------------------------------
 // ZA: the chunk's exit adjoint is zero (its key-side operands vanish): only
 // Zqbar^T Q and dO^T Hq remain
-template <typename CT, int D, int H, int TK, bool ZA = false>
-__global__ void __launch_bounds__(512) gbwd_state_kernel(GlobalArgs a) {
+template <typename CT, int D, int H, bool ZA>
+__global__ void __launch_bounds__(512) gbwd_state_kernel(GlobalArgs a, int TK) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int split = blockIdx.x, m = blockIdx.y, chain = blockIdx.z, ns = gridDim.x;
-  const int C = a.D.C;
+  constexpr int MP = gpiece<D, H>(), NP = H / MP;
+  const int split = blockIdx.x, m = blockIdx.y / NP, h0 = (blockIdx.y % NP) * MP;
+  const int chain = blockIdx.z, ns = gridDim.x;
+  const int C = gpad(a.D.C);
+  const int K = min(TK, C - split * TK);
   constexpr size_t hd = (size_t)H * D;
   const CT* op = (const CT*)a.opT + (size_t)chain * 5 * ((size_t)H + D) * C;
   const CT *ZkbT = op, *ZqbT = ZkbT + (size_t)H * C, *GbT = ZqbT + (size_t)H * C,
            *HkT = GbT + (size_t)H * C, *HqT = HkT + (size_t)H * C, *KT = HqT + (size_t)H * C,
            *QT = KT + (size_t)D * C, *RT = QT + (size_t)D * C, *YkbT = RT + (size_t)D * C,
            *dOT = YkbT + (size_t)D * C;
-  const size_t k0 = (size_t)split * TK;
+  const size_t k0 = (size_t)split * TK, hr = (size_t)h0 * C;  // hr: the piece's operand rows
   float* P = a.part + ((size_t)chain * ns + split) * 4 * hd;
   CT* lds = reinterpret_cast<CT*>(smem);
   if (m == 0) {
-    using BK = Blk<H, D>;
+    using BK = Blk<MP, D>;
     static_assert(BK::NB == 8, "one block per wave");
     const int i0 = (wave_id() / BK::NBN) * BK::RB * 16, j0 = (wave_id() % BK::NBN) * BK::CB * 16;
     f4 acc[BK::RB][BK::CB];
     zero_blk(acc);
     if constexpr (ZA) {
-      const CT* const As[1] = {ZqbT + k0};
+      const CT* const As[1] = {ZqbT + hr + k0};
       const CT* const Bs[1] = {QT + k0};
-      lds_gemm_nt<CT, H, D, GCARRY_KT, 1>(acc, i0, j0, As, Bs, C, TK, lds);
+      lds_gemm_nt<CT, MP, D, GCARRY_KT, 1>(acc, i0, j0, As, Bs, C, K, lds);
     } else {
-      const CT* const As[2] = {ZkbT + k0, ZqbT + k0};
+      const CT* const As[2] = {ZkbT + hr + k0, ZqbT + hr + k0};
       const CT* const Bs[2] = {KT + k0, QT + k0};
-      lds_gemm_nt<CT, H, D, GCARRY_KT, 2>(acc, i0, j0, As, Bs, C, TK, lds);
+      lds_gemm_nt<CT, MP, D, GCARRY_KT, 2>(acc, i0, j0, As, Bs, C, K, lds);
     }
     blk_each4<BK::RB, BK::CB>(i0, j0, [&](int rb, int cb_, int i, int j) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) P[(size_t)(i + r) * D + j] = acc[rb][cb_][r];
+      for (int r = 0; r < 4; ++r) P[(size_t)(h0 + i + r) * D + j] = acc[rb][cb_][r];
     });
   } else {
-    using BK = Blk<D, H>;
+    using BK = Blk<D, MP>;
     static_assert(BK::NB == 8, "one block per wave");
     const int i0 = (wave_id() / BK::NBN) * BK::RB * 16, j0 = (wave_id() % BK::NBN) * BK::CB * 16;
     f4 acc[BK::RB][BK::CB];
     zero_blk(acc);
     if constexpr (ZA) {
       const CT* const As[1] = {dOT + k0};
-      const CT* const Bs[1] = {HqT + k0};
-      lds_gemm_nt<CT, D, H, GCARRY_KT, 1>(acc, i0, j0, As, Bs, C, TK, lds);
+      const CT* const Bs[1] = {HqT + hr + k0};
+      lds_gemm_nt<CT, D, MP, GCARRY_KT, 1>(acc, i0, j0, As, Bs, C, K, lds);
     } else {
       const CT* const As[3] = {RT + k0, YkbT + k0, dOT + k0};
-      const CT* const Bs[3] = {GbT + k0, HkT + k0, HqT + k0};
-      lds_gemm_nt<CT, D, H, GCARRY_KT, 3>(acc, i0, j0, As, Bs, C, TK, lds);
+      const CT* const Bs[3] = {GbT + hr + k0, HkT + hr + k0, HqT + hr + k0};
+      lds_gemm_nt<CT, D, MP, GCARRY_KT, 3>(acc, i0, j0, As, Bs, C, K, lds);
     }
     blk_each4<BK::RB, BK::CB>(i0, j0, [&](int rb, int cb_, int i, int j) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) P[hd + (size_t)(i + r) * H + j] = acc[rb][cb_][r];
+      for (int r = 0; r < 4; ++r) P[hd + (size_t)(i + r) * H + h0 + j] = acc[rb][cb_][r];
     });
   }
 }
@@ -836,8 +873,7 @@ __global__ void __launch_bounds__(512) gbwd_state_kernel(GlobalArgs a) {
 // ---------------------------------------------------------------------------
 template <int D, int H>
 static bool gblk_shape(const GlobalArgs& a) {
-  return a.D.bf16 && a.D.d == D && a.D.hid == H && a.D.C % GTK == 0 &&
-         a.D.C % gtile_rows<H>() == 0 && a.packT && a.opT;
+  return a.D.bf16 && a.D.d == D && a.D.hid == H && a.packT && a.opT;
 }
 
 template <typename IO, typename ACT_T, int ACT, int D, int H>
@@ -845,6 +881,7 @@ static hipError_t gfwd_blk_chunk(const GlobalArgs& a, int n, hipStream_t st) {
   typedef __bf16 CT;
   constexpr int TT = gtile_rows<H>();
   const int chains = a.D.B * a.D.H, C = a.D.C;
+  const bool pad = gpad(C) != C;  // masks in the tiles of padded chunks only
   constexpr size_t hd = (size_t)H * D;
   // chunk 0's state copies; every later chunk's are written by the reduction
   // that forms its state
@@ -861,29 +898,27 @@ static hipError_t gfwd_blk_chunk(const GlobalArgs& a, int n, hipStream_t st) {
       hipError_t e = b.parts_ready ? hipStreamWaitEvent(st, b.parts_ready, 0) : hipErrorInvalidValue;
       if (e != hipSuccess) b.o_final = nullptr;  // no fused sum (the caller sums)
     }
-    auto kq = gfwd_tile_kernel<IO, CT, ACT, D, H, false>;
+    auto kq = pad ? gfwd_tile_kernel<IO, CT, ACT, D, H, false, true> : gfwd_tile_kernel<IO, CT, ACT, D, H, false, false>;
     set_lds_limit((const void*)kq);
-    hipLaunchKernelGGL(kq, dim3(C / TT, chains), dim3(512), (gfwd_tile_lds<D, H, false>()), st, b, n);
+    hipLaunchKernelGGL(kq, dim3(gpad(C) / TT, chains), dim3(512), (gfwd_tile_lds<D, H, false>()), st, b, n);
     if (b.o_final && b.o_fused) *b.o_fused = 1;
     return hipGetLastError();
   }
-  auto k1 = gfwd_tile_kernel<IO, CT, ACT, D, H, true>;
+  auto k1 = pad ? gfwd_tile_kernel<IO, CT, ACT, D, H, true, true> : gfwd_tile_kernel<IO, CT, ACT, D, H, true, false>;
   set_lds_limit((const void*)k1);
-  hipLaunchKernelGGL(k1, dim3(C / TT, chains), dim3(512), (gfwd_tile_lds<D, H, true>()), st, a, n);
+  hipLaunchKernelGGL(k1, dim3(gpad(C) / TT, chains), dim3(512), (gfwd_tile_lds<D, H, true>()), st, a, n);
   if (a.tile_done && n == a.tile_done_n) {
     const hipError_t e = hipEventRecord(a.tile_done, st);
     if (e != hipSuccess) return e;
     if (a.tile_recorded) *a.tile_recorded = 1;
   }
-  const int tk = gtk_of(C), ns = C / tk;
+  const int tk = gtk_of(C), ns = (gpad(C) + tk - 1) / tk;
   const int sec = section_begin("global_carry", st);
-  constexpr size_t lc = lds_gemm_bytes<CT, H, D, GCARRY_KT, 1>();
-  set_lds_limit((const void*)gfwd_carry_kernel<CT, D, H, GTK_LONG>);
-  set_lds_limit((const void*)gfwd_carry_kernel<CT, D, H, GTK>);
-  if (tk == GTK_LONG)
-    hipLaunchKernelGGL((gfwd_carry_kernel<CT, D, H, GTK_LONG>), dim3(ns, 4, chains), dim3(512), lc, st, a);
-  else
-    hipLaunchKernelGGL((gfwd_carry_kernel<CT, D, H, GTK>), dim3(ns, 4, chains), dim3(512), lc, st, a);
+  constexpr int MP = gpiece<D, H>();
+  constexpr size_t lc = lds_gemm_bytes<CT, MP, D, GCARRY_KT, 1>();
+  auto k2 = gfwd_carry_kernel<CT, D, H>;
+  set_lds_limit((const void*)k2);
+  hipLaunchKernelGGL(k2, dim3(ns, 4 * (H / MP), chains), dim3(512), lc, st, a, tk);
   hipLaunchKernelGGL(gcarry_reduce_pack_kernel<CT>, dim3((unsigned)(hd / 1024), chains, 2), dim3(256), 0,
                      st, a, n, ns);
   section_end(sec, st);
@@ -895,6 +930,7 @@ static hipError_t gbwd_blk_chunk(const GlobalArgs& a, int n, hipStream_t st) {
   typedef __bf16 CT;
   constexpr int TT = gtile_rows<H>();
   const int chains = a.D.B * a.D.H, C = a.D.C;
+  const bool pad = gpad(C) != C;  // masks in the tiles of padded chunks only
   constexpr size_t hd = (size_t)H * D;
   // the last chunk (walked first) leaves with a zero adjoint: its tile and
   // state products keep only the terms that do not vanish
@@ -903,58 +939,55 @@ static hipError_t gbwd_blk_chunk(const GlobalArgs& a, int n, hipStream_t st) {
                         4 * hd, (CT*)a.packT + 2 * hd, 4 * hd, chains, D, H, 0x3, st);
   if (za) {
     const size_t lz = (2 * (size_t)TT * D + (size_t)TT * H) * sizeof(CT);
-    hipLaunchKernelGGL((gbwd_tile_last_kernel<IO, CT, ACT, D, H>), dim3(C / TT, chains), dim3(512), lz,
-                       st, a, n);
+    auto kz = pad ? gbwd_tile_last_kernel<IO, CT, ACT, D, H, true> : gbwd_tile_last_kernel<IO, CT, ACT, D, H, false>;
+    hipLaunchKernelGGL(kz, dim3(gpad(C) / TT, chains), dim3(512), lz, st, a, n);
   } else {
     launch_gtranspose<CT>(a.adj + (size_t)((n + 1) & 1) * 4 * hd, 2 * 4 * hd, (CT*)a.packA, 8 * hd,
                           (CT*)a.packA + 4 * hd, 8 * hd, chains, D, H, 0xf, st);
     const size_t l1 = (3 * (size_t)TT * D + 4 * (size_t)TT * H) * sizeof(CT);
-    auto k1 = gbwd_tile_kernel<IO, CT, ACT, D, H>;
+    auto k1 = pad ? gbwd_tile_kernel<IO, CT, ACT, D, H, true> : gbwd_tile_kernel<IO, CT, ACT, D, H, false>;
     set_lds_limit((const void*)k1);
-    hipLaunchKernelGGL(k1, dim3(C / TT, chains), dim3(512), l1, st, a, n);
+    hipLaunchKernelGGL(k1, dim3(gpad(C) / TT, chains), dim3(512), l1, st, a, n);
   }
-  const int tk = gtk_of(C), ns = C / tk;
+  const int tk = gtk_of(C), ns = (gpad(C) + tk - 1) / tk;
   const int sec = section_begin("global_bwd_carry", st);
-  constexpr size_t ls = lds_gemm_bytes<CT, H, D, GCARRY_KT, 1>();
-  set_lds_limit((const void*)gbwd_state_kernel<CT, D, H, GTK>);
-  set_lds_limit((const void*)gbwd_state_kernel<CT, D, H, GTK_LONG>);
-  set_lds_limit((const void*)gbwd_state_kernel<CT, D, H, GTK, true>);
-  set_lds_limit((const void*)gbwd_state_kernel<CT, D, H, GTK_LONG, true>);
-  const dim3 gs(ns, 2, chains);
-  if (tk == GTK_LONG && za)
-    hipLaunchKernelGGL((gbwd_state_kernel<CT, D, H, GTK_LONG, true>), gs, dim3(512), ls, st, a);
-  else if (tk == GTK_LONG)
-    hipLaunchKernelGGL((gbwd_state_kernel<CT, D, H, GTK_LONG>), gs, dim3(512), ls, st, a);
-  else if (za)
-    hipLaunchKernelGGL((gbwd_state_kernel<CT, D, H, GTK, true>), gs, dim3(512), ls, st, a);
-  else
-    hipLaunchKernelGGL((gbwd_state_kernel<CT, D, H, GTK>), gs, dim3(512), ls, st, a);
+  constexpr int MP = gpiece<D, H>();
+  constexpr size_t ls = lds_gemm_bytes<CT, MP, D, GCARRY_KT, 1>();
+  auto k2 = za ? gbwd_state_kernel<CT, D, H, true> : gbwd_state_kernel<CT, D, H, false>;
+  set_lds_limit((const void*)k2);
+  hipLaunchKernelGGL(k2, dim3(ns, 2 * (H / MP), chains), dim3(512), ls, st, a, tk);
   const hipError_t e = launch_gbwd_state_reduce(a, n, ns, st);
   section_end(sec, st);
   return e;
 }
 
+template <int D, int H>
+static bool try_gfwd(const GlobalArgs& a, int n, hipStream_t st, hipError_t* err) {
+  if (!gblk_shape<D, H>(a)) return false;
+  *err = a.D.act == ACT_SILU ? gfwd_blk_chunk<__bf16, void, ACT_SILU, D, H>(a, n, st)
+                             : gfwd_blk_chunk<__bf16, void, ACT_GELU, D, H>(a, n, st);
+  return true;
+}
+template <int D, int H>
+static bool try_gbwd(const GlobalArgs& a, int n, hipStream_t st, hipError_t* err) {
+  if (!gblk_shape<D, H>(a)) return false;
+  *err = a.D.act == ACT_SILU ? gbwd_blk_chunk<__bf16, void, ACT_SILU, D, H>(a, n, st)
+                             : gbwd_blk_chunk<__bf16, void, ACT_GELU, D, H>(a, n, st);
+  return true;
+}
+
 bool launch_global_fwd_blk(const GlobalArgs& a, int n, hipStream_t st, hipError_t* err) {
   if (a.force_generic) return false;
-  if (gblk_shape<64, 256>(a)) {
-    *err = a.D.act == ACT_SILU ? gfwd_blk_chunk<__bf16, void, ACT_SILU, 64, 256>(a, n, st)
-                               : gfwd_blk_chunk<__bf16, void, ACT_GELU, 64, 256>(a, n, st);
-    return true;
-  }
-  return false;
+  return try_gfwd<64, 256>(a, n, st, err) || try_gfwd<128, 512>(a, n, st, err) ||
+         try_gfwd<64, 128>(a, n, st, err) || try_gfwd<32, 128>(a, n, st, err);
 }
 
 bool launch_global_bwd_blk(const GlobalArgs& a, int n, hipStream_t st, hipError_t* err) {
   if (a.force_generic || !a.packA) return false;
-  if (gblk_shape<64, 256>(a)) {
-    *err = a.D.act == ACT_SILU ? gbwd_blk_chunk<__bf16, void, ACT_SILU, 64, 256>(a, n, st)
-                               : gbwd_blk_chunk<__bf16, void, ACT_GELU, 64, 256>(a, n, st);
-    return true;
-  }
-  return false;
+  return try_gbwd<64, 256>(a, n, st, err) || try_gbwd<128, 512>(a, n, st, err) ||
+         try_gbwd<64, 128>(a, n, st, err) || try_gbwd<32, 128>(a, n, st, err);
 }
 
-// splits used by the fixed-size path (the partial buffer must hold them)
-int global_blk_splits(const Dims& D) { return D.C / GTK; }  // the larger count of the two
+int global_blk_pad(int C) { return gpad(C); }
 
 }  // namespace tnt
