@@ -616,6 +616,7 @@ tnt_status run_backward(const tnt_config* c, const Layout& y, const void* q, con
     const bool grouped = i == 0 && y.gsub0;
     a.force_generic = generic_only() || grouped;
     a.hadj = grouped ? (float*)(ws + y.b_hadj[i]) : nullptr;
+    a.walks = conc ? c->n_local : 1;
     a.pass_a_done = (fk && i == 0) ? fk->ea : nullptr;
     a.aux = (fk && i == 0) ? fk->side : nullptr;  // ahead of the global chain there
     a.aux_done = (fk && i == 0) ? fk->es : nullptr;

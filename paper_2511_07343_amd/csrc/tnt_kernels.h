@@ -11,7 +11,7 @@ namespace tnt {
 // Header at the start of a saved buffer (tnt_mem_fwd -> tnt_mem_bwd): which
 // layout, kernel family, ring sizes and configuration wrote it.
 constexpr uint32_t SAVED_MAGIC = 0x544e5453u;  // "STNT"
-constexpr uint32_t SAVED_LAYOUT_VERSION = 4;
+constexpr uint32_t SAVED_LAYOUT_VERSION = 5;
 constexpr size_t SAVED_HEADER_BYTES = 256;
 struct SavedHeader {
   uint32_t magic, layout_version, family, pad;
@@ -112,6 +112,7 @@ struct LocalBwdArgs {
   hipEvent_t aux_mid;                                    // with aux: recorded there once the lower
                                                          // half of the chunks has its pass A
   int force_generic;                                     // 1: skip fixed-size kernels
+  int walks;                                             // walks of this call that run side by side
   // Host side: with defer_gate set, the three-pass kernels may leave their gate
   // pass out (setting *gate_deferred) for launch_local_bwd_gate to run later.
   int defer_gate;

@@ -26,7 +26,10 @@
 // the single-walk fixed-size kernel.
 #include "tnt_local_common.h"
 #include "tnt_local_bwd_helpers.h"
+#include "tnt_local_bwd_split.h"
 #include "tnt_local_record.h"
+
+#include <algorithm>
 
 namespace tnt {
 
@@ -126,13 +129,6 @@ constexpr size_t split_c_lds() {
 
 }  // namespace
 
-struct SplitPtrs {
-  void* brec;       // CT   [units * nch][r.bc.n]  backward records
-  float* brec_f;    // fp32 [units * nch][r.bf.n]
-  int units;
-  int n0, nc;       // passes A and B: the chunks n0 .. n0 + nc - 1 of every unit
-};
-
 // ===========================================================================
 // pass A: backward of the retrieval of every chunk, from dO and the forward record
 // ===========================================================================
@@ -202,7 +198,18 @@ local_bwd_ret_kernel(LocalBwdArgs a, SplitPtrs P) {
              *XT = FR_(XT), *N = FR_(N), *NT = FR_(NT), *QT = FR_(QT), *StrT = FR_(StrT);
     const float *fXK = FRF_(XK), *fHH = FRF_(HH), *fHW2 = FRF_(HW2), *fHS2 = FRF_(HS2),
                 *knorm = FRF_(kn);
-    CT *ZbT = BR_(ZbT), *Q1T = BR_(Q1T), *dOT = BR_(dOT), *dOAT = BR_(dOAT), *dOET = BR_(dOET);
+    CT *ZbT = BR_(ZbT), *Q1T = BR_(Q1T), *dOT = BR_(dOT);
+    constexpr bool SC = rec::rec_scaled(CP);  // the one-CU walk's scaled operands
+    CT *const dOAT = SC ? BR_(dOAT) : nullptr, *const dOET = SC ? BR_(dOET) : nullptr;
+    // the walk's exchange words of group tl, before the launch that walks the last
+    // chunks; with the walk's own stores (past the L2, like its loads): plain stores may
+    // stay in this XCD's L2 while the walk reads an earlier call's words from memory
+    if (P.xch && P.n0 + P.nc == nch && tl < P.groups) {
+      constexpr int NX = 2 * rec::walk_slices(CP, H) * CP * D;
+      unsigned long long* const xw = P.xch + (size_t)tl * NX;
+      for (int e = threadIdx.x; e < NX; e += 512)
+        __hip_atomic_store(xw + e, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     const int tok0 = s * Dm.S + n * C;
     const int l = lane_id_local();
     const CT* pk = (const CT*)a.statesT + ((size_t)u * a.nslots + n) * (4 * hd + (size_t)d * d);
@@ -236,8 +243,10 @@ local_bwd_ret_kernel(LocalBwdArgs a, SplitPtrs P) {
           const size_t et = (size_t)(j0 + q) * Cp + i;  // consecutive lanes: consecutive i
           const float w2 = fHW2[et], s2 = fHS2[et];
           dOT[et] = from_f<CT>(ox[q]);
-          dOAT[et] = from_f<CT>(cf.A[i] * ox[q]);
-          dOET[et] = from_f<CT>(cf.E[i] * ox[q]);
+          if constexpr (SC) {
+            dOAT[et] = from_f<CT>(cf.A[i] * ox[q]);
+            dOET[et] = from_f<CT>(cf.E[i] * ox[q]);
+          }
           const float oq = to_f(from_f<CT>(ox[q]));  // dO as the contractions see it
           sa += oq * w2;
           se += oq * s2;
@@ -515,7 +524,11 @@ __device__ __forceinline__ void mma_pair_dots(f4 (&t0)[RBN], f4 (&t1)[RBN], cons
 }
 
 // ===========================================================================
-// pass B: the carried adjoint, walked back through a unit's chunks
+// pass B on one CU per unit: the carried adjoint, walked back through a unit's
+// chunks with the adjoint in memory.  Chunks of more than 32 rows: there the sliced
+// walk (tnt_local_bwd_walk.hip) has to spill its 64-row tiles beside the
+// register-resident adjoint and takes 57 us a chunk on two CUs, this one 86 us on one
+// (128 units, workload of B 4, H 8, L 8192: step 4.62 ms here, 4.98 ms there).
 // ===========================================================================
 template <typename IO, typename CT, int ACT, int D, int H, int CP>
 __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, SplitPtrs P) {
@@ -931,7 +944,21 @@ __global__ void __launch_bounds__(512) local_bwd_gate_kernel(LocalBwdArgs a, Spl
   float* dkp = a.dk_part + (cbase + tok0) * d;
   const bool fuse = a.dk_out != nullptr;  // write the final dk (every other part is done)
   const bool qk_here = shard_qk && n < nch - 1;
+  constexpr int G = rec::walk_slices(CP, H);
+  // dk so far: pass A's part and the walk's (slice by slice; the one-CU walk adds its own)
   f32x4 k0v = {0.f, 0.f, 0.f, 0.f}, k1v = k0v;
+  if (qrow) {
+    k0v = *reinterpret_cast<const f32x4*>(dkp + (size_t)qi * d + qc);
+    k1v = *reinterpret_cast<const f32x4*>(dkp + (size_t)qi * d + qc + 4);
+    if constexpr (!rec::rec_scaled(CP)) {
+      const float* ds = P.dks + (size_t)t * G * Cp * d + (size_t)qi * d + qc;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        k0v += *reinterpret_cast<const f32x4*>(ds + (size_t)g * Cp * d);
+        k1v += *reinterpret_cast<const f32x4*>(ds + (size_t)g * Cp * d + 4);
+      }
+    }
+  }
   if (qk_here) {
     // Kbar += (Nbar' - N (N . Nbar')) / ||k||, Nbar' = N (Mbar + Mbar^T), Mbar the
     // suffix sum of Xbar^T Q over the shard's later chunks (Mbar + Mbar^T formed
@@ -943,11 +970,7 @@ __global__ void __launch_bounds__(512) local_bwd_gate_kernel(LocalBwdArgs a, Spl
     const float* kn = rf + Y.r.ff.o[rec::kn];
     // the row elements of dk and N, requested ahead of the product
     float nv[8];
-    if (qrow) {
-      k0v = *reinterpret_cast<const f32x4*>(dkp + (size_t)qi * d + qc);
-      k1v = *reinterpret_cast<const f32x4*>(dkp + (size_t)qi * d + qc + 4);
-      load8(N + (size_t)qi * d + qc, nv);
-    }
+    if (qrow) load8(N + (size_t)qi * d + qc, nv);
     for (int e = threadIdx.x * 4; e < d * d; e += blockDim.x * 4) {
       const f32x4 v = *reinterpret_cast<const f32x4*>(Mb + e);
       const int i = e / d, j = e - i * d;
@@ -990,22 +1013,18 @@ __global__ void __launch_bounds__(512) local_bwd_gate_kernel(LocalBwdArgs a, Spl
             k0v[q] += (f8[q] - nv[q] * dt) / nr;
             k1v[q] += (f8[q + 4] - nv[q + 4] * dt) / nr;
           }
-          if (!fuse) {
-            *reinterpret_cast<f32x4*>(dkp + (size_t)qi * d + qc) = k0v;
-            *reinterpret_cast<f32x4*>(dkp + (size_t)qi * d + qc + 4) = k1v;
-          }
         }
       }
     }
     __syncthreads();  // LDS is reused below
   }
+  if (!fuse && qrow && (qk_here || !rec::rec_scaled(CP))) {
+    *reinterpret_cast<f32x4*>(dkp + (size_t)qi * d + qc) = k0v;
+    *reinterpret_cast<f32x4*>(dkp + (size_t)qi * d + qc + 4) = k1v;
+  }
   if (fuse && qrow) {
     // the final dk of the row: every memory's part in a fixed order (the order of
     // the separate sum), this memory's from the registers
-    if (!qk_here) {
-      k0v = *reinterpret_cast<const f32x4*>(dkp + (size_t)qi * d + qc);
-      k1v = *reinterpret_cast<const f32x4*>(dkp + (size_t)qi * d + qc + 4);
-    }
     const size_t e = (cbase + tok0 + qi) * d + qc;
     f32x4 s0 = k0v, s1 = k1v;
     for (int p = 0; p < a.dk_nparts; ++p) {
@@ -1038,10 +1057,21 @@ __global__ void __launch_bounds__(512) local_bwd_gate_kernel(LocalBwdArgs a, Spl
     const int i = threadIdx.x;
     gA[i] = bqf[Y.r.bf.o[rec::gA] + i];
     gE[i] = bqf[Y.r.bf.o[rec::gE] + i];
-    gCC[i] = bqf[Y.r.bf.o[rec::gCC] + i];
-    gB[i] = bqf[Y.r.bf.o[rec::gB] + i];
+    float x = 0.f, y = 0.f;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      x += bqf[Y.r.bf.o[rec::gCC] + g * Cp + i];
+      y += bqf[Y.r.bf.o[rec::gB] + g * Cp + i];
+    }
+    gCC[i] = x;
+    gB[i] = y;
   }
-  if (threadIdx.x < 3) dots[threadIdx.x] = bqf[Y.r.bf.o[rec::dots] + threadIdx.x];
+  if (threadIdx.x < 3) {
+    float x = 0.f;
+#pragma unroll
+    for (int g = 0; g < G; ++g) x += bqf[Y.r.bf.o[rec::dots] + 4 * g + threadIdx.x];
+    dots[threadIdx.x] = x;
+  }
   __syncthreads();
   if (wave_id() == 0) {
     const int i = l;
@@ -1144,26 +1174,34 @@ template <typename CT, int CP, int D, int H>
 constexpr bool split_fits() {
   // pass C's static LDS is under 40 KB
   return split_a_lds<CT, CP, D, H>() + SPLIT_A_STATIC <= 160 * 1024 &&
-         split_b_lds<CT, CP, D, H>() + 2 * 1024 <= 160 * 1024 &&
+         (!rec::rec_scaled(CP) || split_b_lds<CT, CP, D, H>() + 2 * 1024 <= 160 * 1024) &&
          split_c_lds<CT, CP, D>() + 40 * 1024 <= 160 * 1024;
 }
 
 struct SplitSizes {
-  size_t rec_ct, rec_f;  // elements
+  size_t rec_ct, rec_f, dks, xch;  // elements
 };
+
+// groups of the walk's slices at most (the exchange area is sized for them): unlimited
+// where there is nothing to exchange, else what fits the CUs
+inline int walk_groups_max(int units, int slices) {
+  return slices == 1 ? units : std::min(units, WALK_CUS / slices);
+}
 
 template <typename CT, int CP, int D, int H>
 SplitSizes split_sizes(int units, int nch) {
   constexpr SplitLayout Y = make_split_layout(CP, D, H);
   const size_t t = (size_t)units * nch;
-  return SplitSizes{t * Y.r.bc.n, t * Y.r.bf.n};
+  constexpr int G = rec::walk_slices(CP, H);
+  return SplitSizes{t * Y.r.bc.n, t * Y.r.bf.n, rec::rec_scaled(CP) ? 0 : t * G * CP * D,
+                    G > 1 ? (size_t)walk_groups_max(units, G) * 2 * G * CP * D : 0};
 }
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 template <typename CT>
 size_t total_bytes(const SplitSizes& z) {
-  return up256(z.rec_ct * sizeof(CT)) + up256(z.rec_f * 4);
+  return up256(z.rec_ct * sizeof(CT)) + up256(z.rec_f * 4) + up256(z.dks * 4) + up256(z.xch * 8);
 }
 
 template <typename CT>
@@ -1171,7 +1209,9 @@ SplitPtrs carve(void* ws, const SplitSizes& z, int units) {
   char* p = (char*)ws;
   SplitPtrs P{};
   P.brec = p; p += up256(z.rec_ct * sizeof(CT));
-  P.brec_f = (float*)p;
+  P.brec_f = (float*)p; p += up256(z.rec_f * 4);
+  P.dks = (float*)p; p += up256(z.dks * 4);
+  P.xch = z.xch ? (unsigned long long*)p : nullptr;
   P.units = units;
   return P;
 }
@@ -1202,6 +1242,11 @@ bool try_split(const LocalBwdArgs* a, const Dims& Dm, int units, void* ws, hipSt
   if (bytes) *bytes = total_bytes<CT>(z);
   if (!a) return true;
   SplitPtrs P = carve<CT>(ws, z, units);
+  // walks that run beside one another share the CUs
+  constexpr int G = rec::walk_slices(CP, H);
+  const int cus = device_cus();
+  P.groups = walk_groups_max(units, G);
+  if (G > 1) P.groups = std::max(1, std::min(P.groups, (cus ? std::min(cus, WALK_CUS) : WALK_CUS) / G / std::max(1, a->walks)));
   constexpr SplitLayout Y = make_split_layout(CP, D, H);
   const int total = units * nch;
   // When the walks leave half the CUs free and are long (32 chunks or more), the
@@ -1219,17 +1264,13 @@ bool try_split(const LocalBwdArgs* a, const Dims& Dm, int units, void* ws, hipSt
   P.n0 = nlo;
   P.nc = nch - nlo;
   auto ka = local_bwd_ret_kernel<IO, CT, ACT, D, H, CP>;
-  auto kb = local_bwd_chain_kernel<IO, CT, ACT, D, H, CP>;
   auto kc = local_bwd_gate_kernel<CT, D, H, CP>;
-  constexpr size_t lds_a = split_a_lds<CT, CP, D, H>(), lds_b = split_b_lds<CT, CP, D, H>(),
-                   lds_c = split_c_lds<CT, CP, D>();
-  if (!lds_fits((const void*)ka, lds_a) || !lds_fits((const void*)kb, lds_b) ||
-      !lds_fits((const void*)kc, lds_c)) {  // the compiled static LDS, not the estimate
+  constexpr size_t lds_a = split_a_lds<CT, CP, D, H>(), lds_c = split_c_lds<CT, CP, D>();
+  if (!lds_fits((const void*)ka, lds_a) || !lds_fits((const void*)kc, lds_c)) {  // the compiled static LDS, not the estimate
     *err = hipErrorInvalidConfiguration;
     return true;
   }
   set_lds_limit((const void*)ka);
-  set_lds_limit((const void*)kb);
   set_lds_limit((const void*)kc);
   hipLaunchKernelGGL(ka, dim3(units * P.nc), dim3(512), lds_a, st, *a, P);
   auto fail = [&](hipError_t e) {
@@ -1261,10 +1302,23 @@ bool try_split(const LocalBwdArgs* a, const Dims& Dm, int units, void* ws, hipSt
     if ((e = hipEventRecord(a->aux_done, a->aux)) != hipSuccess) return fail(e);
   }
   const int sec = section_begin("local_bwd_walk", st);  // the walk of the carried adjoint alone
-  hipLaunchKernelGGL(kb, dim3(units), dim3(512), lds_b, st, *a, P);
+  auto walk = [&](const SplitPtrs& Q) {
+    hipError_t we = hipErrorInvalidConfiguration;
+    if constexpr (rec::rec_scaled(CP)) {
+      auto kb = local_bwd_chain_kernel<IO, CT, ACT, D, H, CP>;
+      constexpr size_t lds_b = split_b_lds<CT, CP, D, H>();
+      if (!lds_fits((const void*)kb, lds_b)) return we;
+      set_lds_limit((const void*)kb);
+      hipLaunchKernelGGL(kb, dim3(units), dim3(512), lds_b, st, *a, Q);
+      return hipGetLastError();
+    } else {
+      return launch_local_bwd_walk(*a, Q, st, &we) ? we : hipErrorInvalidConfiguration;
+    }
+  };
+  if ((e = walk(P)) != hipSuccess) return fail(e);
   if (halves) {
     if ((e = hipStreamWaitEvent(st, a->aux_mid, 0)) != hipSuccess) return fail(e);
-    hipLaunchKernelGGL(kb, dim3(units), dim3(512), lds_b, st, *a, Plo);
+    if ((e = walk(Plo)) != hipSuccess) return fail(e);
   }
   section_end(sec, st);
   if (a->pass_b_done && (e = hipEventRecord(a->pass_b_done, st)) != hipSuccess) return fail(e);

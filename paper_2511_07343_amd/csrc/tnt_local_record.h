@@ -25,8 +25,9 @@ namespace rec {
 enum FwdCT {
   Hk, HkT, D1, HT, Sp, Spp, G, Sz,              // C x h (Sp, Spp, G, Sz fragment-major)
   PzT, PoT, StrT,                               // C x C
-  K, KT, KcC, Kb, R, RT, RcC, Rb,               // C x d
-  XT, XAT, XET, N, NT, QT,                      // C x d
+  K, KT, KcC, Kb, R, RT, RcC, Rb,               // C x d (KcC, Kb, RcC, Rb, XAT, XET: scaled by
+  XT, XAT, XET, N, NT, QT,                      // cC, b, A, E; empty unless rec_scaled(C))
+  W2r,                                          // d x h, the chunk-entry W2 (else)
   FWD_CT
 };
 // forward record, fp32
@@ -37,7 +38,7 @@ enum FwdF {
   sc,            // 4      A_C, B_C, E_C
   Cc,            // C(C+1)/2  the chunk coefficients c_{i,tau} (tau <= i), row after row
   cA, cE,        // C      A_i, E_i (pass A of the backward reads these and Cc instead of
-                 //        recomputing them; empty unless rec_coefs(C))
+                 //        recomputing them, the sliced walk these; empty unless rec_coefs(C))
   FWD_F
 };
 // backward record, compute type
@@ -47,10 +48,24 @@ enum BwdF {
   Cb,            // C x C  the retrieval's part of cbar
   gA, gE,        // C      the retrieval's dA, dE
   XbQ,           // d x d  Xbar^T Q, then the suffix sum over later chunks
-  gCC, gB,       // C      the walk's cC-bar, b-bar
-  dots,          // 4      dA_C, dE_C, dB_C (the walk's adjoint . state products)
+  gCC, gB,       // C      the walk's cC-bar, b-bar, of each slice
+  dots,          // 4      dA_C, dE_C, dB_C (the walk's adjoint . state products), of each slice
   BWD_F
 };
+
+// Whether the forward record keeps the chunk coefficients for the backward.  At
+// chunks of up to 32 positions, recomputing them (one wave's scan) costs pass A
+// more than reading them back; at 64 the 8 KB per chunk they take costs more.
+__host__ __device__ constexpr bool rec_coefs(int Cp) { return Cp <= 32; }
+
+// Chunks of more than 32 rows: the adjoint is walked on one CU per unit, whose kernel
+// reads the row-scaled operands; shorter ones: in slices of the hidden units, one
+// workgroup each, which scale their operands themselves.
+__host__ __device__ constexpr bool rec_scaled(int Cp) { return !rec_coefs(Cp); }
+__host__ __device__ constexpr int walk_hs(int h) { return h < 128 ? h : 128; }
+__host__ __device__ constexpr int walk_slices(int Cp, int h) {
+  return rec_scaled(Cp) ? 1 : h / walk_hs(h);
+}
 
 template <int NB>
 struct Lay {
@@ -78,19 +93,16 @@ struct RecLayout {
   Lay<BWD_F> bf;
 };
 
-// Whether the forward record keeps the chunk coefficients for the backward.  At
-// chunks of up to 32 positions, recomputing them (one wave's scan) costs pass A
-// more than reading them back; at 64 the 8 KB per chunk they take costs more.
-__host__ __device__ constexpr bool rec_coefs(int Cp) { return Cp <= 32; }
-
 __host__ __device__ constexpr RecLayout make_rec_layout(int Cp, int d, int h) {
   const size_t C = Cp, Cd = C * d, Ch = C * h, CC = C * C, dd = (size_t)d * d;
-  const size_t sfc[FWD_CT] = {Ch, Ch, Ch, Ch, Ch, Ch, Ch, Ch, CC, CC, CC, Cd, Cd, Cd, Cd,
-                              Cd, Cd, Cd, Cd, Cd, Cd, Cd, Cd, Cd, Cd};
-  const size_t cr = rec_coefs(Cp) ? C : 0;
+  const size_t sc = rec_scaled(Cp) ? Cd : 0;
+  const size_t sfc[FWD_CT] = {Ch, Ch, Ch, Ch, Ch, Ch, Ch, Ch, CC, CC, CC, Cd, Cd, sc, sc,
+                              Cd, Cd, sc, sc, Cd, sc, sc, Cd, Cd, Cd,
+                              rec_scaled(Cp) ? 0 : (size_t)d * h};
+  const size_t cr = rec_coefs(Cp) ? C : 0, G = walk_slices(Cp, h);
   const size_t sff[FWD_F] = {CC, CC, Cd, Cd, C, C, C, 4, cr * (cr + 1) / 2, cr, cr};
-  const size_t sbc[BWD_CT] = {Ch, CC, Cd, Cd, Cd};
-  const size_t sbf[BWD_F] = {CC, C, C, dd, C, C, 4};
+  const size_t sbc[BWD_CT] = {Ch, CC, Cd, sc, sc};
+  const size_t sbf[BWD_F] = {CC, C, C, dd, C * G, C * G, 4 * G};
   return RecLayout{make_lay(sfc), make_lay(sff), make_lay(sbc), make_lay(sbf)};
 }
 

@@ -12,9 +12,9 @@
 //   O   = diag(A) H W2^T + diag(E) H S2^T - Po R
 //
 // It also writes the chunk's forward record fields that the backward passes
-// read and that the walk does not write (K, R, X and their scaled and
-// transposed forms, Q^T, N, N^T, tril(Q N^T)^T, Pz^T, Po^T, H^T, s'(Z), X K^T,
-// H Hk^T, (H W2^T)^T, (H S2^T)^T, key norms and the carry coefficients).
+// read and that the walk does not write (K, R and the transposes of K, R, X and Q,
+// N, N^T, tril(Q N^T)^T, Pz^T, Po^T, H^T, s'(Z), X K^T, H Hk^T, (H W2^T)^T,
+// (H S2^T)^T, key norms and the carry coefficients).
 //
 // Sized for two workgroups per CU: LDS holds X, K, R (rows padded by 16 bytes
 // so that the 16-byte operand reads of consecutive rows do not start on the
@@ -196,9 +196,7 @@ local_ret_kernel(LocalFwdArgs a) {
   }
   __syncthreads();
 
-  // ---- the forward record: K, R and their scaled / transposed forms, X^T scaled
-  // and as it is, Q^T,
-  // N, N^T, tril(Q N^T)^T (eight destination elements per thread, 16-byte
+  // ---- the forward record: K, R, K^T, R^T, X^T, Q^T, N, N^T, tril(Q N^T)^T (eight destination elements per thread, 16-byte
   // stores; transposed destinations gather their eight sources from LDS)
   if (fr) {
     auto st8 = [&](int field, size_t e0, const float (&x)[8]) {
@@ -218,31 +216,37 @@ local_ret_kernel(LocalFwdArgs a) {
       const size_t ec = (size_t)jt * LDC + it;             // [D][CP] element e0 in LDS
       cp8(rec::K, e0, sK + ed);
       cp8(rec::R, e0, sR + ed);
-      float kc[8], kb[8], rc[8], rb[8], kt[8], rt[8], xt[8], xa[8], xe[8], qt[8];
+      float kt[8], rt[8], xt[8], qt[8];
 #pragma unroll
       for (int qq = 0; qq < 8; ++qq) {
-        const float kx = to_f(sK[ed + qq]), rx = to_f(sR[ed + qq]);
-        kc[qq] = cf.cC[i] * kx;
-        kb[qq] = cf.bb[i] * kx;
-        rc[qq] = cf.cC[i] * rx;
-        rb[qq] = cf.bb[i] * rx;
         const size_t es = (size_t)(it + qq) * LDD + jt;
         kt[qq] = to_f(sK[es]);
         rt[qq] = to_f(sR[es]);
         xt[qq] = to_f(sX[es]);
-        xa[qq] = cf.A[it + qq] * xt[qq];
-        xe[qq] = cf.E[it + qq] * xt[qq];
         qt[qq] = to_f(sQ[es]);
       }
-      st8(rec::KcC, e0, kc);
-      st8(rec::Kb, e0, kb);
-      st8(rec::RcC, e0, rc);
-      st8(rec::Rb, e0, rb);
+      if constexpr (rec::rec_scaled(CP)) {
+        float kc[8], kb[8], rc[8], rb[8], xa[8], xe[8];
+#pragma unroll
+        for (int qq = 0; qq < 8; ++qq) {
+          const float kx = to_f(sK[ed + qq]), rx = to_f(sR[ed + qq]);
+          kc[qq] = cf.cC[i] * kx;
+          kb[qq] = cf.bb[i] * kx;
+          rc[qq] = cf.cC[i] * rx;
+          rb[qq] = cf.bb[i] * rx;
+          xa[qq] = cf.A[it + qq] * xt[qq];
+          xe[qq] = cf.E[it + qq] * xt[qq];
+        }
+        st8(rec::KcC, e0, kc);
+        st8(rec::Kb, e0, kb);
+        st8(rec::RcC, e0, rc);
+        st8(rec::Rb, e0, rb);
+        st8(rec::XAT, e0, xa);
+        st8(rec::XET, e0, xe);
+      }
       st8(rec::KT, e0, kt);
       st8(rec::RT, e0, rt);
       st8(rec::XT, e0, xt);
-      st8(rec::XAT, e0, xa);
-      st8(rec::XET, e0, xe);
       st8(rec::QT, e0, qt);
       if (qk) {
         cp8(rec::N, e0, sN + ed);

@@ -48,3 +48,25 @@ def test_forward_modes_agree():
     assert torch.equal(a, b)
     # one walk instead of two passes: the same products, some in another order
     assert (c.float() - a.float()).abs().max() <= 1e-2 * a.float().abs().max()
+
+
+@pytest.mark.parametrize("B,H,locals_", [
+    (1, 1, ((16, 32),)),            # one unit: one group of the walk's slices
+    (9, 15, ((5, 10),)),            # more units than groups (128), no multiple of them
+    (8, 20, ((16, 32), (32, 32))),  # two walks side by side, each with half the groups
+], ids=str)
+def test_walk_groups(B, H, locals_):
+    """The sliced walk of the adjoint over few and many units against the runtime-sized
+    kernels (2e-2, the bound of both against the oracle), and twice the same bits: the
+    slices add in a fixed order whatever order they run in."""
+    S = locals_[0][1]
+    cfg = small_config(BF16, ACT_SILU, B=B, H=H, L=2 * S, d=64, hid=256, C_G=2 * S,
+                       locals_=locals_, name=f"walk B{B} H{H} {locals_}")
+    inp = make_inputs(cfg, 503)
+    print(f"\n[case] {cfg.name}", flush=True)
+    got, again = gpu_backward(cfg, inp), gpu_backward(cfg, inp)
+    with tnt.kernel_family(tnt.FAMILY_GENERIC):
+        ref = gpu_backward(cfg, inp)
+    for n in GRADS:
+        assert np.array_equal(got[n], again[n]), n
+    check(cfg, got, ref)
