@@ -241,6 +241,213 @@ __device__ __forceinline__ void gemm(int M, int N, int K, const EA* A, int lda, 
 }
 
 // ----------------------------------------------------------------------------
+// Tiles of the runtime-sized kernels.  Their K loops cannot be unrolled by the
+// compiler, so a loop over single K steps pays one memory round trip per step and
+// per 16x16 tile; that latency bounds these kernels.  Here a wave takes a column of RB
+// tiles at once (a chunk's rows), requests the next K steps (of both products, where two
+// share their A operand) before it multiplies the present ones, and converts after the
+// loads, not between them.  The fp32 form gives lane l the 4 consecutive k at 4*(l/16)
+// of a step of 16, one 16-byte load, and feeds them to 4 products: A and B are permuted
+// alike, so the sum runs over the same k.  Requests of 4 steps (128 k) lose where K is
+// 32: at d 32 they cost 5 % against single steps, requests of 2 gain 20 %.  Forward and
+// backward of 16 heads x 32768 tokens at d 128, hid 512, 64 rows: 181 ms before, 120 ms
+// now; fp32, 6 heads x 1200 tokens at d 32, hid 64, 24 and 12 rows: 4.0 ms before, 2.2 ms.
+// ----------------------------------------------------------------------------
+// K steps per request; the next request is out before the products of this one
+constexpr int run_steps(int RB) { return RB > 2 ? 1 : 2; }
+
+template <int RB> struct RowAcc {  // a column of RB 16x16 tiles
+  f4 v[RB];
+  __device__ __forceinline__ RowAcc() {
+#pragma unroll
+    for (int r = 0; r < RB; ++r) v[r] = f4{0.f, 0.f, 0.f, 0.f};
+  }
+};
+
+template <typename CT> struct RunStep;
+template <> struct RunStep<__bf16> {
+  static constexpr int W = 8, KS = 32;
+  template <typename E> __device__ __forceinline__ static bf16x8 get(const E (&v)[8]) {
+    bf16x8 f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) f[j] = (__bf16)to_f(v[j]);
+    return f;
+  }
+  template <typename EA, typename EB>
+  __device__ __forceinline__ static void mma(f4& acc, const EA (&a)[8], const EB (&b)[8]) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(get(a), get(b), acc, 0, 0, 0);
+  }
+};
+template <> struct RunStep<float> {
+  static constexpr int W = 4, KS = 16;
+  template <typename EA, typename EB>
+  __device__ __forceinline__ static void mma(f4& acc, const EA (&a)[4], const EB (&b)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(to_f(a[j]), to_f(b[j]), acc, 0, 0, 0);
+  }
+};
+
+// the lane's W consecutive k of one step, unconverted; zero past K (a multiple of 16)
+template <int LAY, int W, typename E>
+__device__ __forceinline__ void run_load(E (&v)[W], const E* p, int ld, int idx, int kb, int K) {
+  if (kb >= K) {
+#pragma unroll
+    for (int j = 0; j < W; ++j) v[j] = from_f<E>(0.f);
+  } else if (LAY == KC) {
+    typedef E vec __attribute__((ext_vector_type(16 / sizeof(E))));
+    constexpr int PER = 16 / sizeof(E);
+    static_assert(W % PER == 0, "whole 16-byte loads");
+    const E* q = p + (size_t)idx * ld + kb;
+#pragma unroll
+    for (int t = 0; t < W / PER; ++t) {
+      const vec x = *reinterpret_cast<const vec*>(q + t * PER);
+#pragma unroll
+      for (int j = 0; j < PER; ++j) v[t * PER + j] = x[j];
+    }
+  } else {
+    const E* q = p + (size_t)kb * ld + idx;
+#pragma unroll
+    for (int j = 0; j < W; ++j) v[j] = q[(size_t)j * ld];
+  }
+}
+
+// x += A[i0:i0+16RB, 0:K] * B[0:K, j0:j0+16] and, with B2, y += A * B2; K a multiple
+// of 16; contraction-contiguous operands 16-byte aligned with leading dimensions
+// multiples of 8.
+template <typename CT, int LA, int LB, int RB, bool PAIR, typename EA, typename EB>
+__device__ __forceinline__ void mma_run_(RowAcc<RB>& x, RowAcc<RB>& y, const EA* A, int lda, int i0,
+                                         const EB* B, const EB* B2, int ldb, int j0, int K) {
+  typedef RunStep<CT> RS;
+  constexpr int U = run_steps(RB), W = RS::W, KS = RS::KS;
+  const int l = lane_id_local();
+  const int ko = W * (l >> 4);
+  const int ia = i0 + (l & 15), jb = j0 + (l & 15);
+  struct Step {
+    EA a[RB][W];
+    EB b[W], b2[PAIR ? W : 1];
+  };
+  Step cur[U], nxt[U];
+  auto fetch = [&](Step(&f)[U], int k0) {
+#pragma unroll
+    for (int t = 0; t < U; ++t) {
+      run_load<LB>(f[t].b, B, ldb, jb, k0 + t * KS + ko, K);
+      if constexpr (PAIR) run_load<LB>(f[t].b2, B2, ldb, jb, k0 + t * KS + ko, K);
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+        run_load<LA>(f[t].a[r], A, lda, ia + 16 * r, k0 + t * KS + ko, K);
+    }
+  };
+  auto apply = [&](const Step(&f)[U]) {
+#pragma unroll
+    for (int t = 0; t < U; ++t)
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        RS::mma(x.v[r], f[t].a[r], f[t].b);
+        if constexpr (PAIR) RS::mma(y.v[r], f[t].a[r], f[t].b2);
+      }
+  };
+  fetch(cur, 0);
+#pragma unroll 1
+  for (int k0 = U * KS; k0 < K; k0 += U * KS) {
+    fetch(nxt, k0);
+    apply(cur);
+#pragma unroll
+    for (int t = 0; t < U; ++t) cur[t] = nxt[t];
+  }
+  apply(cur);
+  // The reader may be in another block (after a loop, or after a product that a
+  // flag leaves out), where the compiler has been seen to leave out the wait states
+  // between a matrix product and the read of its result: wait here.
+  auto pin = [&] {
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      asm volatile("" : "+v"(x.v[r]));
+      if constexpr (PAIR) asm volatile("" : "+v"(y.v[r]));
+    }
+  };
+  pin();
+  asm volatile("s_nop 15");
+  pin();
+}
+template <typename CT, int LA, int LB, int RB, typename EA, typename EB>
+__device__ __forceinline__ void mma_run(RowAcc<RB>& x, const EA* A, int lda, int i0, const EB* B,
+                                        int ldb, int j0, int K) {
+  mma_run_<CT, LA, LB, RB, false>(x, x, A, lda, i0, B, (const EB*)nullptr, ldb, j0, K);
+}
+template <typename CT, int LA, int LB, int RB, typename EA, typename EB>
+__device__ __forceinline__ void mma_run2(RowAcc<RB>& x, RowAcc<RB>& y, const EA* A, int lda, int i0,
+                                         const EB* B, const EB* B2, int ldb, int j0, int K) {
+  mma_run_<CT, LA, LB, RB, true>(x, y, A, lda, i0, B, B2, ldb, j0, K);
+}
+
+// One tile's contraction over at most 64, requested by load() and multiplied by
+// mma(): several of them can be in flight together.  Both operands KC.
+template <typename CT> struct RunOp {
+  typedef RunStep<CT> RS;
+  static constexpr int U = 64 / RS::KS;
+  CT a[U][RS::W], b[U][RS::W];
+  __device__ __forceinline__ void load(const CT* A, int lda, int i0, const CT* B, int ldb, int j0,
+                                       int K) {
+    const int l = lane_id_local();
+    const int ko = RS::W * (l >> 4);
+#pragma unroll
+    for (int t = 0; t < U; ++t) {
+      run_load<KC>(a[t], A, lda, i0 + (l & 15), t * RS::KS + ko, K);
+      run_load<KC>(b[t], B, ldb, j0 + (l & 15), t * RS::KS + ko, K);
+    }
+  }
+  __device__ __forceinline__ f4 mma() const {
+    f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < U; ++t) RS::mma(acc, a[t], b[t]);
+    return acc;
+  }
+};
+
+// A chunk's output (Cp rows, N columns) in columns of RB tiles, f(i0, j0).  Waves that
+// share a column's B operand (a memory's state, far larger than the chunk's rows) are
+// neighbours.
+template <int RB, typename F>
+__device__ __forceinline__ void chunk_tiles(int Cp, int N, F&& f) {
+  const int tm = Cp / (16 * RB), nt = tm * (N >> 4);
+  for (int t = wave_id(); t < nt; t += num_waves()) f((t % tm) * 16 * RB, (t / tm) << 4);
+}
+// RB for a chunk of Cp rows: the tallest column that divides it, since taller ones read
+// the states less often (forward of 16 heads x 32768 tokens at d 128, hid 512, 64 rows:
+// 47 ms with single tiles, 31 ms with columns of 4).  In narrow outputs they leave waves
+// idle, which costs less than it saves: at d 64 (4 columns for 8 waves) columns of 4
+// against 2 gain 1 to 3 %, at d 32 columns of 4 against 1 between -2 and +2 %.
+inline int chunk_tile_rows(int Cp) { return Cp % 64 == 0 ? 4 : Cp % 32 == 0 ? 2 : 1; }
+// the 16x16 tiles of an M x N state, f(i0, j0): consecutive waves along a row, which
+// is written in whole lines
+template <typename F>
+__device__ __forceinline__ void state_tiles(int M, int N, F&& f) {
+  const int tn = N >> 4, nt = (M >> 4) * tn;
+  for (int t = wave_id(); t < nt; t += num_waves()) f((t / tn) << 4, (t % tn) << 4);
+}
+// f(i, j, r-th row's tile and register) over the lane's elements of a column of tiles
+template <int RB, typename F>
+__device__ __forceinline__ void chunk_each(int i0, int j0, F&& f) {
+  const int l = lane_id_local();
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) f(i0 + 16 * rb + 4 * (l >> 4) + r, j0 + (l & 15), rb, r);
+}
+
+// out(i, j) = sum_k A(i, k) B(k, j) over a chunk's rows, passed to epi(i, j, value)
+template <typename CT, int LA, int LB, int RB, typename EA, typename EB, typename Epi>
+__device__ __forceinline__ void gemm_run(int Cp, int N, int K, const EA* A, int lda, const EB* B,
+                                         int ldb, Epi&& epi) {
+  chunk_tiles<RB>(Cp, N, [&](int i0, int j0) {
+    RowAcc<RB> acc;
+    mma_run<CT, LA, LB>(acc, A, lda, i0, B, ldb, j0, K);
+    chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) { epi(i, j, acc.v[rb][r]); });
+  });
+}
+
+// ----------------------------------------------------------------------------
 // Register-blocked wave tiles.  An M x N output (multiples of 16, sizes known
 // at compile time) is cut into blocks of RB x CB 16x16 tiles: T/8 tiles per
 // block (1..8), shaped to need the fewest operand fragments.  Blocks go to the

@@ -35,23 +35,15 @@ __device__ __forceinline__ float sum16(float v) {
   return v;
 }
 
-// iterate the 16x16 output tiles of an M x N result over the waves
-template <typename F>
-__device__ __forceinline__ void tiles(int M, int N, F&& f) {
-  const int tn = N >> 4, nt = (M >> 4) * tn;
-  for (int t = wave_id(); t < nt; t += num_waves()) f((t / tn) << 4, (t % tn) << 4);
-}
-
-// D_, H_, CP_ > 0 fix the head dim, hidden width and padded chunk at compile
-// time (all loops unrolled, buffer offsets constant); 0 reads them from `a`.
-template <typename IO, typename CT, int ACT, int D_, int H_, int CP_>
+// RB: a wave's share of a chunk's output, in 16x16 tiles below each other
+template <typename IO, typename CT, int ACT, int RB>
 __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
   __shared__ Coef cf;
   __shared__ float gA[MAXC], gE[MAXC], gCC[MAXC], gB[MAXC], gEta[MAXC], gLa[MAXC], gLb[MAXC];
   __shared__ float red[32];
+  __shared__ float sCb[MAXC][MAXC + 1], sU[MAXC][MAXC + 1];  // cbar and U of the gate adjoints
   const Dims D = a.D;
-  const int d = D_ ? D_ : D.d, h = H_ ? H_ : D.hid, Cp = CP_ ? CP_ : D.Cp;
-  const int C = D.C;
+  const int d = D.d, h = D.hid, C = D.C, Cp = D.Cp;
   const int nshard = D.L / D.S;
   const int u = blockIdx.x;
   const int b = u / (D.H * nshard), hh = (u / nshard) % D.H, s = u % nshard;
@@ -77,7 +69,7 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
      *XbT = B_(bXbT), *dXN = B_(bdXN), *dXNT = B_(bdXNT);
   CT *Wb1T = B_(bWb1T), *Sb1T = B_(bSb1T), *Wb2T = B_(bWb2T), *Sb2T = B_(bSb2T);
   float *fXK = F_(E_XK), *fHH = F_(E_HH), *fdOR = F_(E_dOR), *fdZD1 = F_(E_dZD1), *fCb = F_(E_Cbar),
-        *fU = F_(E_U), *fKb = F_(E_Kbar), *fRb = F_(E_Rbar), *fXb = F_(E_Xbar), *fT3 = F_(E_T3),
+        *fKb = F_(E_Kbar), *fRb = F_(E_Rbar), *fXb = F_(E_Xbar), *fT3 = F_(E_T3),
         *fT4 = F_(E_T4), *fT5 = F_(E_T5), *fT6 = F_(E_T6), *fZkp = F_(E_Zkp), *fMs = F_(E_Msym),
         *pA = F_(E_PartA), *pE = F_(E_PartE);
 #undef B_
@@ -157,17 +149,17 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
       XET[(size_t)j * Cp + i] = from_f<CT>(cf.E[i] * x);
     };
     if (D.qk_proj) {
-      gemm<CT, KC, KC>(Cp, Cp, d, Q, d, N, d, [&](int i, int j, float x) {
+      gemm_run<CT, KC, KC, RB>(Cp, Cp, d, Q, d, N, d, [&](int i, int j, float x) {
         const float y = j <= i ? x : 0.f;
         Str[(size_t)i * Cp + j] = from_f<CT>(y);
         StrT[(size_t)j * Cp + i] = from_f<CT>(y);
       });
       __syncthreads();
-      tiles(Cp, d, [&](int i0, int j0) {
-        f4 acc = zero4();
-        if (shard_qk) mma_tile<CT, KC, KC>(acc, Q, d, i0, Mc, d, j0, d);
-        mma_tile<CT, KC, KC>(acc, Str, Cp, i0, NT, Cp, j0, Cp);
-        tile_each(acc, i0, j0, put_x);
+      chunk_tiles<RB>(Cp, d, [&](int i0, int j0) {
+        RowAcc<RB> acc;
+        if (shard_qk) mma_run<CT, KC, KC>(acc, Q, d, i0, Mc, d, j0, d);
+        mma_run<CT, KC, KC>(acc, Str, Cp, i0, NT, Cp, j0, Cp);
+        chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) { put_x(i, j, acc.v[rb][r]); });
       });
     } else {
       for (int e = threadIdx.x; e < Cp * d; e += blockDim.x) {
@@ -175,7 +167,7 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
         put_x(i, j, to_f(Q[e]));
       }
     }
-    gemm<CT, KC, KC>(Cp, h, d, K, d, W1g, d, [&](int i, int j, float z) {
+    gemm_run<CT, KC, KC, RB>(Cp, h, d, K, d, W1g, d, [&](int i, int j, float z) {
       const ActVals av = act_all<ACT>(z);
       Hk[(size_t)i * h + j] = from_f<CT>(av.s);
       HkT[(size_t)j * Cp + i] = from_f<CT>(av.s);
@@ -183,41 +175,38 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
       Spp[(size_t)i * h + j] = from_f<CT>(av.d2);
     });
     __syncthreads();
-    gemm<CT, KC, KC>(Cp, d, h, Hk, h, W2g, h, [&](int i, int j, float y) {
+    gemm_run<CT, KC, KC, RB>(Cp, d, h, Hk, h, W2g, h, [&](int i, int j, float y) {
       const float r = (i < C) ? rscale * (y - to_f(vg[(size_t)(tok0 + i) * d + j])) : 0.f;
       R[(size_t)i * d + j] = from_f<CT>(r);
       RT[(size_t)j * Cp + i] = from_f<CT>(r);
     });
     __syncthreads();
-    gemm<CT, KC, KC>(Cp, h, d, R, d, W2gT, d, [&](int i, int j, float g) {
+    gemm_run<CT, KC, KC, RB>(Cp, h, d, R, d, W2gT, d, [&](int i, int j, float g) {
       const float d1 = g * to_f(Sp[(size_t)i * h + j]);
       G[(size_t)i * h + j] = from_f<CT>(g);
       D1[(size_t)i * h + j] = from_f<CT>(d1);
       D1T[(size_t)j * Cp + i] = from_f<CT>(d1);
     });
-    gemm<CT, KC, KC>(Cp, Cp, d, X, d, K, d, [&](int i, int j, float x) {
+    gemm_run<CT, KC, KC, RB>(Cp, Cp, d, X, d, K, d, [&](int i, int j, float x) {
       fXK[(size_t)i * Cp + j] = x;
       const float p = j <= i ? cf.c[i][j] * x : 0.f;
       Pz[(size_t)i * Cp + j] = from_f<CT>(p);
       PzT[(size_t)j * Cp + i] = from_f<CT>(p);
     });
     __syncthreads();
-    tiles(Cp, h, [&](int i0, int j0) {
-      f4 a1 = zero4(), a2 = zero4(), a3 = zero4();
-      mma_tile<CT, KC, KC>(a1, X, d, i0, W1, d, j0, d);
-      mma_tile<CT, KC, KC>(a2, X, d, i0, S1, d, j0, d);
-      mma_tile<CT, KC, KC>(a3, Pz, Cp, i0, D1T, Cp, j0, Cp);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
-        const ActVals av = act_all<ACT>(cf.A[i] * a1[r] + cf.E[i] * a2[r] - a3[r]);
+    chunk_tiles<RB>(Cp, h, [&](int i0, int j0) {
+      RowAcc<RB> a1, a2, a3;
+      mma_run2<CT, KC, KC>(a1, a2, X, d, i0, W1, S1, d, j0, d);
+      mma_run<CT, KC, KC>(a3, Pz, Cp, i0, D1T, Cp, j0, Cp);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
+        const ActVals av = act_all<ACT>(cf.A[i] * a1.v[rb][r] + cf.E[i] * a2.v[rb][r] - a3.v[rb][r]);
         H[(size_t)i * h + j] = from_f<CT>(av.s);
         HT[(size_t)j * Cp + i] = from_f<CT>(av.s);
         Sz[(size_t)i * h + j] = from_f<CT>(av.d1);
-      }
+      });
     });
     __syncthreads();
-    gemm<CT, KC, KC>(Cp, Cp, h, H, h, Hk, h, [&](int i, int j, float x) {
+    gemm_run<CT, KC, KC, RB>(Cp, Cp, h, H, h, Hk, h, [&](int i, int j, float x) {
       fHH[(size_t)i * Cp + j] = x;
       const float p = j <= i ? cf.c[i][j] * x : 0.f;
       Po[(size_t)i * Cp + j] = from_f<CT>(p);
@@ -227,7 +216,7 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
 
     // ================= backward through the retrieval
     // dOR = dO R^T ; Q1 = c o dOR ; cbar = -HH o dOR
-    gemm<CT, KC, KC>(Cp, Cp, d, dO, d, R, d, [&](int i, int j, float x) {
+    gemm_run<CT, KC, KC, RB>(Cp, Cp, d, dO, d, R, d, [&](int i, int j, float x) {
       fdOR[(size_t)i * Cp + j] = x;
       const bool lo = j <= i;
       const float q1 = lo ? cf.c[i][j] * x : 0.f;
@@ -237,25 +226,22 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
     });
     __syncthreads();
     // Hbar = diag(A) dO W2 + diag(E) dO S2 - Q1 Hk ; Zbar = Hbar * s'(Z)
-    tiles(Cp, h, [&](int i0, int j0) {
-      f4 a1 = zero4(), a2 = zero4(), a3 = zero4();
-      mma_tile<CT, KC, KC>(a1, dO, d, i0, W2T, d, j0, d);
-      mma_tile<CT, KC, KC>(a2, dO, d, i0, S2T, d, j0, d);
-      mma_tile<CT, KC, KC>(a3, Q1, Cp, i0, HkT, Cp, j0, Cp);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
+    chunk_tiles<RB>(Cp, h, [&](int i0, int j0) {
+      RowAcc<RB> a1, a2, a3;
+      mma_run2<CT, KC, KC>(a1, a2, dO, d, i0, W2T, S2T, d, j0, d);
+      mma_run<CT, KC, KC>(a3, Q1, Cp, i0, HkT, Cp, j0, Cp);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
         const float hv = to_f(H[(size_t)i * h + j]);
-        const float hb = cf.A[i] * a1[r] + cf.E[i] * a2[r] - a3[r];
+        const float hb = cf.A[i] * a1.v[rb][r] + cf.E[i] * a2.v[rb][r] - a3.v[rb][r];
         const float zb = hb * to_f(Sz[(size_t)i * h + j]);
         Zb[(size_t)i * h + j] = from_f<CT>(zb);
         ZbT[(size_t)j * Cp + i] = from_f<CT>(zb);
-        const float sa = sum16(a1[r] * hv), se = sum16(a2[r] * hv);
+        const float sa = sum16(a1.v[rb][r] * hv), se = sum16(a2.v[rb][r] * hv);
         if ((l & 15) == 0) {
           pA[(size_t)(j0 >> 4) * Cp + i] = sa;
           pE[(size_t)(j0 >> 4) * Cp + i] = se;
         }
-      }
+      });
     });
     __syncthreads();
     for (int i = threadIdx.x; i < Cp; i += blockDim.x) {
@@ -268,7 +254,7 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
       gE[i] += se;
     }
     // dZD1 = Zbar D1^T ; Q2 = c o dZD1 ; cbar -= XK o dZD1
-    gemm<CT, KC, KC>(Cp, Cp, h, Zb, h, D1, h, [&](int i, int j, float x) {
+    gemm_run<CT, KC, KC, RB>(Cp, Cp, h, Zb, h, D1, h, [&](int i, int j, float x) {
       fdZD1[(size_t)i * Cp + j] = x;
       const bool lo = j <= i;
       const float q2 = lo ? cf.c[i][j] * x : 0.f;
@@ -278,25 +264,22 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
     });
     __syncthreads();
     // Xbar = diag(A) Zbar W1 + diag(E) Zbar S1 - Q2 K
-    tiles(Cp, d, [&](int i0, int j0) {
-      f4 a1 = zero4(), a2 = zero4(), a3 = zero4();
-      mma_tile<CT, KC, KC>(a1, Zb, h, i0, W1T, h, j0, h);
-      mma_tile<CT, KC, KC>(a2, Zb, h, i0, S1T, h, j0, h);
-      mma_tile<CT, KC, KC>(a3, Q2, Cp, i0, KT, Cp, j0, Cp);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
+    chunk_tiles<RB>(Cp, d, [&](int i0, int j0) {
+      RowAcc<RB> a1, a2, a3;
+      mma_run2<CT, KC, KC>(a1, a2, Zb, h, i0, W1T, S1T, h, j0, h);
+      mma_run<CT, KC, KC>(a3, Q2, Cp, i0, KT, Cp, j0, Cp);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
         const float xv = to_f(X[(size_t)i * d + j]);
-        const float xb = cf.A[i] * a1[r] + cf.E[i] * a2[r] - a3[r];
+        const float xb = cf.A[i] * a1.v[rb][r] + cf.E[i] * a2.v[rb][r] - a3.v[rb][r];
         fXb[(size_t)i * d + j] = xb;
         Xb[(size_t)i * d + j] = from_f<CT>(xb);
         XbT[(size_t)j * Cp + i] = from_f<CT>(xb);
-        const float sa = sum16(a1[r] * xv), se = sum16(a2[r] * xv);
+        const float sa = sum16(a1.v[rb][r] * xv), se = sum16(a2.v[rb][r] * xv);
         if ((l & 15) == 0) {
           pA[(size_t)(j0 >> 4) * Cp + i] = sa;
           pE[(size_t)(j0 >> 4) * Cp + i] = se;
         }
-      }
+      });
     });
     __syncthreads();
     for (int i = threadIdx.x; i < Cp; i += blockDim.x) {
@@ -311,37 +294,31 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
 
     // ================= D1bar, Gbar, second-order part of Zkbar
     // D1bar = -Pz^T Zbar - diag(cC) K W1bar'^T - diag(b) K S1bar'^T
-    tiles(Cp, h, [&](int i0, int j0) {
-      f4 a1 = zero4(), a2 = zero4(), a3 = zero4();
-      mma_tile<CT, KC, KC>(a1, PzT, Cp, i0, ZbT, Cp, j0, Cp);
-      mma_tile<CT, KC, KC>(a2, K, d, i0, Wb1, d, j0, d);
-      mma_tile<CT, KC, KC>(a3, K, d, i0, Sb1, d, j0, d);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
+    chunk_tiles<RB>(Cp, h, [&](int i0, int j0) {
+      RowAcc<RB> a1, a2, a3;
+      mma_run<CT, KC, KC>(a1, PzT, Cp, i0, ZbT, Cp, j0, Cp);
+      mma_run2<CT, KC, KC>(a2, a3, K, d, i0, Wb1, Sb1, d, j0, d);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
         const size_t e = (size_t)i * h + j;
-        const float d1b = -a1[r] - cf.cC[i] * a2[r] - cf.bb[i] * a3[r];
+        const float d1b = -a1.v[rb][r] - cf.cC[i] * a2.v[rb][r] - cf.bb[i] * a3.v[rb][r];
         const float gb = d1b * to_f(Sp[e]);
         Gb[e] = from_f<CT>(gb);
         GbT[(size_t)j * Cp + i] = from_f<CT>(gb);
         fZkp[e] = d1b * to_f(G[e]) * to_f(Spp[e]);
-      }
+      });
     });
     // T3 = D1 W1bar', T4 = D1 S1bar', T5 = Hk W2bar'^T, T6 = Hk S2bar'^T  (C x d)
-    tiles(Cp, d, [&](int i0, int j0) {
-      f4 a3 = zero4(), a4 = zero4(), a5 = zero4(), a6 = zero4();
-      mma_tile<CT, KC, KC>(a3, D1, h, i0, Wb1T, h, j0, h);
-      mma_tile<CT, KC, KC>(a4, D1, h, i0, Sb1T, h, j0, h);
-      mma_tile<CT, KC, KC>(a5, Hk, h, i0, Wb2, h, j0, h);
-      mma_tile<CT, KC, KC>(a6, Hk, h, i0, Sb2, h, j0, h);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const size_t e = (size_t)(i0 + 4 * (l >> 4) + r) * d + j0 + (l & 15);
-        fT3[e] = a3[r];
-        fT4[e] = a4[r];
-        fT5[e] = a5[r];
-        fT6[e] = a6[r];
-      }
+    chunk_tiles<RB>(Cp, d, [&](int i0, int j0) {
+      RowAcc<RB> a3, a4, a5, a6;
+      mma_run2<CT, KC, KC>(a3, a4, D1, h, i0, Wb1T, Sb1T, h, j0, h);
+      mma_run2<CT, KC, KC>(a5, a6, Hk, h, i0, Wb2, Sb2, h, j0, h);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
+        const size_t e = (size_t)i * d + j;
+        fT3[e] = a3.v[rb][r];
+        fT4[e] = a4.v[rb][r];
+        fT5[e] = a5.v[rb][r];
+        fT6[e] = a6.v[rb][r];
+      });
     });
     __syncthreads();
     // cC_bar = -K.T3 - R.T5 ; b_bar = -K.T4 - R.T6 (row dots)
@@ -361,53 +338,48 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
       }
     }
     // Rbar = -Po^T dO - diag(cC) T5 - diag(b) T6 + Gbar W2^T ; Ykbar = (2/d) Rbar ; Vbar = -Ykbar
-    tiles(Cp, d, [&](int i0, int j0) {
-      f4 a1 = zero4(), a2 = zero4();
-      mma_tile<CT, KC, KC>(a1, PoT, Cp, i0, dOT, Cp, j0, Cp);
-      mma_tile<CT, KC, KC>(a2, Gb, h, i0, W2g, h, j0, h);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
+    chunk_tiles<RB>(Cp, d, [&](int i0, int j0) {
+      RowAcc<RB> a1, a2;
+      mma_run<CT, KC, KC>(a1, PoT, Cp, i0, dOT, Cp, j0, Cp);
+      mma_run<CT, KC, KC>(a2, Gb, h, i0, W2g, h, j0, h);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
         const size_t e = (size_t)i * d + j;
-        const float rb = -a1[r] - cf.cC[i] * fT5[e] - cf.bb[i] * fT6[e] + a2[r];
-        const float ykb = (i < C) ? rscale * rb : 0.f;
-        fRb[e] = rb;
+        const float rv =
+            -a1.v[rb][r] - cf.cC[i] * fT5[e] - cf.bb[i] * fT6[e] + a2.v[rb][r];
+        const float ykb = (i < C) ? rscale * rv : 0.f;
+        fRb[e] = rv;
         Ykb[e] = from_f<CT>(ykb);
         YkbT[(size_t)j * Cp + i] = from_f<CT>(ykb);
         if (i < C) dvp[(size_t)(tok0 + i) * d + j] = -ykb;
-      }
+      });
     });
     __syncthreads();
     // Hkbar = -Q1^T H - diag(cC) R W2bar' - diag(b) R S2bar' + Ykbar W2 ;
     // Zkbar = Hkbar * s'(Zk) + D1bar * G * s''(Zk)
-    tiles(Cp, h, [&](int i0, int j0) {
-      f4 a1 = zero4(), a2 = zero4(), a3 = zero4(), a4 = zero4();
-      mma_tile<CT, KC, KC>(a1, Q1T, Cp, i0, HT, Cp, j0, Cp);
-      mma_tile<CT, KC, KC>(a2, R, d, i0, Wb2T, d, j0, d);
-      mma_tile<CT, KC, KC>(a3, R, d, i0, Sb2T, d, j0, d);
-      mma_tile<CT, KC, KC>(a4, Ykb, d, i0, W2gT, d, j0, d);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
+    chunk_tiles<RB>(Cp, h, [&](int i0, int j0) {
+      RowAcc<RB> a1, a2, a3, a4;
+      mma_run<CT, KC, KC>(a1, Q1T, Cp, i0, HT, Cp, j0, Cp);
+      mma_run2<CT, KC, KC>(a2, a3, R, d, i0, Wb2T, Sb2T, d, j0, d);
+      mma_run<CT, KC, KC>(a4, Ykb, d, i0, W2gT, d, j0, d);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
         const size_t e = (size_t)i * h + j;
-        const float hkb = -a1[r] - cf.cC[i] * a2[r] - cf.bb[i] * a3[r] + a4[r];
+        const float hkb = -a1.v[rb][r] - cf.cC[i] * a2.v[rb][r] - cf.bb[i] * a3.v[rb][r] +
+                          a4.v[rb][r];
         const float zkb = hkb * to_f(Sp[e]) + fZkp[e];
         Zkb[e] = from_f<CT>(zkb);
         ZkbT[(size_t)j * Cp + i] = from_f<CT>(zkb);
-      }
+      });
     });
     __syncthreads();
     // Kbar = -Q2^T X - diag(cC) T3 - diag(b) T4 + Zkbar W1
-    tiles(Cp, d, [&](int i0, int j0) {
-      f4 a1 = zero4(), a2 = zero4();
-      mma_tile<CT, KC, KC>(a1, Q2T, Cp, i0, XT, Cp, j0, Cp);
-      mma_tile<CT, KC, KC>(a2, Zkb, h, i0, W1gT, h, j0, h);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
+    chunk_tiles<RB>(Cp, d, [&](int i0, int j0) {
+      RowAcc<RB> a1, a2;
+      mma_run<CT, KC, KC>(a1, Q2T, Cp, i0, XT, Cp, j0, Cp);
+      mma_run<CT, KC, KC>(a2, Zkb, h, i0, W1gT, h, j0, h);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
         const size_t e = (size_t)i * d + j;
-        fKb[e] = -a1[r] - cf.cC[i] * fT3[e] - cf.bb[i] * fT4[e] + a2[r];
-      }
+        fKb[e] = -a1.v[rb][r] - cf.cC[i] * fT3[e] - cf.bb[i] * fT4[e] + a2.v[rb][r];
+      });
     });
     // ================= Q-K projection backward
     if (D.qk_proj) {
@@ -416,26 +388,24 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
           const int i = e / d, j = e - i * d;
           fMs[e] = madj[e] + madj[(size_t)j * d + i];
         }
-      gemm<CT, KC, KC>(Cp, Cp, d, Xb, d, N, d, [&](int i, int j, float x) {
+      gemm_run<CT, KC, KC, RB>(Cp, Cp, d, Xb, d, N, d, [&](int i, int j, float x) {
         const float y = j <= i ? x : 0.f;
         dXN[(size_t)i * Cp + j] = from_f<CT>(y);
         dXNT[(size_t)j * Cp + i] = from_f<CT>(y);
       });
       __syncthreads();
       // Qbar = Xbar M0 + tril(Xbar N^T) N ; Nbar = Str^T Xbar + tril(Xbar N^T)^T Q + N (Mb' + Mb'^T)
-      tiles(Cp, d, [&](int i0, int j0) {
-        f4 q1 = zero4(), n1 = zero4();
-        if (shard_qk) mma_tile<CT, KC, KC>(q1, Xb, d, i0, McT, d, j0, d);
-        mma_tile<CT, KC, KC>(q1, dXN, Cp, i0, NT, Cp, j0, Cp);
-        mma_tile<CT, KC, KC>(n1, StrT, Cp, i0, XbT, Cp, j0, Cp);
-        mma_tile<CT, KC, KC>(n1, dXNT, Cp, i0, QT, Cp, j0, Cp);
-        if (shard_qk) mma_tile<CT, KC, KC>(n1, N, d, i0, fMs, d, j0, d);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
-          if (i < C) dqp[(size_t)(tok0 + i) * d + j] = q1[r];
-          fT3[(size_t)i * d + j] = n1[r];  // Nbar (T3 is no longer needed)
-        }
+      chunk_tiles<RB>(Cp, d, [&](int i0, int j0) {
+        RowAcc<RB> q1, n1;
+        if (shard_qk) mma_run<CT, KC, KC>(q1, Xb, d, i0, McT, d, j0, d);
+        mma_run<CT, KC, KC>(q1, dXN, Cp, i0, NT, Cp, j0, Cp);
+        mma_run<CT, KC, KC>(n1, StrT, Cp, i0, XbT, Cp, j0, Cp);
+        mma_run<CT, KC, KC>(n1, dXNT, Cp, i0, QT, Cp, j0, Cp);
+        if (shard_qk) mma_run<CT, KC, KC>(n1, N, d, i0, fMs, d, j0, d);
+        chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
+          if (i < C) dqp[(size_t)(tok0 + i) * d + j] = q1.v[rb][r];
+          fT3[(size_t)i * d + j] = n1.v[rb][r];  // Nbar (T3 is no longer needed)
+        });
       });
       __syncthreads();
       // Kbar += (Nbar - N (N . Nbar)) / ||k||
@@ -469,13 +439,13 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
     const float dBC = block_sum(pb, red);
 
     // ================= gate adjoints (wave 0; lanes are chunk positions)
-    if (wave_id() == 0) {
-      const int i = l;
-      if (i < Cp) fCb[(size_t)(C - 1) * Cp + i] += gCC[i];
-      if (i == 0) {
-        gA[C - 1] += dAC;
-        gE[C - 1] += dEC;
-      }
+    for (int e = threadIdx.x; e < Cp * Cp; e += blockDim.x) {
+      const int i = e / Cp, j = e - i * Cp;
+      sCb[i][j] = fCb[e] + (i == C - 1 ? gCC[j] : 0.f);
+    }
+    if (threadIdx.x == 0) {
+      gA[C - 1] += dAC;
+      gE[C - 1] += dEC;
     }
     __syncthreads();
     if (wave_id() == 0) {
@@ -484,18 +454,18 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
       if (i < Cp) {
         // eta_bar, column sums, row sums of cbar o c
         for (int r = i; r < Cp; ++r) {
-          const float cb = fCb[(size_t)r * Cp + i];
+          const float cb = sCb[r][i];
           eb += cb * cf.ct[r][i];
           cols += cb * cf.c[r][i];
         }
         eb += gB[i] * cf.ebt[i];
-        for (int t = 0; t <= i; ++t) rows += fCb[(size_t)i * Cp + t] * cf.c[i][t];
+        for (int t = 0; t <= i; ++t) rows += sCb[i][t] * cf.c[i][t];
         // U_{i, j}, j = 0..i
         float lbp = 0.f;
         for (int j = 0; j <= i; ++j) {
-          Ui = expf(cf.lb[j] - lbp) * Ui + fCb[(size_t)i * Cp + j] * cf.eta[j];
+          Ui = expf(cf.lb[j] - lbp) * Ui + sCb[i][j] * cf.eta[j];
           lbp = cf.lb[j];
-          fU[(size_t)i * Cp + j] = Ui;
+          sU[i][j] = Ui;
         }
       }
       gEta[i] = eb;
@@ -511,7 +481,7 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
         float T = 0.f, Yv = 0.f;
         for (int i = j; i < Cp; ++i) {
           const float w = expf(cf.la[i] - cf.la[j]);
-          T += w * fU[(size_t)i * Cp + j];
+          T += w * sU[i][j];
           Yv += w * gE[i];
         }
         const float yl = Yv * expf(cf.lb[j]);
@@ -534,24 +504,32 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
     __syncthreads();
 
     // ================= adjoint of the chunk-entry state (in place)
-    tiles(h, d, [&](int i0, int j0) {  // W1bar, S1bar : h x d
-      f4 a1 = zero4(), a2 = zero4(), a3 = zero4();
-      mma_tile<CT, KC, KC>(a1, ZbT, Cp, i0, XAT, Cp, j0, Cp);
-      mma_tile<CT, KC, KC>(a2, ZkbT, Cp, i0, KT, Cp, j0, Cp);
-      mma_tile<CT, KC, KC>(a3, ZbT, Cp, i0, XET, Cp, j0, Cp);
-      f4 nw, ns;
+    state_tiles(h, d, [&](int i0, int j0) {  // W1bar, S1bar : h x d
+      RunOp<CT> o1, o2, o3;
+      o1.load(ZbT, Cp, i0, XAT, Cp, j0, Cp);
+      o2.load(ZkbT, Cp, i0, KT, Cp, j0, Cp);
+      o3.load(ZbT, Cp, i0, XET, Cp, j0, Cp);
+      const int l = lane_id_local();
+      const size_t e0 = (size_t)(i0 + 4 * (l >> 4)) * d + j0 + (l & 15);
+      f4 w, sv, ha = zero4(), nw, ns;  // all loads before the first store
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const size_t e = (size_t)(i0 + 4 * (l >> 4) + r) * d + j0 + (l & 15);
-        const float w = Wb1[e], sv = Sb1[e];
+        w[r] = Wb1[e0 + (size_t)r * d];
+        sv[r] = Sb1[e0 + (size_t)r * d];
+        if (hadj) ha[r] = hadj[e0 + (size_t)r * d];
+      }
+      const f4 a1 = o1.mma(), a2 = o2.mma(), a3 = o3.mma();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const size_t e = e0 + (size_t)r * d;
         float gp = a2[r];  // the gradient point's share
         if (hadj) {
-          gp += hadj[e];
+          gp += ha[r];
           hadj[e] = g_first ? 0.f : gp;
           if (!g_first) gp = 0.f;
         }
-        nw[r] = cf.AC * w + a1[r] + gp;
-        ns[r] = cf.EC * w + cf.BC * sv + a3[r];
+        nw[r] = cf.AC * w[r] + a1[r] + gp;
+        ns[r] = cf.EC * w[r] + cf.BC * sv[r] + a3[r];
         Wb1[e] = nw[r];
         Sb1[e] = ns[r];
       }
@@ -560,25 +538,33 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
       store4<CT>(Wb1T + et, nw);
       store4<CT>(Sb1T + et, ns);
     });
-    tiles(d, h, [&](int i0, int j0) {  // W2bar, S2bar : d x h
-      f4 a1 = zero4(), a2 = zero4(), a3 = zero4(), a4 = zero4();
-      mma_tile<CT, KC, KC>(a1, dOAT, Cp, i0, HT, Cp, j0, Cp);
-      mma_tile<CT, KC, KC>(a2, RT, Cp, i0, GbT, Cp, j0, Cp);
-      mma_tile<CT, KC, KC>(a3, YkbT, Cp, i0, HkT, Cp, j0, Cp);
-      mma_tile<CT, KC, KC>(a4, dOET, Cp, i0, HT, Cp, j0, Cp);
-      f4 nw, ns;
+    state_tiles(d, h, [&](int i0, int j0) {  // W2bar, S2bar : d x h
+      RunOp<CT> o1, o2, o3, o4;
+      o1.load(dOAT, Cp, i0, HT, Cp, j0, Cp);
+      o2.load(RT, Cp, i0, GbT, Cp, j0, Cp);
+      o3.load(YkbT, Cp, i0, HkT, Cp, j0, Cp);
+      o4.load(dOET, Cp, i0, HT, Cp, j0, Cp);
+      const int l = lane_id_local();
+      const size_t e0 = (size_t)(i0 + 4 * (l >> 4)) * h + j0 + (l & 15);
+      f4 w, sv, ha = zero4(), nw, ns;  // all loads before the first store
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const size_t e = (size_t)(i0 + 4 * (l >> 4) + r) * h + j0 + (l & 15);
-        const float w = Wb2[e], sv = Sb2[e];
+        w[r] = Wb2[e0 + (size_t)r * h];
+        sv[r] = Sb2[e0 + (size_t)r * h];
+        if (hadj) ha[r] = hadj[hd + e0 + (size_t)r * h];
+      }
+      const f4 a1 = o1.mma(), a2 = o2.mma(), a3 = o3.mma(), a4 = o4.mma();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const size_t e = e0 + (size_t)r * h;
         float gp = a2[r] + a3[r];  // the gradient point's share
         if (hadj) {
-          gp += hadj[hd + e];
+          gp += ha[r];
           hadj[hd + e] = g_first ? 0.f : gp;
           if (!g_first) gp = 0.f;
         }
-        nw[r] = cf.AC * w + a1[r] + gp;
-        ns[r] = cf.EC * w + cf.BC * sv + a4[r];
+        nw[r] = cf.AC * w[r] + a1[r] + gp;
+        ns[r] = cf.EC * w[r] + cf.BC * sv[r] + a4[r];
         Wb2[e] = nw[r];
         Sb2[e] = ns[r];
       }
@@ -587,14 +573,17 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
       store4<CT>(Sb2T + et, ns);
     });
     if (shard_qk)
-      tiles(d, d, [&](int i0, int j0) {
-        f4 a1 = zero4();
-        mma_tile<CT, KC, KC>(a1, XbT, Cp, i0, QT, Cp, j0, Cp);
+      state_tiles(d, d, [&](int i0, int j0) {
+        RunOp<CT> o;
+        o.load(XbT, Cp, i0, QT, Cp, j0, Cp);
+        const int l = lane_id_local();
+        const size_t e0 = (size_t)(i0 + 4 * (l >> 4)) * d + j0 + (l & 15);
+        f4 m;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const size_t e = (size_t)(i0 + 4 * (l >> 4) + r) * d + j0 + (l & 15);
-          madj[e] += a1[r];
-        }
+        for (int r = 0; r < 4; ++r) m[r] = madj[e0 + (size_t)r * d];
+        const f4 x = o.mma();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) madj[e0 + (size_t)r * d] = m[r] + x[r];
       });
     __syncthreads();
   }
@@ -603,14 +592,22 @@ __global__ void __launch_bounds__(512) local_bwd_kernel(LocalBwdArgs a) {
   for (size_t e = threadIdx.x; e < 2 * hd; e += blockDim.x) dst[e] = adj[e];
 }
 
-template <typename IO, typename CT, int ACT, int D_, int H_, int CP_>
-static bool try_bwd(const LocalBwdArgs& a, int units, hipStream_t st, hipError_t* err) {
-  if (D_ && (a.D.d != D_ || a.D.hid != H_ || a.D.Cp != CP_)) return false;
-  if (a.D.act != ACT) return false;
-  hipLaunchKernelGGL((local_bwd_kernel<IO, CT, ACT, D_, H_, CP_>), dim3(units), dim3(512), 0,
-                     st, a);
-  *err = hipGetLastError();
-  return true;
+template <typename IO, typename CT, int RB>
+static hipError_t launch_bwd_rb(const LocalBwdArgs& a, int units, hipStream_t st) {
+  if (a.D.act == ACT_GELU)
+    hipLaunchKernelGGL((local_bwd_kernel<IO, CT, ACT_GELU, RB>), dim3(units), dim3(512), 0, st, a);
+  else
+    hipLaunchKernelGGL((local_bwd_kernel<IO, CT, ACT_SILU, RB>), dim3(units), dim3(512), 0, st, a);
+  return hipGetLastError();
+}
+
+template <typename IO, typename CT>
+static hipError_t launch_bwd_t(const LocalBwdArgs& a, int units, hipStream_t st) {
+  switch (chunk_tile_rows(a.D.Cp)) {
+    case 4: return launch_bwd_rb<IO, CT, 4>(a, units, st);
+    case 2: return launch_bwd_rb<IO, CT, 2>(a, units, st);
+    default: return launch_bwd_rb<IO, CT, 1>(a, units, st);
+  }
 }
 
 static hipError_t launch_local_bwd_rest(const LocalBwdArgs& a, int units, hipStream_t st);
@@ -634,16 +631,8 @@ static hipError_t launch_local_bwd_rest(const LocalBwdArgs& a, int units, hipStr
     if (e != hipSuccess) return e;
   }
   if (!a.force_generic && launch_local_bwd_blk(a, units, st, &e)) return e;
-  if (a.D.bf16) {
-    if (try_bwd<__bf16, __bf16, ACT_GELU, 0, 0, 0>(a, units, st, &e) ||
-        try_bwd<__bf16, __bf16, ACT_SILU, 0, 0, 0>(a, units, st, &e))
-      return e;
-  } else {
-    if (try_bwd<float, float, ACT_GELU, 0, 0, 0>(a, units, st, &e) ||
-        try_bwd<float, float, ACT_SILU, 0, 0, 0>(a, units, st, &e))
-      return e;
-  }
-  return hipErrorInvalidValue;
+  return a.D.bf16 ? launch_bwd_t<__bf16, __bf16>(a, units, st)
+                  : launch_bwd_t<float, float>(a, units, st);
 }
 
 // dW_init[h] = sum over batch rows and shards of the per-unit adjoints

@@ -43,7 +43,8 @@ size_t local_plan(const Dims& D, LocalPlan* p, bool backward) {
   return off;
 }
 
-template <typename IO, typename CT, int ACT>
+// RB: a wave's share of a chunk's output, in 16x16 tiles below each other
+template <typename IO, typename CT, int ACT, int RB>
 __global__ void __launch_bounds__(512) local_fwd_kernel(LocalFwdArgs a) {
   __shared__ Coef cf;
   const Dims D = a.D;
@@ -109,30 +110,37 @@ __global__ void __launch_bounds__(512) local_fwd_kernel(LocalFwdArgs a) {
 
     // ---- Q-K projection: X = Q M0^T + tril(Q N^T) N ; M' = M0 + N^T N
     if (D.qk_proj) {
-      gemm<CT, KC, KC>(Cp, Cp, d, sQ, d, sN, d, [&](int i, int j, float x) {
+      gemm_run<CT, KC, KC, RB>(Cp, Cp, d, sQ, d, sN, d, [&](int i, int j, float x) {
         sS[(size_t)i * Cp + j] = from_f<CT>(j <= i ? x : 0.f);
       });
       __syncthreads();
-      {
-        const int tn = d >> 4, nt = (Cp >> 4) * tn;
-        for (int t = wave_id(); t < nt; t += num_waves()) {
-          const int i0 = (t / tn) << 4, j0 = (t % tn) << 4;
-          f4 acc = zero4();
-          if (shard_qk) mma_tile<CT, KC, KC>(acc, sQ, d, i0, Mc, d, j0, d);
-          mma_tile<CT, KC, KC>(acc, sS, Cp, i0, sNT, Cp, j0, Cp);
-          tile_each(acc, i0, j0, [&](int i, int j, float x) { sX[(size_t)i * d + j] = from_f<CT>(x); });
-        }
-      }
+      chunk_tiles<RB>(Cp, d, [&](int i0, int j0) {
+        RowAcc<RB> acc;
+        if (shard_qk) mma_run<CT, KC, KC>(acc, sQ, d, i0, Mc, d, j0, d);
+        mma_run<CT, KC, KC>(acc, sS, Cp, i0, sNT, Cp, j0, Cp);
+        chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
+          sX[(size_t)i * d + j] = from_f<CT>(acc.v[rb][r]);
+        });
+      });
       if (shard_qk)
-        gemm<CT, KC, KC>(d, d, Cp, sNT, Cp, sNT, Cp, [&](int i, int j, float x) {
-          Mn[(size_t)i * d + j] = Mc[(size_t)i * d + j] + x;
+        state_tiles(d, d, [&](int i0, int j0) {
+          RunOp<CT> o;
+          o.load(sNT, Cp, i0, sNT, Cp, j0, Cp);
+          const int l = lane_id_local();
+          const size_t e0 = (size_t)(i0 + 4 * (l >> 4)) * d + j0 + (l & 15);
+          f4 m;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) m[r] = Mc[e0 + (size_t)r * d];
+          const f4 x = o.mma();
+#pragma unroll
+          for (int r = 0; r < 4; ++r) Mn[e0 + (size_t)r * d] = m[r] + x[r];
         });
     } else {
       for (int e = threadIdx.x; e < Cp * d; e += blockDim.x) sX[e] = sQ[e];
     }
 
     // ---- Zk = K W1^T -> Hk, s'(Zk)
-    gemm<CT, KC, KC>(Cp, h, d, sK, d, W1g, d, [&](int i, int j, float z) {
+    gemm_run<CT, KC, KC, RB>(Cp, h, d, sK, d, W1g, d, [&](int i, int j, float z) {
       const ActVals av = act_all<ACT>(z);
       sHk[(size_t)i * h + j] = from_f<CT>(av.s);
       sHkT[(size_t)j * Cp + i] = from_f<CT>(av.s);
@@ -148,7 +156,7 @@ __global__ void __launch_bounds__(512) local_fwd_kernel(LocalFwdArgs a) {
     __syncthreads();
 
     // ---- R = (2/d) (Hk W2^T - V)
-    gemm<CT, KC, KC>(Cp, d, h, sHk, h, W2g, h, [&](int i, int j, float y) {
+    gemm_run<CT, KC, KC, RB>(Cp, d, h, sHk, h, W2g, h, [&](int i, int j, float y) {
       const float r = (i < C) ? rscale * (y - to_f(v[(size_t)(tok0 + i) * d + j])) : 0.f;
       sR[(size_t)i * d + j] = from_f<CT>(r);
       sRT[(size_t)j * Cp + i] = from_f<CT>(r);
@@ -158,100 +166,101 @@ __global__ void __launch_bounds__(512) local_fwd_kernel(LocalFwdArgs a) {
     __syncthreads();
 
     // ---- D1 = (R W2) * s'(Zk)
-    gemm<CT, KC, MC>(Cp, h, d, sR, d, W2g, h, [&](int i, int j, float g) {
+    gemm_run<CT, KC, MC, RB>(Cp, h, d, sR, d, W2g, h, [&](int i, int j, float g) {
       sD1T[(size_t)j * Cp + i] = from_f<CT>(g * to_f(sSp[(size_t)i * h + j]));
     });
     __syncthreads();
 
     // ---- carry into the next slot
-    {
-      const int tn = d >> 4, nt = (h >> 4) * tn;  // W1', S1' : h x d
-      for (int t = wave_id(); t < nt; t += num_waves()) {
-        const int i0 = (t / tn) << 4, j0 = (t % tn) << 4;
-        f4 aw = zero4(), as = zero4();
-        mma_tile<CT, KC, KC>(aw, sD1T, Cp, i0, sKcT, Cp, j0, Cp);
-        mma_tile<CT, KC, KC>(as, sD1T, Cp, i0, sKbT, Cp, j0, Cp);
-        const int l = lane_id();
+    state_tiles(h, d, [&](int i0, int j0) {  // W1', S1' : h x d
+      RunOp<CT> ow, os;
+      ow.load(sD1T, Cp, i0, sKcT, Cp, j0, Cp);
+      os.load(sD1T, Cp, i0, sKbT, Cp, j0, Cp);
+      const int l = lane_id_local();
+      const size_t e0 = (size_t)(i0 + 4 * (l >> 4)) * d + j0 + (l & 15);
+      f4 w, sv;  // all loads before the first store, which the compiler may not pass
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const size_t e = (size_t)(i0 + 4 * (l >> 4) + r) * d + j0 + (l & 15);
-          W1n[e] = cf.AC * W1[e] + cf.EC * S1[e] - aw[r];
-          S1n[e] = cf.BC * S1[e] - as[r];
-        }
+      for (int r = 0; r < 4; ++r) {
+        w[r] = W1[e0 + (size_t)r * d];
+        sv[r] = S1[e0 + (size_t)r * d];
       }
-    }
-    {
-      const int tn = h >> 4, nt = (d >> 4) * tn;  // W2', S2' : d x h
-      for (int t = wave_id(); t < nt; t += num_waves()) {
-        const int i0 = (t / tn) << 4, j0 = (t % tn) << 4;
-        f4 aw = zero4(), as = zero4();
-        mma_tile<CT, KC, KC>(aw, sRcT, Cp, i0, sHkT, Cp, j0, Cp);
-        mma_tile<CT, KC, KC>(as, sRbT, Cp, i0, sHkT, Cp, j0, Cp);
-        const int l = lane_id();
+      const f4 aw = ow.mma(), as = os.mma();
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const size_t e = (size_t)(i0 + 4 * (l >> 4) + r) * h + j0 + (l & 15);
-          W2n[e] = cf.AC * W2[e] + cf.EC * S2[e] - aw[r];
-          S2n[e] = cf.BC * S2[e] - as[r];
-        }
+      for (int r = 0; r < 4; ++r) {
+        W1n[e0 + (size_t)r * d] = cf.AC * w[r] + cf.EC * sv[r] - aw[r];
+        S1n[e0 + (size_t)r * d] = cf.BC * sv[r] - as[r];
       }
-    }
+    });
+    state_tiles(d, h, [&](int i0, int j0) {  // W2', S2' : d x h
+      RunOp<CT> ow, os;
+      ow.load(sRcT, Cp, i0, sHkT, Cp, j0, Cp);
+      os.load(sRbT, Cp, i0, sHkT, Cp, j0, Cp);
+      const int l = lane_id_local();
+      const size_t e0 = (size_t)(i0 + 4 * (l >> 4)) * h + j0 + (l & 15);
+      f4 w, sv;  // all loads before the first store, which the compiler may not pass
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        w[r] = W2[e0 + (size_t)r * h];
+        sv[r] = S2[e0 + (size_t)r * h];
+      }
+      const f4 aw = ow.mma(), as = os.mma();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        W2n[e0 + (size_t)r * h] = cf.AC * w[r] + cf.EC * sv[r] - aw[r];
+        S2n[e0 + (size_t)r * h] = cf.BC * sv[r] - as[r];
+      }
+    });
 
     // ---- retrieval, dual form
-    gemm<CT, KC, KC>(Cp, Cp, d, sX, d, sK, d, [&](int i, int j, float x) {
+    gemm_run<CT, KC, KC, RB>(Cp, Cp, d, sX, d, sK, d, [&](int i, int j, float x) {
       sP[(size_t)i * Cp + j] = from_f<CT>(j <= i ? cf.c[i][j] * x : 0.f);
     });
     __syncthreads();
-    {
-      const int tn = h >> 4, nt = (Cp >> 4) * tn;
-      for (int t = wave_id(); t < nt; t += num_waves()) {
-        const int i0 = (t / tn) << 4, j0 = (t % tn) << 4;
-        f4 a1 = zero4(), a2 = zero4(), a3 = zero4();
-        mma_tile<CT, KC, KC>(a1, sX, d, i0, W1, d, j0, d);
-        mma_tile<CT, KC, KC>(a2, sX, d, i0, S1, d, j0, d);
-        mma_tile<CT, KC, KC>(a3, sP, Cp, i0, sD1T, Cp, j0, Cp);
-        const int l = lane_id();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
-          const float z = cf.A[i] * a1[r] + cf.E[i] * a2[r] - a3[r];
-          sH[(size_t)i * h + j] = from_f<CT>(act_f<ACT>(z));
-        }
-      }
-    }
+    chunk_tiles<RB>(Cp, h, [&](int i0, int j0) {
+      RowAcc<RB> a1, a2, a3;
+      mma_run2<CT, KC, KC>(a1, a2, sX, d, i0, W1, S1, d, j0, d);
+      mma_run<CT, KC, KC>(a3, sP, Cp, i0, sD1T, Cp, j0, Cp);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
+        const float z = cf.A[i] * a1.v[rb][r] + cf.E[i] * a2.v[rb][r] - a3.v[rb][r];
+        sH[(size_t)i * h + j] = from_f<CT>(act_f<ACT>(z));
+      });
+    });
     __syncthreads();
-    gemm<CT, KC, KC>(Cp, Cp, h, sH, h, sHk, h, [&](int i, int j, float x) {
+    gemm_run<CT, KC, KC, RB>(Cp, Cp, h, sH, h, sHk, h, [&](int i, int j, float x) {
       sP[(size_t)i * Cp + j] = from_f<CT>(j <= i ? cf.c[i][j] * x : 0.f);
     });
     __syncthreads();
-    {
-      const int tn = d >> 4, nt = (Cp >> 4) * tn;
-      for (int t = wave_id(); t < nt; t += num_waves()) {
-        const int i0 = (t / tn) << 4, j0 = (t % tn) << 4;
-        f4 a1 = zero4(), a2 = zero4(), a3 = zero4();
-        mma_tile<CT, KC, KC>(a1, sH, h, i0, W2, h, j0, h);
-        mma_tile<CT, KC, KC>(a2, sH, h, i0, S2, h, j0, h);
-        mma_tile<CT, KC, KC>(a3, sP, Cp, i0, sRT, Cp, j0, Cp);
-        const int l = lane_id();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
-          if (i < C) o[(size_t)(tok0 + i) * d + j] = cf.A[i] * a1[r] + cf.E[i] * a2[r] - a3[r];
-        }
-      }
-    }
+    chunk_tiles<RB>(Cp, d, [&](int i0, int j0) {
+      RowAcc<RB> a1, a2, a3;
+      mma_run2<CT, KC, KC>(a1, a2, sH, h, i0, W2, S2, h, j0, h);
+      mma_run<CT, KC, KC>(a3, sP, Cp, i0, sRT, Cp, j0, Cp);
+      chunk_each<RB>(i0, j0, [&](int i, int j, int rb, int r) {
+        if (i < C)
+          o[(size_t)(tok0 + i) * d + j] =
+              cf.A[i] * a1.v[rb][r] + cf.E[i] * a2.v[rb][r] - a3.v[rb][r];
+      });
+    });
     __syncthreads();
   }
 }
 
-template <typename IO, typename CT>
-static hipError_t launch_local_fwd_t(const LocalFwdArgs& a, int units, hipStream_t st) {
+template <typename IO, typename CT, int RB>
+static hipError_t launch_local_fwd_rb(const LocalFwdArgs& a, int units, hipStream_t st) {
   dim3 grid(units), block(512);
   if (a.D.act == ACT_GELU)
-    hipLaunchKernelGGL((local_fwd_kernel<IO, CT, ACT_GELU>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((local_fwd_kernel<IO, CT, ACT_GELU, RB>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((local_fwd_kernel<IO, CT, ACT_SILU>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((local_fwd_kernel<IO, CT, ACT_SILU, RB>), grid, block, 0, st, a);
   return hipGetLastError();
+}
+
+template <typename IO, typename CT>
+static hipError_t launch_local_fwd_t(const LocalFwdArgs& a, int units, hipStream_t st) {
+  switch (chunk_tile_rows(a.D.Cp)) {
+    case 4: return launch_local_fwd_rb<IO, CT, 4>(a, units, st);
+    case 2: return launch_local_fwd_rb<IO, CT, 2>(a, units, st);
+    default: return launch_local_fwd_rb<IO, CT, 1>(a, units, st);
+  }
 }
 
 hipError_t launch_local_fwd(const LocalFwdArgs& a, int units, hipStream_t st) {
