@@ -699,7 +699,8 @@ __global__ void __launch_bounds__(256) pack_states_kernel(const float* st, const
 
 hipError_t launch_pack_states(const float* states, const float* mstates, void* out, int units,
                               int nslots, int d, int hid, int with_m, int bf16, hipStream_t st) {
-  const int tiles = ((hid + 31) / 32) * ((d + 31) / 32);
+  // the d x d sum M has more tiles than the hid x d matrices where hid < d
+  const int tiles = ((std::max(hid, d) + 31) / 32) * ((d + 31) / 32);
   const size_t slots = (size_t)units * nslots;
   const dim3 grid(tiles, (unsigned)std::min<size_t>(slots, 65535), 5);
   if (bf16)

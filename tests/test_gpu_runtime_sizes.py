@@ -44,3 +44,14 @@ def test_forced_generic(C, d):
     with tnt.kernel_family(tnt.FAMILY_GENERIC):
         got = gpu_backward(cfg, inp)
     check(cfg, got, gpu_backward(cfg, inp))
+
+
+@pytest.mark.parametrize("cfg", [cfg_of(F32, 64, 16, 50),
+                                 cfg_of(F32, 128, 32, 20, has_global=0),
+                                 cfg_of(BF16, 128, 64, 55)], ids=lambda c: c.name)
+def test_hid_below_head_size(cfg):
+    """hid < d: the packed transpose of the Q-K sum is the largest of a state's matrices
+    (only its first hid / 32 rows of tiles used to be written, and dq was wrong)."""
+    inp = make_inputs(cfg, 603)
+    print(f"\n[case] {cfg.name}", flush=True)
+    check(cfg, gpu_backward(cfg, inp), oracle_backward(cfg, inp))
