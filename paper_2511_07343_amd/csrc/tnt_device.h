@@ -251,7 +251,8 @@ __device__ __forceinline__ void gemm(int M, int N, int K, const EA* A, int lda, 
 // alike, so the sum runs over the same k.  Requests of 4 steps (128 k) lose where K is
 // 32: at d 32 they cost 5 % against single steps, requests of 2 gain 20 %.  Forward and
 // backward of 16 heads x 32768 tokens at d 128, hid 512, 64 rows: 181 ms before, 120 ms
-// now; fp32, 6 heads x 1200 tokens at d 32, hid 64, 24 and 12 rows: 4.0 ms before, 2.2 ms.
+// now; fp32, 6 heads x 1200 tokens at d 32, hid 64, 24 and 12 rows: 4.0 ms before, 2.2 ms
+// now.
 // ----------------------------------------------------------------------------
 // K steps per request; the next request is out before the products of this one
 constexpr int run_steps(int RB) { return RB > 2 ? 1 : 2; }
@@ -416,9 +417,14 @@ __device__ __forceinline__ void chunk_tiles(int Cp, int N, F&& f) {
 // RB for a chunk of Cp rows: the tallest column that divides it, since taller ones read
 // the states less often (forward of 16 heads x 32768 tokens at d 128, hid 512, 64 rows:
 // 47 ms with single tiles, 31 ms with columns of 4).  In narrow outputs they leave waves
-// idle, which costs less than it saves: at d 64 (4 columns for 8 waves) columns of 4
-// against 2 gain 1 to 3 %, at d 32 columns of 4 against 1 between -2 and +2 %.
-inline int chunk_tile_rows(int Cp) { return Cp % 64 == 0 ? 4 : Cp % 32 == 0 ? 2 : 1; }
+// idle, which costs less than it saves down to d 32: at d 64 columns of 4 against 2 gain
+// 1 to 3 %, at d 32 columns of 4 against 1 between -2 and +2 %.  At d 16 an output is
+// one column, and one wave of eight would work: 12 heads x 192 tokens at d 16, hid 32
+// take 621 us with the tallest columns, 514 with single tiles.
+inline int chunk_tile_rows(int Cp, int d) {
+  if (d < 32) return 1;
+  return Cp % 64 == 0 ? 4 : Cp % 32 == 0 ? 2 : 1;
+}
 // the 16x16 tiles of an M x N state, f(i0, j0): consecutive waves along a row, which
 // is written in whole lines
 template <typename F>

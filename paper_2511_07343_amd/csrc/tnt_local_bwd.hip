@@ -603,7 +603,7 @@ static hipError_t launch_bwd_rb(const LocalBwdArgs& a, int units, hipStream_t st
 
 template <typename IO, typename CT>
 static hipError_t launch_bwd_t(const LocalBwdArgs& a, int units, hipStream_t st) {
-  switch (chunk_tile_rows(a.D.Cp)) {
+  switch (chunk_tile_rows(a.D.Cp, a.D.d)) {
     case 4: return launch_bwd_rb<IO, CT, 4>(a, units, st);
     case 2: return launch_bwd_rb<IO, CT, 2>(a, units, st);
     default: return launch_bwd_rb<IO, CT, 1>(a, units, st);
