@@ -381,6 +381,24 @@ __device__ __forceinline__ void mma_run2(RowAcc<RB>& x, RowAcc<RB>& y, const EA*
                                          const EB* B, const EB* B2, int ldb, int j0, int K) {
   mma_run_<CT, LA, LB, RB, true>(x, y, A, lda, i0, B, B2, ldb, j0, K);
 }
+template <typename CT, int LA, int LB, typename EA, typename EB>
+__device__ __forceinline__ void mma_run(f4& acc, const EA* A, int lda, int i0, const EB* B, int ldb,
+                                        int j0, int K) {
+  RowAcc<1> x;
+  x.v[0] = acc;
+  mma_run<CT, LA, LB, 1>(x, A, lda, i0, B, ldb, j0, K);
+  acc = x.v[0];
+}
+template <typename CT, int LA, int LB, typename EA, typename EB>
+__device__ __forceinline__ void mma_run2(f4& acc, f4& acc2, const EA* A, int lda, int i0,
+                                         const EB* B, const EB* B2, int ldb, int j0, int K) {
+  RowAcc<1> x, y;
+  x.v[0] = acc;
+  y.v[0] = acc2;
+  mma_run2<CT, LA, LB, 1>(x, y, A, lda, i0, B, B2, ldb, j0, K);
+  acc = x.v[0];
+  acc2 = y.v[0];
+}
 
 // One tile's contraction over at most 64, requested by load() and multiplied by
 // mma(): several of them can be in flight together.  Both operands KC.

@@ -24,12 +24,6 @@
 
 namespace tnt {
 
-template <typename F>
-__device__ __forceinline__ void gtiles(int M, int N, F&& f) {
-  const int tn = N >> 4, nt = (M >> 4) * tn;
-  for (int t = wave_id(); t < nt; t += num_waves()) f((t / tn) << 4, (t % tn) << 4);
-}
-
 constexpr int GB_TT = 32;  // tokens per phase-A workgroup
 
 // per-workgroup scratch of phase A (CT elements / fp32 elements)
@@ -117,11 +111,11 @@ __global__ void __launch_bounds__(256) gbwd_a_kernel(GlobalArgs a, int n, void* 
   }
   __syncthreads();
   // Zk -> Hk, s', s'' ; Zq -> s'(Zq) ; Zqbar = (dO V2) * s'(Zq)
-  gtiles(TT, h, [&](int i0, int j0) {
+  chunk_tiles<1>(TT, h, [&](int i0, int j0) {
     f4 az = zero4(), aq = zero4(), ap = zero4();
-    mma_tile<CT, KC, KC>(az, sK, d, i0, V1, d, j0, d);
-    mma_tile<CT, KC, KC>(aq, sQ, d, i0, V1, d, j0, d);
-    mma_tile<CT, KC, MC>(ap, sdO, d, i0, V2, h, j0, d);
+    mma_run<CT, KC, KC>(az, sK, d, i0, V1, d, j0, d);
+    mma_run<CT, KC, KC>(aq, sQ, d, i0, V1, d, j0, d);
+    mma_run<CT, KC, MC>(ap, sdO, d, i0, V2, h, j0, d);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const size_t e = (size_t)(i0 + 4 * (l >> 4) + r) * h + j0 + (l & 15);
@@ -135,12 +129,11 @@ __global__ void __launch_bounds__(256) gbwd_a_kernel(GlobalArgs a, int n, void* 
   });
   __syncthreads();
   // R = (2/d)(Hk V2^T - V) ; T5 = Hk V2bar'^T ; T6 = Hk S2bar'^T ; Qbar = Zqbar V1
-  gtiles(TT, d, [&](int i0, int j0) {
+  chunk_tiles<1>(TT, d, [&](int i0, int j0) {
     f4 ay = zero4(), a5 = zero4(), a6 = zero4(), aq = zero4();
-    mma_tile<CT, KC, KC>(ay, sHk, h, i0, V2, h, j0, h);
-    mma_tile<CT, KC, KC>(a5, sHk, h, i0, Vb2, h, j0, h);
-    mma_tile<CT, KC, KC>(a6, sHk, h, i0, Sb2, h, j0, h);
-    mma_tile<CT, KC, MC>(aq, sZqb, h, i0, V1, d, j0, h);
+    mma_run<CT, KC, KC>(ay, sHk, h, i0, V2, h, j0, h);
+    mma_run2<CT, KC, KC>(a5, a6, sHk, h, i0, Vb2, Sb2, h, j0, h);
+    mma_run<CT, KC, MC>(aq, sZqb, h, i0, V1, d, j0, h);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
@@ -157,11 +150,10 @@ __global__ void __launch_bounds__(256) gbwd_a_kernel(GlobalArgs a, int n, void* 
   });
   __syncthreads();
   // G = R V2 ; D1 = G s' ; D1bar = -cC K V1bar'^T - b K S1bar'^T ; Gbar, Zkbar part
-  gtiles(TT, h, [&](int i0, int j0) {
+  chunk_tiles<1>(TT, h, [&](int i0, int j0) {
     f4 ag = zero4(), a1 = zero4(), a2 = zero4();
-    mma_tile<CT, KC, MC>(ag, sR, d, i0, V2, h, j0, d);
-    mma_tile<CT, KC, KC>(a1, sK, d, i0, Vb1, d, j0, d);
-    mma_tile<CT, KC, KC>(a2, sK, d, i0, Sb1, d, j0, d);
+    mma_run<CT, KC, MC>(ag, sR, d, i0, V2, h, j0, d);
+    mma_run2<CT, KC, KC>(a1, a2, sK, d, i0, Vb1, Sb1, d, j0, d);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = i0 + 4 * (l >> 4) + r;
@@ -176,11 +168,10 @@ __global__ void __launch_bounds__(256) gbwd_a_kernel(GlobalArgs a, int n, void* 
   });
   __syncthreads();
   // T3 = D1 V1bar', T4 = D1 S1bar' ; Rbar = -cC T5 - b T6 + Gbar V2^T ; Ykbar ; Vbar
-  gtiles(TT, d, [&](int i0, int j0) {
+  chunk_tiles<1>(TT, d, [&](int i0, int j0) {
     f4 a3 = zero4(), a4 = zero4(), ag = zero4();
-    mma_tile<CT, KC, MC>(a3, sD1, h, i0, Vb1, d, j0, h);
-    mma_tile<CT, KC, MC>(a4, sD1, h, i0, Sb1, d, j0, h);
-    mma_tile<CT, KC, KC>(ag, sGb, h, i0, V2, h, j0, h);
+    mma_run2<CT, KC, MC>(a3, a4, sD1, h, i0, Vb1, Sb1, d, j0, h);
+    mma_run<CT, KC, KC>(ag, sGb, h, i0, V2, h, j0, h);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
@@ -214,11 +205,10 @@ __global__ void __launch_bounds__(256) gbwd_a_kernel(GlobalArgs a, int n, void* 
     }
   }
   // Hkbar = -cC R V2bar' - b R S2bar' + Ykbar V2 ; Zkbar
-  gtiles(TT, h, [&](int i0, int j0) {
+  chunk_tiles<1>(TT, h, [&](int i0, int j0) {
     f4 a7 = zero4(), a8 = zero4(), ay = zero4();
-    mma_tile<CT, KC, MC>(a7, sR, d, i0, Vb2, h, j0, d);
-    mma_tile<CT, KC, MC>(a8, sR, d, i0, Sb2, h, j0, d);
-    mma_tile<CT, KC, MC>(ay, sYkb, d, i0, V2, h, j0, d);
+    mma_run2<CT, KC, MC>(a7, a8, sR, d, i0, Vb2, Sb2, h, j0, d);
+    mma_run<CT, KC, MC>(ay, sYkb, d, i0, V2, h, j0, d);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = i0 + 4 * (l >> 4) + r;
@@ -229,9 +219,9 @@ __global__ void __launch_bounds__(256) gbwd_a_kernel(GlobalArgs a, int n, void* 
   });
   __syncthreads();
   // Kbar = -cC T3 - b T4 + Zkbar V1
-  gtiles(TT, d, [&](int i0, int j0) {
+  chunk_tiles<1>(TT, d, [&](int i0, int j0) {
     f4 ak = zero4();
-    mma_tile<CT, KC, MC>(ak, sZkb, h, i0, V1, d, j0, h);
+    mma_run<CT, KC, MC>(ak, sZkb, h, i0, V1, d, j0, h);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = i0 + 4 * (l >> 4) + r, j = j0 + (l & 15);
@@ -242,6 +232,9 @@ __global__ void __launch_bounds__(256) gbwd_a_kernel(GlobalArgs a, int n, void* 
 }
 
 // ---- phase B: adjoint of the chunk-entry state, one hidden slice per workgroup
+// Few workgroups and long chains of products: bound by the latency of their loads, so
+// the products of one operand are requested together (forward and backward of 6 heads x
+// 1200 tokens, d 32, hid 64, fp32: 2.19 ms with single K steps, 2.05 ms).
 constexpr int GBB_HS = 16;
 constexpr int GBB_TT = 32;
 
@@ -315,15 +308,13 @@ __global__ void __launch_bounds__(256) gbwd_b_kernel(GlobalArgs a, int n) {
       const int i0 = t * 16;
       f4 az = zero4(), ag = zero4(), a1 = zero4(), a2 = zero4(), a7 = zero4(), a8 = zero4(),
          ay = zero4(), aq = zero4(), ap = zero4();
-      mma_tile<CT, KC, KC>(az, sK, d, i0, V1 + (size_t)s0 * d, d, 0, d);
-      mma_tile<CT, KC, MC>(ag, sR, d, i0, V2 + s0, h, 0, d);
-      mma_tile<CT, KC, KC>(a1, sK, d, i0, Vb1 + (size_t)s0 * d, d, 0, d);
-      mma_tile<CT, KC, KC>(a2, sK, d, i0, Sb1 + (size_t)s0 * d, d, 0, d);
-      mma_tile<CT, KC, MC>(a7, sR, d, i0, Vb2 + s0, h, 0, d);
-      mma_tile<CT, KC, MC>(a8, sR, d, i0, Sb2 + s0, h, 0, d);
-      mma_tile<CT, KC, MC>(ay, sYk, d, i0, V2 + s0, h, 0, d);
-      mma_tile<CT, KC, KC>(aq, sQ, d, i0, V1 + (size_t)s0 * d, d, 0, d);
-      mma_tile<CT, KC, MC>(ap, sdO, d, i0, V2 + s0, h, 0, d);
+      mma_run<CT, KC, KC>(az, sK, d, i0, V1 + (size_t)s0 * d, d, 0, d);
+      mma_run<CT, KC, MC>(ag, sR, d, i0, V2 + s0, h, 0, d);
+      mma_run2<CT, KC, KC>(a1, a2, sK, d, i0, Vb1 + (size_t)s0 * d, Sb1 + (size_t)s0 * d, d, 0, d);
+      mma_run2<CT, KC, MC>(a7, a8, sR, d, i0, Vb2 + s0, Sb2 + s0, h, 0, d);
+      mma_run<CT, KC, MC>(ay, sYk, d, i0, V2 + s0, h, 0, d);
+      mma_run<CT, KC, KC>(aq, sQ, d, i0, V1 + (size_t)s0 * d, d, 0, d);
+      mma_run<CT, KC, MC>(ap, sdO, d, i0, V2 + s0, h, 0, d);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = i0 + 4 * (l >> 4) + r, j = l & 15;
@@ -344,11 +335,11 @@ __global__ void __launch_bounds__(256) gbwd_b_kernel(GlobalArgs a, int n) {
     __syncthreads();
     for (int x = 0, t = wave_id(); t < nt1; t += num_waves(), ++x) {
       const int j0 = t * 16;
-      mma_tile<CT, KC, KC>(av1[x], sZkbT, TT, 0, sKT, TT, j0, TT);
-      mma_tile<CT, KC, KC>(av1[x], sZqbT, TT, 0, sQT, TT, j0, TT);
-      mma_tile<CT, KC, KC>(av2[x], sRT, TT, j0, sGbT, TT, 0, TT);
-      mma_tile<CT, KC, KC>(av2[x], sYkT, TT, j0, sHkT, TT, 0, TT);
-      mma_tile<CT, KC, KC>(av2[x], sdOT, TT, j0, sHqT, TT, 0, TT);
+      mma_run<CT, KC, KC>(av1[x], sZkbT, TT, 0, sKT, TT, j0, TT);
+      mma_run<CT, KC, KC>(av1[x], sZqbT, TT, 0, sQT, TT, j0, TT);
+      mma_run<CT, KC, KC>(av2[x], sRT, TT, j0, sGbT, TT, 0, TT);
+      mma_run<CT, KC, KC>(av2[x], sYkT, TT, j0, sHkT, TT, 0, TT);
+      mma_run<CT, KC, KC>(av2[x], sdOT, TT, j0, sHqT, TT, 0, TT);
     }
     __syncthreads();
   }
@@ -451,12 +442,7 @@ template <typename IO, typename CT, int ACT>
 static hipError_t launch_gbwd_t(const GlobalArgs& a, int n, void* scratch, size_t f32_off,
                                 hipStream_t st) {
   if (!a.force_generic) {
-    if constexpr (sizeof(IO) == 2) {
-      if (a.D.d == 64 && a.D.hid == 256)
-        return launch_gbwd_dims<IO, CT, ACT, 64, 256>(a, n, scratch, f32_off, st);
-      if (a.D.d == 128 && a.D.hid == 512)
-        return launch_gbwd_dims<IO, CT, ACT, 128, 512>(a, n, scratch, f32_off, st);
-    } else {
+    if constexpr (sizeof(IO) == 4) {
       if (a.D.d == 16 && a.D.hid == 32)
         return launch_gbwd_dims<IO, CT, ACT, 16, 32>(a, n, scratch, f32_off, st);
     }

@@ -198,19 +198,19 @@ __global__ void __launch_bounds__(256) global_p1_kernel(GlobalArgs a, int n, int
     sK[e] = from_f<CT>(i < rows ? to_f(k[e]) : 0.f);
   }
   __syncthreads();
-  gemm<CT, KC, KC>(TT, h, d, sQ, d, V1, d, [&](int i, int j, float z) {
+  gemm_run<CT, KC, KC, 1>(TT, h, d, sQ, d, V1, d, [&](int i, int j, float z) {
     sH[(size_t)i * h + j] = from_f<CT>(act_f<ACT>(z));
   });
   __syncthreads();
-  gemm<CT, KC, KC>(TT, d, h, sH, h, V2, h, [&](int i, int j, float x) {
+  gemm_run<CT, KC, KC, 1>(TT, d, h, sH, h, V2, h, [&](int i, int j, float x) {
     if (i < rows) o[(size_t)i * d + j] = x;
   });
   __syncthreads();
-  gemm<CT, KC, KC>(TT, h, d, sK, d, V1, d, [&](int i, int j, float z) {
+  gemm_run<CT, KC, KC, 1>(TT, h, d, sK, d, V1, d, [&](int i, int j, float z) {
     sH[(size_t)i * h + j] = from_f<CT>(act_f<ACT>(z));
   });
   __syncthreads();
-  gemm<CT, KC, KC>(TT, d, h, sH, h, V2, h, [&](int i, int j, float y) {
+  gemm_run<CT, KC, KC, 1>(TT, d, h, sH, h, V2, h, [&](int i, int j, float y) {
     if (i < rows) R[(size_t)i * d + j] = rscale * (y - to_f(v[(size_t)i * d + j]));
   });
 }
@@ -279,8 +279,8 @@ __global__ void __launch_bounds__(256) global_p2_kernel(GlobalArgs a, int n, int
     for (int t = wave_id(); t < TT / 16; t += num_waves()) {
       const int i0 = t * 16;
       f4 az = zero4(), ag = zero4();
-      mma_tile<CT, KC, KC>(az, sK, d, i0, V1 + (size_t)s0 * d, d, 0, d);
-      mma_tile<CT, KC, MC>(ag, sR, d, i0, V2 + s0, h, 0, d);
+      mma_run<CT, KC, KC>(az, sK, d, i0, V1 + (size_t)s0 * d, d, 0, d);
+      mma_run<CT, KC, MC>(ag, sR, d, i0, V2 + s0, h, 0, d);
       const int l = lane_id();
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -293,10 +293,10 @@ __global__ void __launch_bounds__(256) global_p2_kernel(GlobalArgs a, int n, int
     __syncthreads();
     for (int x = 0, t = wave_id(); t < nt1; t += num_waves(), ++x) {
       const int j0 = t * 16;
-      mma_tile<CT, KC, KC>(aw1[x], sD1T, TT, 0, sKcT, TT, j0, TT);
-      mma_tile<CT, KC, KC>(as1[x], sD1T, TT, 0, sKbT, TT, j0, TT);
-      mma_tile<CT, KC, KC>(aw2[x], sRcT, TT, j0, sHkT, TT, 0, TT);
-      mma_tile<CT, KC, KC>(as2[x], sRbT, TT, j0, sHkT, TT, 0, TT);
+      mma_run<CT, KC, KC>(aw1[x], sD1T, TT, 0, sKcT, TT, j0, TT);
+      mma_run<CT, KC, KC>(as1[x], sD1T, TT, 0, sKbT, TT, j0, TT);
+      mma_run<CT, KC, KC>(aw2[x], sRcT, TT, j0, sHkT, TT, 0, TT);
+      mma_run<CT, KC, KC>(as2[x], sRbT, TT, j0, sHkT, TT, 0, TT);
     }
     __syncthreads();
   }
@@ -385,11 +385,7 @@ static hipError_t launch_gfwd_dims(const GlobalArgs& a, int n, hipStream_t st) {
 template <typename IO, typename CT, int ACT>
 static hipError_t launch_gfwd_t(const GlobalArgs& a, int n, hipStream_t st) {
   if (!a.force_generic) {
-    if constexpr (sizeof(IO) == 2) {
-      if (a.D.d == 64 && a.D.hid == 256) return launch_gfwd_dims<IO, CT, ACT, 64, 256>(a, n, st);
-      if (a.D.d == 128 && a.D.hid == 512)
-        return launch_gfwd_dims<IO, CT, ACT, 128, 512>(a, n, st);
-    } else {
+    if constexpr (sizeof(IO) == 4) {
       if (a.D.d == 16 && a.D.hid == 32) return launch_gfwd_dims<IO, CT, ACT, 16, 32>(a, n, st);
     }
   }
