@@ -191,7 +191,7 @@ static void launch_gtranspose(const float* src, size_t src_stride, CT* dst, size
 // ---------------------------------------------------------------------------
 template <int D, int H, bool KS>
 constexpr size_t gfwd_tile_lds() {  // padded rows, compute type (2 bytes)
-  return (KS ? 2 * (size_t)gtile_rows<H>() * (D + 8) + 3 * (size_t)gtile_rows<H>() * (H + 8)
+  return (KS ? 2 * (size_t)gtile_rows<H>() * (D + 8) + 2 * (size_t)gtile_rows<H>() * (H + 8)
              : (size_t)gtile_rows<H>() * (D + 8) + (size_t)gtile_rows<H>() * (H + 8)) * 2;
 }
 
@@ -206,7 +206,6 @@ __global__ void __launch_bounds__(512) gfwd_tile_kernel(GlobalArgs a, int n) {
   CT* sK = sQ + TT * LD;                 // [TT][LD]   (KS only)
   CT* sHq = KS ? sK + TT * LD : sK;      // [TT][LH]
   CT* sHk = sHq + TT * LH;               // [TT][LH]   (KS only)
-  CT* sSp = sHk + TT * LH;               // [TT][LH]  s'(Zk)   (KS only)
   __shared__ float cC[TT], bb[TT];
   const Dims Dm = a.D;
   const int Ct = Dm.C, C = PAD ? gpad(Ct) : Ct;  // tokens of the chunk, its padded rows
@@ -255,6 +254,10 @@ __global__ void __launch_bounds__(512) gfwd_tile_kernel(GlobalArgs a, int n) {
   __syncthreads();
   using BH = Blk<TT, H>;
   using BD = Blk<TT, D>;
+  // a wave's block of the TT x H products is the same in every phase, so s'(Zk) stays
+  // with it in fp32
+  static_assert(BH::NB == 8, "one (TT x H) block per wave");
+  f4 sp[BH::RB][BH::CB];
   // Zq = Q V1^T -> Hq ; Zk = K V1^T -> Hk, s'(Zk)
   for_blocks<TT, H>([&](int i0, int j0) {
     f4 aq[BH::RB][BH::CB], ak[BH::RB][BH::CB];
@@ -273,7 +276,7 @@ __global__ void __launch_bounds__(512) gfwd_tile_kernel(GlobalArgs a, int n) {
         if constexpr (KS) {
           const ActVals z = act_all<ACT>(ak[rb][cb_][r]);
           sHk[e] = from_f<CT>(z.s);
-          sSp[e] = from_f<CT>(z.d1);
+          sp[rb][cb_][r] = z.d1;
           hv[r] = z.s;
         }
       }
@@ -328,7 +331,7 @@ __global__ void __launch_bounds__(512) gfwd_tile_kernel(GlobalArgs a, int n) {
     blk_each4<BH::RB, BH::CB>(i0, j0, [&](int rb, int cb_, int i, int j) {
       f4 dv;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) dv[r] = ag[rb][cb_][r] * to_f(sSp[(size_t)(i + r) * LH + j]);
+      for (int r = 0; r < 4; ++r) dv[r] = ag[rb][cb_][r] * sp[rb][cb_][r];
       store4<CT>(D1T + (size_t)j * C + r0 + i, dv);
     });
   });
@@ -468,6 +471,11 @@ __global__ void __launch_bounds__(512) gfwd_carry_kernel(GlobalArgs a, int TK) {
 // ---------------------------------------------------------------------------
 // backward, token tiles of TT rows of chunk n (exit adjoint in slot (n+1)&1)
 // ---------------------------------------------------------------------------
+template <int D, int H>
+constexpr bool gbwd_zk_lds() {
+  return H > 256 || D < 64;
+}
+
 template <typename IO, typename CT, int ACT, int D, int H, bool PAD>
 __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
   constexpr int TT = gtile_rows<H>();
@@ -476,12 +484,11 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
   CT* rA = reinterpret_cast<CT*>(smem);  // [TT][D] K
   CT* rB = rA + TT * D;                  // [TT][D] Q, then R
   CT* rC = rB + TT * D;                  // [TT][D] dO, then Ykbar
-  CT* rD = rC + TT * D;                  // [TT][H] Zk
-  CT* rE = rD + TT * H;                  // [TT][H] Hk, then D1, then Zkbar
-  CT* rF = rE + TT * H;                  // [TT][H] Zqbar, then Gbar
-  CT* rG = rF + TT * H;                  // [TT][H] D1bar G s''(Zk)
-  CT *sK = rA, *sQ = rB, *sR = rB, *sdO = rC, *sYkb = rC, *sZk = rD, *sHk = rE, *sD1 = rE,
-     *sZkb = rE, *sZqb = rF, *sGb = rF, *sZkp = rG;
+  CT* rD = rC + TT * D;                  // [TT][H] Hk, then D1, then Zkbar
+  CT* rE = rD + TT * H;                  // [TT][H] Zqbar, then Gbar
+  float* rF = reinterpret_cast<float*>(rE + TT * H);  // Zk of every wave's block (H > 256)
+  CT *sK = rA, *sQ = rB, *sR = rB, *sdO = rC, *sYkb = rC, *sHk = rD, *sD1 = rD, *sZkb = rD,
+     *sZqb = rE, *sGb = rE;
   __shared__ float cC[TT], bb[TT];
   __shared__ float gp[2][TN][TT];
   const Dims Dm = a.D;
@@ -540,6 +547,19 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
   __syncthreads();
   using BH = Blk<TT, H>;
   using BD = Blk<TT, D>;
+  // A wave's block of the TT x H products is the same in every phase: Zk and the
+  // second-order term D1bar G s''(Zk) stay with it in fp32 (as LDS copies in the
+  // compute type they were rounded).  At 512 x 128 both do not fit the registers (55 to
+  // 77 of them spilled), so Zk is in LDS there, a lane's values where it wrote them.
+  static_assert(BH::NB == 8, "one (TT x H) block per wave");
+  constexpr bool ZL = gbwd_zk_lds<D, H>();
+  f4 zkr[ZL ? 1 : BH::RB][ZL ? 1 : BH::CB], zkp[BH::RB][BH::CB];
+  auto zk_at = [&](int rb, int cb_) -> f4& {
+    if constexpr (ZL)
+      return *reinterpret_cast<f4*>(rF + (((wave_id() * BH::RB + rb) * BH::CB + cb_) * WAVE + l) * 4);
+    else
+      return zkr[rb][cb_];
+  };
   // Zk -> Hk ; Zq -> Hq ; Zqbar = (dO V2) * s'(Zq)
   for_blocks<TT, H>([&](int i0, int j0) {
     f4 ak[BH::RB][BH::CB], aq[BH::RB][BH::CB], ap[BH::RB][BH::CB];
@@ -551,6 +571,7 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
     mma_blk<CT, KC, KC, BH::RB, BH::CB, D>(ap, sdO, D, i0, V2T, D, j0);
     blk_each4<BH::RB, BH::CB>(i0, j0, [&](int rb, int cb_, int i, int j) {
       f4 hk, hq, zq;
+      zk_at(rb, cb_) = ak[rb][cb_];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const size_t e = (size_t)(i + r) * H + j;
@@ -559,7 +580,6 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
         hk[r] = act_f<ACT>(zk);
         hq[r] = z.s;
         zq[r] = ap[rb][cb_][r] * z.d1;
-        sZk[e] = from_f<CT>(zk);
         sHk[e] = from_f<CT>(hk[r]);
         sZqb[e] = from_f<CT>(zq[r]);
       }
@@ -611,17 +631,18 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
     mma_blk<CT, KC, KC, BH::RB, BH::CB, D>(a2, sK, D, i0, Sb1, D, j0);
     blk_each4<BH::RB, BH::CB>(i0, j0, [&](int rb, int cb_, int i, int j) {
       f4 gv;
+      const f4 zk = zk_at(rb, cb_);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int ii = i + r;
         const size_t e = (size_t)ii * H + j;
-        const ActVals z = act_all<ACT>(to_f(sZk[e]));
+        const ActVals z = act_all<ACT>(zk[r]);
         const float g = ag[rb][cb_][r];
         const float d1b = -cC[ii] * a1[rb][cb_][r] - bb[ii] * a2[rb][cb_][r];
         sD1[e] = from_f<CT>(g * z.d1);
         gv[r] = d1b * z.d1;
         sGb[e] = from_f<CT>(gv[r]);
-        sZkp[e] = from_f<CT>(d1b * g * z.d2);
+        zkp[rb][cb_][r] = d1b * g * z.d2;
       }
       store4<CT>(GbT + (size_t)j * C + r0 + i, gv);
     });
@@ -680,13 +701,14 @@ __global__ void __launch_bounds__(512) gbwd_tile_kernel(GlobalArgs a, int n) {
     mma_blk<CT, KC, KC, BH::RB, BH::CB, D>(ay, sYkb, D, i0, V2T, D, j0);
     blk_each4<BH::RB, BH::CB>(i0, j0, [&](int rb, int cb_, int i, int j) {
       f4 zv;
+      const f4 zk = zk_at(rb, cb_);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int ii = i + r;
         const size_t e = (size_t)ii * H + j;
-        const ActVals z = act_all<ACT>(to_f(sZk[e]));
+        const ActVals z = act_all<ACT>(zk[r]);
         const float hkb = -cC[ii] * a7[rb][cb_][r] - bb[ii] * a8[rb][cb_][r] + ay[rb][cb_][r];
-        zv[r] = hkb * z.d1 + to_f(sZkp[e]);
+        zv[r] = hkb * z.d1 + zkp[rb][cb_][r];
         sZkb[e] = from_f<CT>(zv[r]);
       }
       store4<CT>(ZkbT + (size_t)j * C + r0 + i, zv);
@@ -944,7 +966,8 @@ static hipError_t gbwd_blk_chunk(const GlobalArgs& a, int n, hipStream_t st) {
   } else {
     launch_gtranspose<CT>(a.adj + (size_t)((n + 1) & 1) * 4 * hd, 2 * 4 * hd, (CT*)a.packA, 8 * hd,
                           (CT*)a.packA + 4 * hd, 8 * hd, chains, D, H, 0xf, st);
-    const size_t l1 = (3 * (size_t)TT * D + 4 * (size_t)TT * H) * sizeof(CT);
+    const size_t l1 = (3 * (size_t)TT * D + 2 * (size_t)TT * H) * sizeof(CT) +
+                      (gbwd_zk_lds<D, H>() ? (size_t)TT * H * sizeof(float) : 0);
     auto k1 = pad ? gbwd_tile_kernel<IO, CT, ACT, D, H, true> : gbwd_tile_kernel<IO, CT, ACT, D, H, false>;
     set_lds_limit((const void*)k1);
     hipLaunchKernelGGL(k1, dim3(gpad(C) / TT, chains), dim3(512), l1, st, a, n);
