@@ -198,9 +198,7 @@ local_bwd_ret_kernel(LocalBwdArgs a, SplitPtrs P) {
              *XT = FR_(XT), *N = FR_(N), *NT = FR_(NT), *QT = FR_(QT), *StrT = FR_(StrT);
     const float *fXK = FRF_(XK), *fHH = FRF_(HH), *fHW2 = FRF_(HW2), *fHS2 = FRF_(HS2),
                 *knorm = FRF_(kn);
-    CT *ZbT = BR_(ZbT), *Q1T = BR_(Q1T), *dOT = BR_(dOT);
-    constexpr bool SC = rec::rec_scaled(CP);  // the one-CU walk's scaled operands
-    CT *const dOAT = SC ? BR_(dOAT) : nullptr, *const dOET = SC ? BR_(dOET) : nullptr;
+    CT *ZbT = BR_(ZbT), *Q1T = BR_(Q1T), *dOT = BR_(dOT), *dOAT = BR_(dOAT), *dOET = BR_(dOET);
     // the walk's exchange words of group tl, before the launch that walks the last
     // chunks; with the walk's own stores (past the L2, like its loads): plain stores may
     // stay in this XCD's L2 while the walk reads an earlier call's words from memory
@@ -243,10 +241,8 @@ local_bwd_ret_kernel(LocalBwdArgs a, SplitPtrs P) {
           const size_t et = (size_t)(j0 + q) * Cp + i;  // consecutive lanes: consecutive i
           const float w2 = fHW2[et], s2 = fHS2[et];
           dOT[et] = from_f<CT>(ox[q]);
-          if constexpr (SC) {
-            dOAT[et] = from_f<CT>(cf.A[i] * ox[q]);
-            dOET[et] = from_f<CT>(cf.E[i] * ox[q]);
-          }
+          dOAT[et] = from_f<CT>(cf.A[i] * ox[q]);
+          dOET[et] = from_f<CT>(cf.E[i] * ox[q]);
           const float oq = to_f(from_f<CT>(ox[q]));  // dO as the contractions see it
           sa += oq * w2;
           se += oq * s2;

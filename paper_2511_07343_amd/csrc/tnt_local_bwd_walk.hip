@@ -62,16 +62,18 @@ struct BWalk {
   static constexpr int PzT = 0, Q1T = PzT + CP * LC8, K = Q1T + CP * LC8, R = K + CP * LK;
   static constexpr int endA1 = R + CP * LK;
   static constexpr int Yk = 0, YkT = Yk + CP * LD8, KT = YkT + D * LC8, endA2 = KT + D * LC4;
+  // dO^T and, scaled by A_i and by E_i, X^T and dO^T
   static constexpr int dOT = (cmax(endA1, endA2) + 7) / 8 * 8;
-  static constexpr int XT = dOT + D * LC8, RT = XT + D * LC8;
+  static constexpr int XAT = dOT + D * LC8, XET = XAT + D * LC8, dOAT = XET + D * LC8,
+                       dOET = dOAT + D * LC8, RT = dOET + D * LC8;
   static constexpr int adj = (RT + D * LC4 + 7) / 8 * 8;  // W1bar^T, S1bar^T, W2bar, S2bar [D][LH]
   static constexpr int sG = adj + 4 * D * LH;             // Gbar, then Zkbar [CP][LH]
   static constexpr int total = sG + CP * LH;
   static_assert(Q1T % 8 == 0 && YkT % 8 == 0 && K % 4 == 0 && R % 4 == 0 && KT % 4 == 0 &&
-                    XT % 8 == 0 && RT % 4 == 0 && sG % 8 == 0,
+                    XAT % 8 == 0 && RT % 4 == 0 && sG % 8 == 0,
                 "aligned rows");
   static_assert(2 * DT <= NW && D % 32 == 0, "a wave per column strip of T3, T4 and of T5, T6");
-  static_assert(CP * CP / 8 <= NT && CP * D / 8 <= NT && 4 * CP <= NT, "one vector per thread");
+  static_assert(CP * CP / 8 <= NT && CP * D / 8 <= NT && 2 * CP <= NT, "one vector per thread");
 };
 
 // 16 bytes of a row at contraction offset k0 + 8 g, zero past K
@@ -134,11 +136,12 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
   constexpr size_t hd = (size_t)H * D;
   constexpr rec::RecLayout RL = rec::make_rec_layout(CP, D, H);
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ __align__(16) float sC[CP], sB[CP], sA[CP], sE[CP];
+  __shared__ __align__(16) float sC[CP], sB[CP];
   __shared__ float sc3[4], dpart[3][NW], pC[2 * DT][CP], pB[2 * DT][CP];
   CT* const L = reinterpret_cast<CT*>(smem);
   CT *sPzT = L + B::PzT, *sQ1T = L + B::Q1T, *sK = L + B::K, *sR = L + B::R, *sYk = L + B::Yk,
-     *sYkT = L + B::YkT, *sKT = L + B::KT, *sdOT = L + B::dOT, *sXT = L + B::XT, *sRT = L + B::RT,
+     *sYkT = L + B::YkT, *sKT = L + B::KT, *sdOT = L + B::dOT, *sXAT = L + B::XAT, *sXET = L + B::XET, *sdOAT = L + B::dOAT,
+     *sdOET = L + B::dOET, *sRT = L + B::RT,
      *sAdj = L + B::adj, *sGz = L + B::sG;
 
   const int blk = (int)blockIdx.x / (8 * G), rem = (int)blockIdx.x % (8 * G);
@@ -167,7 +170,7 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
   };
   // a chunk's shared operands and coefficients, one vector of each per thread
   struct Stage {
-    bf16x8 pz, q1, k, r, dO, x, rt;
+    bf16x8 pz, q1, k, r, rt;
     float cf, sc;
   };
   auto prefetch = [&](size_t t, Stage& S) {
@@ -182,15 +185,9 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
     if (tid < CP * D / 8) {
       S.k = *reinterpret_cast<const bf16x8*>(rc + RL.fc.o[rec::K] + 8 * tid);
       S.r = *reinterpret_cast<const bf16x8*>(rc + RL.fc.o[rec::R] + 8 * tid);
-      S.dO = *reinterpret_cast<const bf16x8*>(bq + RL.bc.o[rec::dOT] + 8 * tid);
-      S.x = *reinterpret_cast<const bf16x8*>(rc + RL.fc.o[rec::XT] + 8 * tid);
       S.rt = *reinterpret_cast<const bf16x8*>(rc + RL.fc.o[rec::RT] + 8 * tid);
     }
-    if (tid < 4 * CP) {
-      const int f = tid / CP;
-      const size_t o = f == 0 ? RL.ff.o[rec::cC] : f == 1 ? RL.ff.o[rec::bb] : f == 2 ? RL.ff.o[rec::cA] : RL.ff.o[rec::cE];
-      S.cf = rf[o + tid % CP];
-    }
+    if (tid < 2 * CP) S.cf = rf[(tid < CP ? RL.ff.o[rec::cC] : RL.ff.o[rec::bb]) + tid % CP];
     if (tid < 3) S.sc = rf[RL.ff.o[rec::sc] + tid];
   };
   auto put8 = [](CT* p, const bf16x8& v) {  // rows that are only 8-byte aligned
@@ -208,14 +205,9 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
       const int i = e / D, c = e % D, j = e / CP, ct = e % CP;
       put8(sK + i * LK + c, S.k);
       put8(sR + i * LK + c, S.r);
-      *reinterpret_cast<bf16x8*>(sdOT + j * LC8 + ct) = S.dO;
-      *reinterpret_cast<bf16x8*>(sXT + j * LC8 + ct) = S.x;
       put8(sRT + j * LC4 + ct, S.rt);
     }
-    if (tid < 4 * CP) {
-      const int f = tid / CP;
-      (f == 0 ? sC : f == 1 ? sB : f == 2 ? sA : sE)[tid % CP] = S.cf;
-    }
+    if (tid < 2 * CP) (tid < CP ? sC : sB)[tid % CP] = S.cf;
     if (tid < 3) sc3[tid] = S.sc;
   };
   // Ykbar = (2/d) Rbar of tile (it, strip) into LDS, row-wise and transposed; dv = -Ykbar
@@ -409,7 +401,15 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
       bf16x4 gb[TM];
       f4 zkp[TM];
       bf16x8 kt;  // K^T of the chunk, into LDS once region A is dead
-      if (const int tid = tid_local(); tid < CP * D / 8) kt = at<bf16x8>(rc + RL.fc.o[rec::KT], 8 * tid);
+      bf16x8 xa, xe, da, de, dO;  // X^T and dO^T (scaled), into LDS before the next barrier
+      if (const int tid = tid_local(); tid < CP * D / 8) {
+        kt = at<bf16x8>(rc + RL.fc.o[rec::KT], 8 * tid);
+        xa = at<bf16x8>(rc + RL.fc.o[rec::XAT], 8 * tid);
+        xe = at<bf16x8>(rc + RL.fc.o[rec::XET], 8 * tid);
+        da = at<bf16x8>(bq + RL.bc.o[rec::dOAT], 8 * tid);
+        de = at<bf16x8>(bq + RL.bc.o[rec::dOET], 8 * tid);
+        if (sl == 0) dO = at<bf16x8>(bq + RL.bc.o[rec::dOT], 8 * tid);
+      }
       {
         const Lane y;
         const int g = y.g, lc = y.lc;
@@ -473,7 +473,15 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
         for (int ks = 0; ks < HS / 32; ++ks) wf[ks] = gfrag<HS>(p + h0, (16 * strip + (l & 15)) * H, 32 * ks, l >> 4);
       };
       if (pair == 1) load_wf(rc + RL.fc.o[rec::W2r]);
-      __syncthreads();  // Gbar complete; region A is dead
+      if (const int t8 = 8 * tid_local(); t8 < CP * D) {
+        const int e = (t8 / CP) * LC8 + t8 % CP;
+        *reinterpret_cast<bf16x8*>(sXAT + e) = xa;
+        *reinterpret_cast<bf16x8*>(sXET + e) = xe;
+        *reinterpret_cast<bf16x8*>(sdOAT + e) = da;
+        *reinterpret_cast<bf16x8*>(sdOET + e) = de;
+        if (sl == 0) *reinterpret_cast<bf16x8*>(sdOT + e) = dO;
+      }
+      __syncthreads();  // Gbar, X^T and dO^T complete; region A is dead
 
       const int tid = tid_local();
       if (tid < CP * D / 8) put8(sKT + (8 * tid / CP) * LC4 + 8 * tid % CP, kt);
@@ -533,45 +541,28 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
       }
       // ---- the adjoint update's terms without Ykbar
       const float AC = sc3[0], BC = sc3[1], EC = sc3[2];
-      // the operand with its contraction rows scaled by A_i and by E_i (past CP: zeros)
-      auto scaled = [&](const bf16x8& v, int c, int g, bf16x8& xa, bf16x8& xe) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int i = CP % 32 == 0 ? 32 * c + 8 * g + q : (8 * g + q) % CP;
-          const float x = (float)v[q];
-          xa[q] = (CT)(sA[i] * x);
-          xe[q] = (CT)(sE[i] * x);
-        }
-      };
       {
         const Lane y;
         const int g = y.g, lc = y.lc;
-        bf16x8 xa[NCI], xe[NCI];
-#pragma unroll
-        for (int c = 0; c < NCI; ++c) scaled(zb[c], c, g, xa[c], xe[c]);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
           f4 nw = AC * w1[dt], ns = EC * w1[dt] + BC * s1[dt];
 #pragma unroll
           for (int c = 0; c < NCI; ++c) {
-            const bf16x8 ax = frag16<CP>(sXT + (16 * dt + lc) * LC8, 32 * c, g);
-            mma32(nw, ax, xa[c]);
-            mma32(ns, ax, xe[c]);
+            mma32(nw, frag16<CP>(sXAT + (16 * dt + lc) * LC8, 32 * c, g), zb[c]);
+            mma32(ns, frag16<CP>(sXET + (16 * dt + lc) * LC8, 32 * c, g), zb[c]);
           }
           w1[dt] = nw;
           s1[dt] = ns;
         }
-#pragma unroll
-        for (int c = 0; c < NCI; ++c) scaled(ht[c], c, g, xa[c], xe[c]);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
           const int row = 16 * dt + lc;
           f4 nw = AC * w2[dt], ns = EC * w2[dt] + BC * s2[dt];
 #pragma unroll
           for (int c = 0; c < NCI; ++c) {
-            const bf16x8 ao = frag16<CP>(sdOT + row * LC8, 32 * c, g);
-            mma32(nw, ao, xa[c]);
-            mma32(ns, ao, xe[c]);
+            mma32(nw, frag16<CP>(sdOAT + row * LC8, 32 * c, g), ht[c]);
+            mma32(ns, frag16<CP>(sdOET + row * LC8, 32 * c, g), ht[c]);
             const bf16x8 bg = TM == 1 ? join(gb[0], zero_bf4()) : join(gb[(2 * c) % TM], gb[(2 * c + 1) % TM]);
             mma32(nw, a_pair(sRT, LC4, row, 32 * c, g, TM > 1), bg);
           }

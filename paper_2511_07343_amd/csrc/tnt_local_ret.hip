@@ -186,7 +186,18 @@ local_ret_kernel(LocalFwdArgs a) {
         }
       }
       mma_tile<CT, KC, KC>(acc, sS, LDC, i0, sNT, LDC, j0, CP);
-      tile_each(acc, i0, j0, [&](int i, int j, float x) { sX[(size_t)i * LDD + j] = from_f<CT>(x); });
+      const int i = i0 + 4 * (l >> 4), j = j0 + (l & 15);
+      f4 xa, xe;  // scaled in fp32: rounded once
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        sX[(size_t)(i + r) * LDD + j] = from_f<CT>(acc[r]);
+        xa[r] = cf.A[i + r] * acc[r];
+        xe[r] = cf.E[i + r] * acc[r];
+      }
+      if (fr) {
+        store4<CT>(fr + RL.fc.o[rec::XAT] + (size_t)j * CP + i, xa);
+        store4<CT>(fr + RL.fc.o[rec::XET] + (size_t)j * CP + i, xe);
+      }
     }
   } else {
     for (int e = threadIdx.x; e < CP * D; e += 512) {
@@ -226,7 +237,7 @@ local_ret_kernel(LocalFwdArgs a) {
         qt[qq] = to_f(sQ[es]);
       }
       if constexpr (rec::rec_scaled(CP)) {
-        float kc[8], kb[8], rc[8], rb[8], xa[8], xe[8];
+        float kc[8], kb[8], rc[8], rb[8];
 #pragma unroll
         for (int qq = 0; qq < 8; ++qq) {
           const float kx = to_f(sK[ed + qq]), rx = to_f(sR[ed + qq]);
@@ -234,13 +245,19 @@ local_ret_kernel(LocalFwdArgs a) {
           kb[qq] = cf.bb[i] * kx;
           rc[qq] = cf.cC[i] * rx;
           rb[qq] = cf.bb[i] * rx;
-          xa[qq] = cf.A[it + qq] * xt[qq];
-          xe[qq] = cf.E[it + qq] * xt[qq];
         }
         st8(rec::KcC, e0, kc);
         st8(rec::Kb, e0, kb);
         st8(rec::RcC, e0, rc);
         st8(rec::Rb, e0, rb);
+      }
+      if (!qk) {  // X = Q, exact in the compute type
+        float xa[8], xe[8];
+#pragma unroll
+        for (int qq = 0; qq < 8; ++qq) {
+          xa[qq] = cf.A[it + qq] * xt[qq];
+          xe[qq] = cf.E[it + qq] * xt[qq];
+        }
         st8(rec::XAT, e0, xa);
         st8(rec::XET, e0, xe);
       }

@@ -384,10 +384,10 @@ __global__ void __launch_bounds__(512) local_walk_kernel(LocalFwdArgs a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int i = i0 + 4 * g + r;
-          const CT rv = (CT)(i < C ? rscale * (acc[r] - vv[r]) : 0.f);
-          sR[(size_t)i * LK + j0 + lc] = rv;
-          rc[r] = -cf.cC[i] * (float)rv;
-          rb[r] = -cf.bb[i] * (float)rv;
+          const float rv = i < C ? rscale * (acc[r] - vv[r]) : 0.f;
+          sR[(size_t)i * LK + j0 + lc] = (CT)rv;
+          rc[r] = -cf.cC[i] * rv;  // (scaled in fp32: rounded once)
+          rb[r] = -cf.bb[i] * rv;
         }
         *reinterpret_cast<bf16x4*>(sRcT + (size_t)(j0 + lc) * LT + i0 + 4 * g) = cvt4(rc);
         *reinterpret_cast<bf16x4*>(sRbT + (size_t)(j0 + lc) * LT + i0 + 4 * g) = cvt4(rb);
