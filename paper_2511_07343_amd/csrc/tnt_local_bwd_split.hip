@@ -589,8 +589,7 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
     f4 zkp[BCH0::RB][BCH0::CB];
     const CT *Hk = R_(Hk), *HkT = R_(HkT), *D1 = R_(D1), *ZbT = BQ_(ZbT), *HT = R_(HT),
              *Sp = R_(Sp), *Spp = R_(Spp), *G = R_(G), *PzT = R_(PzT), *Q1T = BQ_(Q1T),
-             *PoT = R_(PoT), *K = R_(K), *KT = R_(KT), *KcC = R_(KcC), *Kb = R_(Kb), *R = R_(R),
-             *RT = R_(RT), *RcC = R_(RcC), *Rb = R_(Rb), *dOT = BQ_(dOT), *XAT = R_(XAT),
+             *PoT = R_(PoT), *K = R_(K), *KT = R_(KT), *R = R_(R), *RT = R_(RT), *dOT = BQ_(dOT), *XAT = R_(XAT),
              *XET = R_(XET), *dOAT = BQ_(dOAT), *dOET = BQ_(dOET);
     const int tok0 = s * Dm.S + n * C;
     const int l = lane_id_local();
@@ -678,7 +677,9 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
     }
     // D1bar = -Pz^T Zbar - diag(cC) K W1bar'^T - diag(b) K S1bar'^T ; Gbar = D1bar * s'(Zk);
     // Hkbar so far = -Q1^T H - diag(cC) R W2bar' - diag(b) R S2bar' ; the Zkbar terms known
-    // now, D1bar * G * s''(Zk) + Hkbar * s'(Zk), are kept per fragment
+    // now, D1bar * G * s''(Zk) + Hkbar * s'(Zk), are kept per fragment.  The gate
+    // coefficients scale the accumulators' rows in fp32 (K and R scaled ahead would be
+    // rounded twice).
     for_blocks<CP, H>([&](int i0, int j0) {
       typedef CT ct4 __attribute__((ext_vector_type(4)));
       ct4 spv[BCH::RB][BCH::CB], gv4[BCH::RB][BCH::CB], sppv[BCH::RB][BCH::CB];  // ahead of the products
@@ -688,17 +689,37 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
         gv4[rb][cb] = *reinterpret_cast<const ct4*>(G + fo);
         sppv[rb][cb] = *reinterpret_cast<const ct4*>(Spp + fo);
       });
+      // diag(cC) A B0 + diag(b) A B1 = diag(cC) (A B0 + diag(b / cC) A B1) in one set of
+      // accumulators; cC >= b >= 0 (for lr >= 0), both 0 in rows past the chunk
       f4 a1[BCH::RB][BCH::CB], a2[BCH::RB][BCH::CB];
       zero_blk(a1);
       zero_blk(a2);
+      if (!zadj) {
+        f4 cc[BCH::RB], cb[BCH::RB];
+#pragma unroll
+        for (int rb = 0; rb < BCH::RB; ++rb) {
+          cc[rb] = load4<float>(RF_(cC) + i0 + 16 * rb + 4 * (l >> 4));
+          cb[rb] = load4<float>(RF_(bb) + i0 + 16 * rb + 4 * (l >> 4));
+        }
+        mma_blk<CT, KC, KC, BCH::RB, BCH::CB, D>(a1, K, d, i0, Sb1, d, j0);
+        mma_blk<CT, KC, MC, BCH::RB, BCH::CB, D>(a2, R, d, i0, Sb2, h, j0);
+        blk_each4<BCH::RB, BCH::CB>(i0, j0, [&](int rb, int cb_, int, int) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float q = cc[rb][r] != 0.f ? cb[rb][r] / cc[rb][r] : 0.f;
+            a1[rb][cb_][r] *= q;
+            a2[rb][cb_][r] *= q;
+          }
+        });
+        mma_blk<CT, KC, KC, BCH::RB, BCH::CB, D>(a1, K, d, i0, Wb1, d, j0);
+        mma_blk<CT, KC, MC, BCH::RB, BCH::CB, D>(a2, R, d, i0, Wb2, h, j0);
+        blk_each4<BCH::RB, BCH::CB>(i0, j0, [&](int rb, int cb_, int, int) {
+          a1[rb][cb_] *= cc[rb];
+          a2[rb][cb_] *= cc[rb];
+        });
+      }
       mma_blk<CT, KC, KC, BCH::RB, BCH::CB, CP>(a1, PzT, Cp, i0, ZbT, Cp, j0);
       mma_blk<CT, KC, KC, BCH::RB, BCH::CB, CP>(a2, Q1T, Cp, i0, HT, Cp, j0);
-      if (!zadj) {
-        mma_blk<CT, KC, KC, BCH::RB, BCH::CB, D>(a1, KcC, d, i0, Wb1, d, j0);
-        mma_blk<CT, KC, KC, BCH::RB, BCH::CB, D>(a1, Kb, d, i0, Sb1, d, j0);
-        mma_blk<CT, KC, MC, BCH::RB, BCH::CB, D>(a2, RcC, d, i0, Wb2, h, j0);
-        mma_blk<CT, KC, MC, BCH::RB, BCH::CB, D>(a2, Rb, d, i0, Sb2, h, j0);
-      }
       blk_each4<BCH::RB, BCH::CB>(i0, j0, [&](int rb, int cb, int i, int j) {
         f4 gv, zp;
 #pragma unroll
@@ -946,7 +967,7 @@ __global__ void __launch_bounds__(512) local_bwd_gate_kernel(LocalBwdArgs a, Spl
   if (qrow) {
     k0v = *reinterpret_cast<const f32x4*>(dkp + (size_t)qi * d + qc);
     k1v = *reinterpret_cast<const f32x4*>(dkp + (size_t)qi * d + qc + 4);
-    if constexpr (!rec::rec_scaled(CP)) {
+    if constexpr (rec::walk_sliced(CP)) {
       const float* ds = P.dks + (size_t)t * G * Cp * d + (size_t)qi * d + qc;
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -1014,7 +1035,7 @@ __global__ void __launch_bounds__(512) local_bwd_gate_kernel(LocalBwdArgs a, Spl
     }
     __syncthreads();  // LDS is reused below
   }
-  if (!fuse && qrow && (qk_here || !rec::rec_scaled(CP))) {
+  if (!fuse && qrow && (qk_here || rec::walk_sliced(CP))) {
     *reinterpret_cast<f32x4*>(dkp + (size_t)qi * d + qc) = k0v;
     *reinterpret_cast<f32x4*>(dkp + (size_t)qi * d + qc + 4) = k1v;
   }
@@ -1170,7 +1191,7 @@ template <typename CT, int CP, int D, int H>
 constexpr bool split_fits() {
   // pass C's static LDS is under 40 KB
   return split_a_lds<CT, CP, D, H>() + SPLIT_A_STATIC <= 160 * 1024 &&
-         (!rec::rec_scaled(CP) || split_b_lds<CT, CP, D, H>() + 2 * 1024 <= 160 * 1024) &&
+         (rec::walk_sliced(CP) || split_b_lds<CT, CP, D, H>() + 2 * 1024 <= 160 * 1024) &&
          split_c_lds<CT, CP, D>() + 40 * 1024 <= 160 * 1024;
 }
 
@@ -1189,7 +1210,7 @@ SplitSizes split_sizes(int units, int nch) {
   constexpr SplitLayout Y = make_split_layout(CP, D, H);
   const size_t t = (size_t)units * nch;
   constexpr int G = rec::walk_slices(CP, H);
-  return SplitSizes{t * Y.r.bc.n, t * Y.r.bf.n, rec::rec_scaled(CP) ? 0 : t * G * CP * D,
+  return SplitSizes{t * Y.r.bc.n, t * Y.r.bf.n, rec::walk_sliced(CP) ? t * G * CP * D : 0,
                     G > 1 ? (size_t)walk_groups_max(units, G) * 2 * G * CP * D : 0};
 }
 
@@ -1300,7 +1321,7 @@ bool try_split(const LocalBwdArgs* a, const Dims& Dm, int units, void* ws, hipSt
   const int sec = section_begin("local_bwd_walk", st);  // the walk of the carried adjoint alone
   auto walk = [&](const SplitPtrs& Q) {
     hipError_t we = hipErrorInvalidConfiguration;
-    if constexpr (rec::rec_scaled(CP)) {
+    if constexpr (!rec::walk_sliced(CP)) {
       auto kb = local_bwd_chain_kernel<IO, CT, ACT, D, H, CP>;
       constexpr size_t lds_b = split_b_lds<CT, CP, D, H>();
       if (!lds_fits((const void*)kb, lds_b)) return we;

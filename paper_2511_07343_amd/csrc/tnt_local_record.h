@@ -25,10 +25,9 @@ namespace rec {
 enum FwdCT {
   Hk, HkT, D1, HT, Sp, Spp, G, Sz,              // C x h (Sp, Spp, G, Sz fragment-major)
   PzT, PoT, StrT,                               // C x C
-  K, KT, KcC, Kb, R, RT, RcC, Rb,               // C x d (KcC, Kb, RcC, Rb, XAT, XET: scaled by
-  XT, XAT, XET, N, NT, QT,                      // cC, b, A, E; the first four empty unless
-                                                // rec_scaled(C))
-  W2r,                                          // d x h, the chunk-entry W2 (else)
+  K, KT, R, RT, XT, XAT, XET, N, NT, QT,        // C x d (XAT, XET: X^T scaled by A and by E)
+  W2r,                                          // d x h, the chunk-entry W2 (empty unless
+                                                // walk_sliced(C))
   FWD_CT
 };
 // forward record, fp32
@@ -59,13 +58,12 @@ enum BwdF {
 // more than reading them back; at 64 the 8 KB per chunk they take costs more.
 __host__ __device__ constexpr bool rec_coefs(int Cp) { return Cp <= 32; }
 
-// Chunks of more than 32 rows: the adjoint is walked on one CU per unit, whose kernel
-// reads K and R scaled by rows; shorter ones: in slices of the hidden units, one
-// workgroup each, which scale the products with K and R instead.
-__host__ __device__ constexpr bool rec_scaled(int Cp) { return !rec_coefs(Cp); }
+// Chunks of more than 32 rows: the adjoint is walked on one CU per unit; shorter ones: in
+// slices of the hidden units, one workgroup each.
+__host__ __device__ constexpr bool walk_sliced(int Cp) { return Cp <= 32; }
 __host__ __device__ constexpr int walk_hs(int h) { return h < 128 ? h : 128; }
 __host__ __device__ constexpr int walk_slices(int Cp, int h) {
-  return rec_scaled(Cp) ? 1 : h / walk_hs(h);
+  return walk_sliced(Cp) ? h / walk_hs(h) : 1;
 }
 
 template <int NB>
@@ -96,10 +94,9 @@ struct RecLayout {
 
 __host__ __device__ constexpr RecLayout make_rec_layout(int Cp, int d, int h) {
   const size_t C = Cp, Cd = C * d, Ch = C * h, CC = C * C, dd = (size_t)d * d;
-  const size_t sc = rec_scaled(Cp) ? Cd : 0;
-  const size_t sfc[FWD_CT] = {Ch, Ch, Ch, Ch, Ch, Ch, Ch, Ch, CC, CC, CC, Cd, Cd, sc, sc,
-                              Cd, Cd, sc, sc, Cd, Cd, Cd, Cd, Cd, Cd,
-                              rec_scaled(Cp) ? 0 : (size_t)d * h};
+  const size_t sfc[FWD_CT] = {Ch, Ch, Ch, Ch, Ch, Ch, Ch, Ch, CC, CC, CC, Cd, Cd, Cd, Cd,
+                              Cd, Cd, Cd, Cd, Cd, Cd,
+                              walk_sliced(Cp) ? (size_t)d * h : 0};
   const size_t cr = rec_coefs(Cp) ? C : 0, G = walk_slices(Cp, h);
   const size_t sff[FWD_F] = {CC, CC, Cd, Cd, C, C, C, 4, cr * (cr + 1) / 2, cr, cr};
   const size_t sbc[BWD_CT] = {Ch, CC, Cd, Cd, Cd};

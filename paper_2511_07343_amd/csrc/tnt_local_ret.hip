@@ -236,21 +236,6 @@ local_ret_kernel(LocalFwdArgs a) {
         xt[qq] = to_f(sX[es]);
         qt[qq] = to_f(sQ[es]);
       }
-      if constexpr (rec::rec_scaled(CP)) {
-        float kc[8], kb[8], rc[8], rb[8];
-#pragma unroll
-        for (int qq = 0; qq < 8; ++qq) {
-          const float kx = to_f(sK[ed + qq]), rx = to_f(sR[ed + qq]);
-          kc[qq] = cf.cC[i] * kx;
-          kb[qq] = cf.bb[i] * kx;
-          rc[qq] = cf.cC[i] * rx;
-          rb[qq] = cf.bb[i] * rx;
-        }
-        st8(rec::KcC, e0, kc);
-        st8(rec::Kb, e0, kb);
-        st8(rec::RcC, e0, rc);
-        st8(rec::Rb, e0, rb);
-      }
       if (!qk) {  // X = Q, exact in the compute type
         float xa[8], xe[8];
 #pragma unroll

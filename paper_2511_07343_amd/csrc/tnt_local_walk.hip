@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(512) local_walk_kernel(LocalFwdArgs a) {
         *reinterpret_cast<bf16x4*>(sRbT + (size_t)(j0 + lc) * LT + i0 + 4 * g) = cvt4(rb);
       }
     }
-    if (!rec::rec_scaled(CP) && fr)  // the chunk-entry W2 by rows, from its LDS copy (which the carry overwrites)
+    if (rec::walk_sliced(CP) && fr)  // the chunk-entry W2 by rows, from its LDS copy (which the carry overwrites)
       for (int e = threadIdx.x * 8; e < (int)hd; e += blockDim.x * 8)
         *reinterpret_cast<bf16x8*>(fr + RL.fc.o[rec::W2r] + e) =
             *reinterpret_cast<const bf16x8*>(sW2 + (size_t)(e / HID) * LH + e % HID);

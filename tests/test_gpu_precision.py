@@ -52,7 +52,7 @@ def test_global_activation_argument(d, hid, act):
 # outputs whose error against 64 bits is compared; ddecay and the like are sums over the
 # state, of which a case has too few for a narrow bound
 LOCAL = [(ACT_GELU, 16, ("dv", "dlr", "dW1")), (ACT_GELU, 32, ("dv", "dlr", "dW1")),
-         (ACT_SILU, 33, ("dlr", "dW1")), (ACT_GELU, 48, ("dlr", "dW1"))]
+         (ACT_SILU, 33, ("dv", "dlr", "dW1")), (ACT_GELU, 48, ("dv", "dlr", "dW1"))]
 
 
 @pytest.mark.parametrize("act,C,names", LOCAL, ids=str)
