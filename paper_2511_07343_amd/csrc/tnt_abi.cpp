@@ -106,7 +106,7 @@ struct Layout {
   size_t hd, io_elems, gates;
   // saved (or workspace-resident) chunk states
   size_t sv_g, sv_l[TNT_MAX_LOCAL], sv_m[TNT_MAX_LOCAL], sv_t[TNT_MAX_LOCAL],
-      sv_fr[TNT_MAX_LOCAL], sv_frf[TNT_MAX_LOCAL], saved_bytes;
+      sv_lo[TNT_MAX_LOCAL], sv_fr[TNT_MAX_LOCAL], sv_frf[TNT_MAX_LOCAL], saved_bytes;
   int g_chunks, l_units[TNT_MAX_LOCAL], l_chunks[TNT_MAX_LOCAL];
   int l_fslots[TNT_MAX_LOCAL];  // 0: every fp32 chunk-entry state saved; else the walk's ring
   // forward workspace
@@ -198,6 +198,11 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
     off += up((size_t)y.l_units[i] * (y.l_chunks[i] + 1) * dd * f);
     y.sv_t[i] = off;  // CT transposes of every slot, written by the forward
     off += up((size_t)y.l_units[i] * (y.l_chunks[i] + 1) * (4 * y.hd + dd) * cts);
+    y.sv_lo[i] = SIZE_MAX;
+    if (y.l_fslots[i] && rec::exact_dots(D.Cp, D.C, D.act)) {
+      y.sv_lo[i] = off;
+      off += up((size_t)y.l_units[i] * (y.l_chunks[i] + 1) * 4 * y.hd);
+    }
     // forward records of the chunk-parallel passes (shapes with both split kernels)
     y.sv_fr[i] = y.sv_frf[i] = SIZE_MAX;
     if (recs) {
@@ -480,6 +485,7 @@ tnt_status run_forward(const tnt_config* c, const Layout& y, const void* q, cons
     a.states = sv ? (float*)(sv + y.sv_l[i]) : (float*)(ws + y.ring_l[i]);
     a.mstates = sv ? (float*)(sv + y.sv_m[i]) : two_i ? (float*)(ws + y.w_nm[i]) : (float*)(ws + y.ring_m[i]);
     a.statesT = sv ? (void*)(sv + y.sv_t[i]) : two_i ? (void*)(ws + y.w_nt[i]) : nullptr;
+    a.statesLo = (sv && y.sv_lo[i] != SIZE_MAX) ? (void*)(sv + y.sv_lo[i]) : nullptr;
     a.frec = (sv && y.sv_fr[i] != SIZE_MAX) ? (void*)(sv + y.sv_fr[i]) : nullptr;
     a.frec_f = (sv && y.sv_frf[i] != SIZE_MAX) ? (float*)(sv + y.sv_frf[i]) : nullptr;
     const bool grouped = i == 0 && y.gsub0;
@@ -599,6 +605,7 @@ tnt_status run_backward(const tnt_config* c, const Layout& y, const void* q, con
     a.nslots = y.l_chunks[i] + 1;
     a.fslots = y.l_fslots[i];
     a.statesT = sv + y.sv_t[i];
+    a.statesLo = y.sv_lo[i] != SIZE_MAX ? (const void*)(sv + y.sv_lo[i]) : nullptr;
     a.frec = y.sv_fr[i] != SIZE_MAX ? (const void*)(sv + y.sv_fr[i]) : nullptr;
     a.frec_f = y.sv_frf[i] != SIZE_MAX ? (const float*)(sv + y.sv_frf[i]) : nullptr;
     a.adj = (float*)(ws + y.b_adj_l[i]);

@@ -11,7 +11,7 @@ namespace tnt {
 // Header at the start of a saved buffer (tnt_mem_fwd -> tnt_mem_bwd): which
 // layout, kernel family, ring sizes and configuration wrote it.
 constexpr uint32_t SAVED_MAGIC = 0x544e5453u;  // "STNT"
-constexpr uint32_t SAVED_LAYOUT_VERSION = 7;
+constexpr uint32_t SAVED_LAYOUT_VERSION = 8;
 constexpr size_t SAVED_HEADER_BYTES = 256;
 struct SavedHeader {
   uint32_t magic, layout_version, family, pad;
@@ -58,6 +58,8 @@ struct LocalFwdArgs {
                                                          // W1^T, W2^T, S1^T, S2^T, M^T of every slot
   void* fsplit;                                          // null, or local_fwd_split_bytes(D, units)
                                                          // bytes: the split forward (saved states only)
+  void* statesLo;                                        // null, or [units][nslots][4*hid*d] bytes: what
+                                                         // the rounding of the copies left (rem_pack)
   void* frec; float* frec_f;                             // null, or the forward records (saved
                                                          // buffer) the backward passes read
   int nslots;
@@ -79,6 +81,7 @@ struct LocalBwdArgs {
   const float* mstates;
   const void* statesT;                                   // CT [units][nslots][4*hid*d + d*d]:
                                                          // W1^T, W2^T, S1^T, S2^T, M^T
+  const void* statesLo;                                  // as in LocalFwdArgs
   int nslots;
   int fslots;                                            // nonzero: `states` holds only the walk's
                                                          // ring, not every chunk-entry state

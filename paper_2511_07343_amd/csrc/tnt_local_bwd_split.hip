@@ -28,6 +28,7 @@
 #include "tnt_local_bwd_helpers.h"
 #include "tnt_local_bwd_split.h"
 #include "tnt_local_record.h"
+#include "tnt_regtile.h"
 
 #include <algorithm>
 
@@ -475,10 +476,10 @@ local_bwd_ret_kernel(LocalBwdArgs a, SplitPtrs P) {
 // the elementwise products with two compute-type matrices S0, S1 of the B
 // operands' shape (layout SL: KC as the B operands, MC transposed, leading
 // dimension lds), both sides as the MFMAs see them (compute type):
-// pa += B0 . S0, pe += B0 . S1, pb += B1 . S1.
-template <int RBN, int K, int G, int SL, int BL = KC, typename EB = float>
+// pa += B0 . S0, pe += B0 . S1, pb += B1 . S1 (DOTS).
+template <int RBN, int K, int G, int SL, bool DOTS, int BL = KC>
 __device__ __forceinline__ void mma_pair_dots(f4 (&t0)[RBN], f4 (&t1)[RBN], const __bf16* A,
-                                              int lda, const EB* B0, const EB* B1, int ldb,
+                                              int lda, const float* B0, const float* B1, int ldb,
                                               int j0, const __bf16* S0, const __bf16* S1,
                                               int lds, float& pa, float& pe, float& pb) {
   typedef Mma<__bf16> MM;
@@ -497,8 +498,10 @@ __device__ __forceinline__ void mma_pair_dots(f4 (&t0)[RBN], f4 (&t1)[RBN], cons
         fa[st][r] = MM::template load<KC>(A, lda, 16 * r + (l & 15), k0, K, nullptr);
       f0[st] = MM::template load<BL>(B0, ldb, jr, k0, K, nullptr);
       f1[st] = MM::template load<BL>(B1, ldb, jr, k0, K, nullptr);
-      s0[st] = MM::template load<SL>(S0, lds, jr, k0, K, nullptr);
-      s1[st] = MM::template load<SL>(S1, lds, jr, k0, K, nullptr);
+      if constexpr (DOTS) {
+        s0[st] = MM::template load<SL>(S0, lds, jr, k0, K, nullptr);
+        s1[st] = MM::template load<SL>(S1, lds, jr, k0, K, nullptr);
+      }
     }
 #pragma unroll
     for (int st = 0; st < G; ++st) {
@@ -507,14 +510,15 @@ __device__ __forceinline__ void mma_pair_dots(f4 (&t0)[RBN], f4 (&t1)[RBN], cons
         MM::mma(t0[r], fa[st][r], f0[st]);
         MM::mma(t1[r], fa[st][r], f1[st]);
       }
+      if constexpr (DOTS)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const float x0 = (float)f0[st][q], x1 = (float)f1[st][q];
-        const float y0 = (float)s0[st][q], y1 = (float)s1[st][q];
-        pa += x0 * y0;
-        pe += x0 * y1;
-        pb += x1 * y1;
-      }
+        for (int q = 0; q < 8; ++q) {
+          const float x0 = (float)f0[st][q], x1 = (float)f1[st][q];
+          const float y0 = (float)s0[st][q], y1 = (float)s1[st][q];
+          pa += x0 * y0;
+          pe += x0 * y1;
+          pb += x1 * y1;
+        }
     }
   }
 }
@@ -526,7 +530,7 @@ __device__ __forceinline__ void mma_pair_dots(f4 (&t0)[RBN], f4 (&t1)[RBN], cons
 // register-resident adjoint and takes 57 us a chunk on two CUs, this one 86 us on one
 // (128 units, workload of B 4, H 8, L 8192: step 4.62 ms here, 4.98 ms there).
 // ===========================================================================
-template <typename IO, typename CT, int ACT, int D, int H, int CP>
+template <typename IO, typename CT, int ACT, int D, int H, int CP, bool LO>
 __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, SplitPtrs P) {
   __shared__ float sC[MAXC], sB[MAXC], sc3[4];
   __shared__ float dpart[3][16];
@@ -595,6 +599,7 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
     const int l = lane_id_local();
     const CT* pk = (const CT*)a.statesT + ((size_t)u * a.nslots + n) * (4 * hd + (size_t)d * d);
     const CT *W1T = pk, *W2T = pk + hd, *S1T = pk + 2 * hd, *S2T = pk + 3 * hd;
+    const rem2* lo = LO ? (const rem2*)a.statesLo + ((size_t)u * a.nslots + n) * (hd / 2) : nullptr;
     using BCD = Blk<CP, D>;
     using BCH = Blk<CP, H>;
     auto fofs = [&](int i0, int j0, int rb, int cb) -> size_t {
@@ -606,6 +611,16 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
       return ((size_t)((blk * BCD::RB + rb) * BCD::CB + cb) * WAVE + l) * 4;
     };
 
+    auto put_dots = [&](float pa, float pe, float pb) {
+      pa = wave_sum(pa);
+      pe = wave_sum(pe);
+      pb = wave_sum(pb);
+      if (l == 0) {
+        dpart[0][wave_id()] = pa;
+        dpart[1][wave_id()] = pe;
+        dpart[2][wave_id()] = pb;
+      }
+    };
     // ---- phase 1: chunk coefficients; T3..T6 with the adjoint . state dot products
     // (dA_C, dE_C, dB_C); D1bar -> Gbar; the first part of Hkbar
     if (threadIdx.x < Cp) {
@@ -620,7 +635,8 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
     // The strips of the adjoint's B operands cover it whole: the adjoint . state products
     // are taken from the same fragments, both sides as the MFMAs see them (the adjoint
     // read down its fp32 columns and rounded to the compute type, the state from its
-    // transposed compute-type copy).
+    // transposed compute-type copy).  LO: in phase 4 instead, where the fp32 adjoint is in
+    // the registers, from the state copies and their remainders.
     {
       static_assert(D == 64, "two pairs of four column strips for eight waves");
       static_assert(sizeof(CT) == 2, "bf16 operands");
@@ -642,18 +658,11 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
       }
       if (zadj) {
       } else if (pair == 0) {
-        mma_pair_dots<RBN, H, 4, KC, MC>(t0, t1, D1, h, Wb1, Sb1, d, j0, W1T, S1T, h, pa, pe, pb);
+        mma_pair_dots<RBN, H, 4, KC, !LO, MC>(t0, t1, D1, h, Wb1, Sb1, d, j0, W1T, S1T, h, pa, pe, pb);
       } else {
-        mma_pair_dots<RBN, H, 4, MC>(t0, t1, Hk, h, Wb2, Sb2, h, j0, W2T, S2T, d, pa, pe, pb);
+        mma_pair_dots<RBN, H, 4, MC, !LO>(t0, t1, Hk, h, Wb2, Sb2, h, j0, W2T, S2T, d, pa, pe, pb);
       }
-      pa = wave_sum(pa);
-      pe = wave_sum(pe);
-      pb = wave_sum(pb);
-      if (l == 0) {
-        dpart[0][wave_id()] = pa;
-        dpart[1][wave_id()] = pe;
-        dpart[2][wave_id()] = pb;
-      }
+      if constexpr (!LO) put_dots(pa, pe, pb);
       float* const q0 = pair == 0 ? pC : pC2;
       float* const q1 = pair == 0 ? pB : pB2;
       float* const f0 = pair == 0 ? fT3 : fT5;
@@ -747,12 +756,15 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
       BQF_(gCC)[i] = -sc_;
       BQF_(gB)[i] = -sb_;
     }
-    if (threadIdx.x < 3) {
-      float x = 0.f;
+    auto sum_dots = [&]() {
+      if (threadIdx.x < 3) {
+        float x = 0.f;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) x += dpart[threadIdx.x][w];
-      BQF_(dots)[threadIdx.x] = x;
-    }
+        for (int w = 0; w < 8; ++w) x += dpart[threadIdx.x][w];
+        BQF_(dots)[threadIdx.x] = x;
+      }
+    };
+    if constexpr (!LO) sum_dots();
     for_blocks<CP, D>([&](int i0, int j0) {
       f4 a1[BCD::RB][BCD::CB], a2[BCD::RB][BCD::CB];
       zero_blk(a1);
@@ -827,6 +839,36 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
     const float AC = sc3[0], BC = sc3[1], EC = sc3[2];
     using BHD = Blk<H, D>;
     using BDH = Blk<D, H>;
+    float pa = 0.f, pe = 0.f, pb = 0.f;  // LO: the adjoint . state products
+    // the state at a block's tiles: four rows of its transposed copies and the remainders,
+    // requested ahead of the block's products
+    auto load_state = [&](auto& L, const CT* W, const CT* S, const rem2* rem, auto&& at, auto&& tile, int i0, int j0) {
+      blk_each4<BHD::RB, BHD::CB>(i0, j0, [&](int rb, int cb, int i, int j) {
+        const uint32_t o = at(i, j);
+        L.w[rb][cb] = *reinterpret_cast<const bf16x4*>(W + o);
+        L.s[rb][cb] = *reinterpret_cast<const bf16x4*>(S + o);
+        L.r[rb][cb] = rem[tile(i0 / 16 + rb, j0 / 16 + cb)];
+      });
+    };
+    auto add_dots = [&](const auto& ow, const auto& os, const auto& L) {
+#pragma unroll
+      for (int rb = 0; rb < BHD::RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < BHD::CB; ++cb) {
+          const f4 y0 = rem_unpack(L.w[rb][cb], L.r[rb][cb][0]), y1 = rem_unpack(L.s[rb][cb], L.r[rb][cb][1]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            pa += ow[rb][cb][r] * y0[r];
+            pe += ow[rb][cb][r] * y1[r];
+            pb += os[rb][cb][r] * y1[r];
+          }
+        }
+    };
+    struct StateBlk {
+      bf16x4 w[BHD::RB][BHD::CB], s[BHD::RB][BHD::CB];
+      rem2 r[BHD::RB][BHD::CB];
+    };
+    static_assert(BHD::RB == BDH::RB && BHD::CB == BDH::CB, "blocks of one shape");
     for_blocks<H, D>([&](int i0, int j0) {  // W1bar, S1bar : h x d
       f4 a1[BHD::RB][BHD::CB], a3[BHD::RB][BHD::CB], ow[BHD::RB][BHD::CB], os[BHD::RB][BHD::CB];
       zero_blk(ow);
@@ -839,6 +881,11 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
             os[rb][cb][r] = Sb1[(size_t)(i + r) * d + j];
           }
         });
+      StateBlk L;
+      if (LO && !zadj) 
+        load_state(L, W1T, S1T, lo, [](int i, int j) { return j * H + i; },
+                   [&](int ti, int tj) { return rem_ofs(D / 16, tj, ti, l); }, i0, j0);
+      if (LO && !zadj) add_dots(ow, os, L);
       zero_blk(a1);
       zero_blk(a3);
       mma_blk_shared<CT, BHD::RB, BHD::CB, CP, true>(a1, a3, ZbT, ZbT, Cp, i0, XAT, XET, Cp, j0);
@@ -868,6 +915,11 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
             os[rb][cb][r] = Sb2[(size_t)(i + r) * h + j];
           }
         });
+      StateBlk L;
+      if (LO && !zadj) 
+        load_state(L, W2T, S2T, lo + hd / 4, [](int i, int j) { return j * D + i; },
+                   [&](int ti, int tj) { return rem_ofs(D / 16, ti, tj, l); }, i0, j0);
+      if (LO && !zadj) add_dots(ow, os, L);
       zero_blk(a1);
       zero_blk(a4);
       mma_blk_shared<CT, BDH::RB, BDH::CB, CP, false>(a1, a4, dOAT, dOET, Cp, i0, HT, HT, Cp, j0);
@@ -886,7 +938,9 @@ __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, Sp
         }
       });
     });
+    if constexpr (LO) put_dots(pa, pe, pb);
     __syncthreads();
+    if constexpr (LO) sum_dots();
 #undef R_
 #undef RF_
 #undef BQ_
@@ -1322,7 +1376,7 @@ bool try_split(const LocalBwdArgs* a, const Dims& Dm, int units, void* ws, hipSt
   auto walk = [&](const SplitPtrs& Q) {
     hipError_t we = hipErrorInvalidConfiguration;
     if constexpr (!rec::walk_sliced(CP)) {
-      auto kb = local_bwd_chain_kernel<IO, CT, ACT, D, H, CP>;
+      auto kb = a->statesLo ? local_bwd_chain_kernel<IO, CT, ACT, D, H, CP, true> : local_bwd_chain_kernel<IO, CT, ACT, D, H, CP, false>;
       constexpr size_t lds_b = split_b_lds<CT, CP, D, H>();
       if (!lds_fits((const void*)kb, lds_b)) return we;
       set_lds_limit((const void*)kb);

@@ -127,7 +127,8 @@ __device__ __forceinline__ float row_sum16(float x) {
 
 }  // namespace
 
-template <int D, int H, int CP>
+// LO: the adjoint . state products in fp32, from the registers and the two state copies
+template <int D, int H, int CP, bool LO>
 __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(LocalBwdArgs a, SplitPtrs P) {
   using CT = __bf16;
   using B = BWalk<D, H, CP>;
@@ -167,6 +168,60 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
       *reinterpret_cast<bf16x4*>(p + 2 * D * LH) = cvt4(quad_transpose(w2[dt]));
       *reinterpret_cast<bf16x4*>(p + 3 * D * LH) = cvt4(quad_transpose(s2[dt]));
     }
+  };
+  auto put_dots = [&](float pa, float pe, float pb) {  // summed after the chunk's first barrier
+    pa = wave_sum(pa);
+    pe = wave_sum(pe);
+    pb = wave_sum(pb);
+    if (lane_id_local() == 0) {
+      dpart[0][w] = pa;
+      dpart[1][w] = pe;
+      dpart[2][w] = pb;
+    }
+  };
+  // LO: a chunk's adjoint . state products, taken at the end of the chunk before (in the
+  // order of the walk), where the adjoint is final and few registers are in use (beside
+  // the chunk's first products, or requested ahead of the last barrier, they spilled 80
+  // registers at 16 rows; here none).  The state at the lane's adjoint
+  // tiles: copy and remainder of W1, S1 (by rows, transposed within the quad) and W2, S2.
+  struct StatePairs {
+    bf16x4 v[LO ? 4 : 1][DT];
+    rem2 r[LO ? 2 : 1][DT];
+  };
+  auto load_pairs = [&](int u, int n, StatePairs& L) {
+    const size_t slot = (size_t)u * a.nslots + n;
+    const CT* hi = launder_global((const CT*)a.statesT + slot * (4 * hd + (size_t)D * D));
+    const rem2* lo = launder_global((const rem2*)a.statesLo + slot * (hd / 2));
+    const Lane y;
+    const int q = y.lc & 3, h = h0 + 16 * w + y.lc;
+#pragma unroll
+    for (int m = 0; m < (LO ? 4 : 0); ++m)  // W1, W2, S1, S2
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        const uint32_t e = m % 2 ? h * D + 16 * dt + 4 * y.g : (16 * dt + 4 * y.g + q) * H + h - q;
+        L.v[m][dt] = at<bf16x4>(hi + m * hd, e);
+        if (m < 2) L.r[m][dt] = lo[m * hd / 4 + rem_ofs(DT, dt, h0 / 16 + w, m ? y.l : rem_lane1(y.l))];
+      }
+  };
+  auto exact_dots = [&](const StatePairs& L) {
+    float pa = 0.f, pe = 0.f, pb = 0.f;
+    auto value = [&](int m, int dt) {
+      const f4 x = rem_unpack(L.v[m][dt], L.r[m % 2][dt][m / 2]);
+      return m % 2 ? x : quad_transpose(x);
+    };
+#pragma unroll
+    for (int m = 0; m < (LO ? 2 : 0); ++m)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        const f4 y0 = value(m, dt), y1 = value(m + 2, dt), x0 = m ? w2[dt] : w1[dt], x1 = m ? s2[dt] : s1[dt];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          pa += x0[r] * y0[r];
+          pe += x0[r] * y1[r];
+          pb += x1[r] * y1[r];
+        }
+      }
+    put_dots(pa, pe, pb);
   };
   // a chunk's shared operands and coefficients, one vector of each per thread
   struct Stage {
@@ -250,6 +305,11 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
       }
     }
     write_copies();
+    if constexpr (LO) {
+      StatePairs L;
+      load_pairs(u, nlast, L);
+      exact_dots(L);
+    }
     __syncthreads();
 
     for (int n = nlast; n >= P.n0; --n, ++turn) {
@@ -264,8 +324,9 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
 
       // ---- T3, T4 (D1 with W1bar', S1bar') or T5, T6 (Hk with W2bar', S2bar') on the wave's
       // strip, and the adjoint . state products (W1bar, S1bar from their LDS copies, W2bar,
-      // S2bar from the registers, the state from its compute-type copies).  Every load of
-      // the phase is requested ahead of the first product: one memory round trip.
+      // S2bar from the registers, the state from its compute-type copies; LO: done already).
+      // Every load of the phase is requested ahead of the first product: one memory round
+      // trip.
       f4 t0[TM], t1[TM];
 #pragma unroll
       for (int it = 0; it < TM; ++it) t0[it] = t1[it] = zero4();
@@ -292,17 +353,19 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
         constexpr int IT = D * HS / 8 / NT;
         static_assert(D * HS / 8 % NT == 0, "whole vectors per thread");
         bf16x8 y0[IT], y1[IT];
-#pragma unroll
-        for (int p = 0; p < IT; ++p) {
-          const int v = tid + p * NT, j = v / (HS / 8), c = 8 * (v % (HS / 8));
-          y0[p] = at<bf16x8>(W1T, j * H + h0 + c);
-          y1[p] = at<bf16x8>(S1T, j * H + h0 + c);
-        }
         bf16x4 v0[DT], v1[DT];
+        if constexpr (!LO) {
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          v0[dt] = at<bf16x4>(W2T, hrow * D + 16 * dt + 4 * g);
-          v1[dt] = at<bf16x4>(S2T, hrow * D + 16 * dt + 4 * g);
+          for (int p = 0; p < IT; ++p) {
+            const int v = tid + p * NT, j = v / (HS / 8), c = 8 * (v % (HS / 8));
+            y0[p] = at<bf16x8>(W1T, j * H + h0 + c);
+            y1[p] = at<bf16x8>(S1T, j * H + h0 + c);
+          }
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) {
+            v0[dt] = at<bf16x4>(W2T, hrow * D + 16 * dt + 4 * g);
+            v1[dt] = at<bf16x4>(S2T, hrow * D + 16 * dt + 4 * g);
+          }
         }
         Stage S;
         prefetch(t, S);
@@ -327,34 +390,29 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
             if (k0 + KG < NKH) load_fa(k0 + KG);
           }
         }
-        float pa = 0.f, pe = 0.f, pb = 0.f;
+        if constexpr (!LO) {
+          float pa = 0.f, pe = 0.f, pb = 0.f;
 #pragma unroll
-        for (int p = 0; p < IT; ++p) {
-          const int v = tid + p * NT, j = v / (HS / 8), c = 8 * (v % (HS / 8));
-          const bf16x8 x0 = *reinterpret_cast<const bf16x8*>(sAdj + j * LH + c);
-          const bf16x8 x1 = *reinterpret_cast<const bf16x8*>(sAdj + D * LH + j * LH + c);
+          for (int p = 0; p < IT; ++p) {
+            const int v = tid + p * NT, j = v / (HS / 8), c = 8 * (v % (HS / 8));
+            const bf16x8 x0 = *reinterpret_cast<const bf16x8*>(sAdj + j * LH + c);
+            const bf16x8 x1 = *reinterpret_cast<const bf16x8*>(sAdj + D * LH + j * LH + c);
 #pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            pa += (float)x0[q] * (float)y0[p][q];
-            pe += (float)x0[q] * (float)y1[p][q];
-            pb += (float)x1[q] * (float)y1[p][q];
+            for (int q = 0; q < 8; ++q) {
+              pa += (float)x0[q] * (float)y0[p][q];
+              pe += (float)x0[q] * (float)y1[p][q];
+              pb += (float)x1[q] * (float)y1[p][q];
+            }
           }
-        }
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+          for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            pa += w2[dt][r] * (float)v0[dt][r];
-            pe += w2[dt][r] * (float)v1[dt][r];
-            pb += s2[dt][r] * (float)v1[dt][r];
-          }
-        pa = wave_sum(pa);
-        pe = wave_sum(pe);
-        pb = wave_sum(pb);
-        if (l == 0) {
-          dpart[0][w] = pa;
-          dpart[1][w] = pe;
-          dpart[2][w] = pb;
+            for (int r = 0; r < 4; ++r) {
+              pa += w2[dt][r] * (float)v0[dt][r];
+              pe += w2[dt][r] * (float)v1[dt][r];
+              pb += s2[dt][r] * (float)v1[dt][r];
+            }
+          put_dots(pa, pe, pb);
         }
         stage(S);
       }
@@ -676,6 +734,11 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
           *reinterpret_cast<f32x4*>(dk + (size_t)(i + q) * D + j - q) = f32x4{v[0], v[1], v[2], v[3]};
         }
       }
+      if (LO && n > P.n0) {
+        StatePairs L;
+        load_pairs(u, n - 1, L);
+        exact_dots(L);
+      }
     }
     // the adjoint for the launch of the earlier chunks, or of the learned init
     {
@@ -698,12 +761,12 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
 }
 
 namespace {
-template <int D, int H, int CP>
+template <int D, int H, int CP, bool LO>
 bool try_walk(const LocalBwdArgs& a, const SplitPtrs& P, hipStream_t st, hipError_t* err) {
-  if (a.D.d != D || a.D.hid != H || a.D.Cp != CP) return false;
+  if (a.D.d != D || a.D.hid != H || a.D.Cp != CP || (a.statesLo != nullptr) != LO) return false;
   using B = BWalk<D, H, CP>;
   constexpr size_t lds = (size_t)B::total * sizeof(__bf16);
-  auto kern = local_bwd_walk_kernel<D, H, CP>;
+  auto kern = local_bwd_walk_kernel<D, H, CP, LO>;
   if (!lds_fits((const void*)kern, lds)) {
     *err = hipErrorInvalidConfiguration;
     return true;
@@ -717,7 +780,8 @@ bool try_walk(const LocalBwdArgs& a, const SplitPtrs& P, hipStream_t st, hipErro
 }  // namespace
 
 bool launch_local_bwd_walk(const LocalBwdArgs& a, const SplitPtrs& P, hipStream_t st, hipError_t* err) {
-  return try_walk<64, 256, 32>(a, P, st, err) || try_walk<64, 256, 16>(a, P, st, err);
+  return try_walk<64, 256, 32, false>(a, P, st, err) || try_walk<64, 256, 16, false>(a, P, st, err) ||
+         try_walk<64, 256, 32, true>(a, P, st, err) || try_walk<64, 256, 16, true>(a, P, st, err);
 }
 
 }  // namespace tnt

@@ -81,7 +81,8 @@ constexpr size_t walk_lds_bytes() {
   return (size_t)WalkLds<D, HID, CP>::total * sizeof(__bf16);
 }
 
-template <typename IO, int ACT, int D, int HID, int CP>
+// LO: also what the rounding of the state copies left (a.statesLo)
+template <typename IO, int ACT, int D, int HID, int CP, bool LO>
 __global__ void __launch_bounds__(512) local_walk_kernel(LocalFwdArgs a) {
   using CT = __bf16;
   using Ly = WalkLds<D, HID, CP>;
@@ -114,6 +115,7 @@ __global__ void __launch_bounds__(512) local_walk_kernel(LocalFwdArgs a) {
   const float* dec = a.decay + chain * Dm.L;
   constexpr size_t PS = 4 * hd + (size_t)D * D;  // CT elements per transposed slot
   CT* const pku = (CT*)a.statesT + (size_t)u * a.nslots * PS;
+  rem2* const lou = LO ? (rem2*)a.statesLo + (size_t)u * a.nslots * (hd / 2) : nullptr;
   float* const mst = a.mstates + (size_t)u * a.nslots * D * D;
   const bool shard_qk = Dm.qk_proj && Dm.qk_scope == 0;
   const float rscale = 2.0f / (float)D;
@@ -143,9 +145,10 @@ __global__ void __launch_bounds__(512) local_walk_kernel(LocalFwdArgs a) {
 
   // compute-type transposes of the state into a slot, the fp32 Q-K sum, and
   // the LDS copy of W2 that the next chunk's Yk reads
-  auto write_slot = [&](CT* pk, float* ms) {
-    pk = launder_global(pk);
-    ms = launder_global(ms);
+  auto write_slot = [&](int slot) {
+    CT* const pk = launder_global(pku + (size_t)slot * PS);
+    float* const ms = launder_global(mst + (size_t)slot * D * D);
+    rem2* const lo = LO ? launder_global(lou + (size_t)slot * (hd / 2)) : nullptr;
     const int ll = lane_id_local(), lc = ll & 15, g = ll >> 4;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -175,6 +178,11 @@ __global__ void __launch_bounds__(512) local_walk_kernel(LocalFwdArgs a) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) sW2[(size_t)(d0 + r) * LH + h] = (CT)W2[dt][ht][r];
         }
+        if constexpr (LO) {
+          lo[rem_ofs(DT, dt, w * HT + ht, rem_lane1(ll))] =
+              rem2{rem_pack(quad_transpose(W1T[dt][ht])), rem_pack(quad_transpose(S1T[dt][ht]))};
+          lo[hd / 4 + rem_ofs(DT, dt, w * HT + ht, ll)] = rem2{rem_pack(W2[dt][ht]), rem_pack(S2[dt][ht])};
+        }
         store4<CT>(pk + hd + (size_t)h * D + d0, W2[dt][ht]);      // W2^T [HID][D]
         store4<CT>(pk + 3 * hd + (size_t)h * D + d0, S2[dt][ht]);  // S2^T [HID][D]
       }
@@ -192,7 +200,7 @@ __global__ void __launch_bounds__(512) local_walk_kernel(LocalFwdArgs a) {
         }
       }
   };
-  write_slot(pku, mst);
+  write_slot(0);
 
   // Loads of a chunk's inputs are issued ahead of the phase that uses them:
   // the keys and gates of chunk n + 1 during chunk n's carry (their round trip
@@ -488,7 +496,7 @@ __global__ void __launch_bounds__(512) local_walk_kernel(LocalFwdArgs a) {
         S2[dt][ht] = s2;
       }
     }
-    write_slot(pku + (size_t)(n + 1) * PS, mst + (size_t)(n + 1) * D * D);
+    write_slot(n + 1);
     if (EARLY && n + 1 < nch) {  // the next chunk's coefficients (its buffer was chunk n - 1's)
       scan_coefs(cfs[(n + 1) & 1]);
       if (n + 2 < nch) load_gates(tok0 + 2 * C);
@@ -498,12 +506,12 @@ __global__ void __launch_bounds__(512) local_walk_kernel(LocalFwdArgs a) {
 
 // Launches the walk for the fixed-size shapes it is built for; false when
 // `a` is not one of them.
-template <typename IO, int ACT, int D, int HID, int CP>
+template <typename IO, int ACT, int D, int HID, int CP, bool LO = false>
 static bool try_walk(const LocalFwdArgs& a, int units, hipStream_t st, hipError_t* err) {
-  if (a.D.d != D || a.D.hid != HID || a.D.Cp != CP || a.D.act != ACT) return false;
+  if (a.D.d != D || a.D.hid != HID || a.D.Cp != CP || a.D.act != ACT || (a.statesLo != nullptr) != LO) return false;
   constexpr size_t lds = walk_lds_bytes<D, HID, CP>();
   static_assert(lds + 2 * sizeof(WalkCoef) <= 160 * 1024, "LDS of one CU");
-  auto kern = local_walk_kernel<IO, ACT, D, HID, CP>;
+  auto kern = local_walk_kernel<IO, ACT, D, HID, CP, LO>;
   if (!lds_fits((const void*)kern, lds)) {  // the compiled static LDS, not the estimate
     *err = hipErrorInvalidConfiguration;
     return true;
@@ -524,7 +532,11 @@ bool launch_local_walk(const LocalFwdArgs& a, int units, hipStream_t st, hipErro
          try_walk<__bf16, ACT_SILU, 64, 256, 16>(a, units, st, err) ||
          try_walk<__bf16, ACT_GELU, 64, 256, 64>(a, units, st, err) ||
          try_walk<__bf16, ACT_GELU, 64, 256, 32>(a, units, st, err) ||
-         try_walk<__bf16, ACT_GELU, 64, 256, 16>(a, units, st, err);
+         try_walk<__bf16, ACT_GELU, 64, 256, 16>(a, units, st, err) ||
+         try_walk<__bf16, ACT_SILU, 64, 256, 64, true>(a, units, st, err) ||
+         try_walk<__bf16, ACT_GELU, 64, 256, 64, true>(a, units, st, err) ||
+         try_walk<__bf16, ACT_GELU, 64, 256, 32, true>(a, units, st, err) ||
+         try_walk<__bf16, ACT_GELU, 64, 256, 16, true>(a, units, st, err);
 }
 
 }  // namespace tnt

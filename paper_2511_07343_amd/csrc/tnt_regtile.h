@@ -55,6 +55,43 @@ __device__ __forceinline__ bf16x8 a_pair(const __bf16* A, int ld, int row, int k
   return join(x, y);
 }
 
+// A float's bits 8 to 15, the byte that follows its bf16 value, of four floats in a word.
+// Beside the bf16 value they give the float back to 2^-17 of itself: the byte as a signed
+// one counts from the rounded value (which lies above the float where the byte's top bit
+// is set; a float half way between two bf16 values, 1 in 2^16, comes back one off).
+__device__ __forceinline__ unsigned rem_pack(const f4& x) {
+  const float a = x[0], b = x[1], c = x[2], d = x[3];
+  const unsigned lo = __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, b), __builtin_bit_cast(unsigned, a), 0x0c0c0501u);
+  const unsigned hi = __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, d), __builtin_bit_cast(unsigned, c), 0x05010c0cu);
+  return lo | hi;
+}
+__device__ __forceinline__ f4 rem_unpack(const bf16x4& hi, unsigned w) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  const u2 h = __builtin_bit_cast(u2, hi);
+  f4 x;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const unsigned top = r % 2 ? (h[r / 2] & 0xffff0000u) : (h[r / 2] << 16);
+    const int q = (int)(w << (24 - 8 * r)) >> 24;
+    const unsigned bits = (top | 0x80u) + ((unsigned)q << 8);
+    x[r] = __builtin_bit_cast(float, bits);
+  }
+  return x;
+}
+// The remainders of a state in words of two (W and S): first those of W1, S1, then (after
+// hid d / 4) of W2, S2, a 16 x 16 tile (d tile dt of nd, hidden tile ht) in the order of
+// the lanes that hold it: of W1, S1 lane l has hidden rows 4 (l / 16) .. + 3 of column
+// l % 16 of d, of W2, S2 rows 4 (l / 16) .. + 3 of d of hidden column l % 16.  A store or
+// load of a tile is one run of 512 bytes (by matrix rows, stores of 32-byte pieces cost
+// the forward walk 3.5 us a chunk).
+typedef unsigned rem2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t rem_ofs(int nd, int dt, int ht, int l) {
+  return (uint32_t)((ht * nd + dt) * 64 + l);
+}
+// the lane that holds, of W1, the values that lane l of the transposed tile has after a
+// transpose within its quad
+__device__ __forceinline__ int rem_lane1(int l) { return (l & 12) * 4 + (l >> 4) * 4 + (l & 3); }
+
 __device__ __forceinline__ void mma32(f4& acc, const bf16x8& a, const bf16x8& b) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
 }

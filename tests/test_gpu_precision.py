@@ -49,18 +49,13 @@ def test_global_activation_argument(d, hid, act):
         assert e <= bound, (n, e)
 
 
-# outputs whose error against 64 bits is compared; ddecay and the like are sums over the
-# state, of which a case has too few for a narrow bound
-LOCAL = [(ACT_GELU, 16, ("dv", "dlr", "dW1")), (ACT_GELU, 32, ("dv", "dlr", "dW1")),
-         (ACT_SILU, 33, ("dv", "dlr", "dW1")), (ACT_GELU, 48, ("dv", "dlr", "dW1"))]
-
-
-@pytest.mark.parametrize("act,C,names", LOCAL, ids=str)
-def test_local_operands_rounded_once(act, C, names):
+@pytest.mark.parametrize("act,C", [(ACT_GELU, 16), (ACT_GELU, 32), (ACT_SILU, 33), (ACT_GELU, 48)])
+def test_local_roundings(act, C):
     """The error against 64 bits is that of the runtime-sized kernels: operands scaled by a
     gate coefficient are rounded once, after the scaling.  1 %: the two families' errors
     differ by the elements that their sums' order takes over a rounding boundary; one
-    operand in ten rounded twice adds 2 to 9 %."""
+    operand in ten rounded twice adds 2 to 9 %.  And the adjoint . state products behind the
+    gate gradients are taken from fp32 values."""
     cfg = small_config(BF16, act, B=1, H=4, L=32 * C, d=64, hid=256, C_G=32 * C,
                        locals_=((C, 16 * C),), name=f"local C_L={C} act={act}")
     inp = make_inputs(cfg, 712)
@@ -68,10 +63,17 @@ def test_local_operands_rounded_once(act, C, names):
     a, b = both_families(cfg, inp, False)
     ref = {k: torch.from_numpy(v) for k, v in oracle_backward(cfg, inp).items()}
     bad = []
-    for n in names:
+    for n in ("dv", "dW1"):
         ea, eb = float((a[n] - ref[n]).norm()), float((b[n] - ref[n]).norm())
         print(f"  {n:7s} {ea / float(ref[n].norm()):.3e} / {eb / float(ref[n].norm()):.3e} = {ea / eb:.3f}",
               flush=True)
         if ea > 1.01 * eb:
             bad.append((n, ea / eb))
+    # the gate gradients: half of what one more rounding to bf16 would add (2^-9 / sqrt(3)),
+    # of the adjoint or of the state, in the sums of adjoint . state products
+    for n in ("dlr", "dmom", "ddecay"):
+        e = float((a[n] - b[n]).norm() / b[n].norm())
+        print(f"  {n:7s} apart {e:.2e}", flush=True)
+        if e > 0.5 * 2.0 ** -9 / 3 ** 0.5:
+            bad.append((n, e))
     assert not bad, bad
