@@ -216,9 +216,12 @@ tnt_status tnt_mem_fwd_noalloc(const tnt_config* cfg, const void* q, const void*
  * blocks ordered [M][B][H], followed by a scratch area of M*B*H blocks of
  * 2*hid + d + 3*G*d floats (G = hid / min(64, hid)), each rounded up to a
  * multiple of 64 floats, whose contents are undefined between calls.  Calls
- * on one state must be serialised (same stream).  Up to 16 tokens between two
- * chunk boundaries take two launches over (hidden-unit slice, chain, memory)
- * workgroups, a boundary one more. */
+ * on one state must be serialised (same stream).  The tokens between two chunk
+ * boundaries go in launches of up to 16 together, and no more than have room in a
+ * chain's scratch area for their shares of the output (d floats a token and global
+ * memory, G*d a token and local memory: 8 tokens at d 64, hid 256, global + one
+ * local).  Such a group takes two launches, a token by itself three, a boundary
+ * one more. */
 
 /* Bytes of the carried state (0 if the config is invalid). */
 size_t tnt_mem_state_size(const tnt_config* cfg);

@@ -264,6 +264,7 @@ struct StepArgs {
   // block) holds sc_stride floats per (memory, chain); a launch takes tokens
   // t0 .. t0 + n - 1
   int G, HS, t0, n;
+  int one;  // 1: a token by itself (its own kernels and scratch layout)
   float* scratch;
   size_t sc_stride;
 };

@@ -28,16 +28,29 @@
 //           x = M_t q come from a private copy of its Q-K sum.
 //   out     o = the sum of the retrieval shares (global memory first, fixed
 //           order); M += k k^T / ||k||^2 of every token.
-// A third launch, before them, where a memory's chunk or shard begins: W^ <- W,
-// or the reset.  The products at the entry weights are fp32 MFMA tiles of 16
-// tokens (rows past the call's tokens zero); a token's row does not depend on the
-// other rows, so every cut of a sequence gives bitwise the same results.
+// A further launch, before them, where a memory's chunk or shard begins: W^ <- W,
+// or the reset.
 //
-// Bound by latency at few tokens and by the state's bytes (read and written once a
-// launch, W^ read once per slice through L2) at one token: the slice's whole state
-// is requested before the first product.  B 4, H 8, d 64, hid 256, global + one
-// local: one token 22.9 us (31.1 with three launches per token, which also read every
-// weight once more); 77 tokens at B 2 336 us (2104: three launches per token).
+// One token by itself, and few of a wide head or of many chains (step_alone), take
+//   entry   the slice's z, its share of y and of the global retrieval, and its
+//           rows of a local memory's query
+//   update  r from the shares, delta, the update and the retrieval share
+// instead of the tokens launch: there W^1 is read once and W^2 twice, not G times
+// each (from G XCDs: the slices of a chain are neighbours in the grid), and a
+// workgroup's registers leave room for several on a CU (the tokens launch takes a
+// CU's registers with one workgroup at d 64, and spills at d 128).
+//
+// The products at the entry weights are fp32 MFMA tiles of 16 tokens (rows past the
+// launch's tokens zero), y a sum of one such product per slice in the order of the
+// slices, in both forms; a token's row does not depend on the other rows, so every
+// cut of a sequence gives bitwise the same results.
+//
+// Bound by the launches' latency at few chains (entry, update and out: 14.7 us for one
+// chain at d 64, hid 256, global + one local) and by the state's bytes at many: its 14
+// hid d floats per (memory, chain) and token (W^1, W1, S1, W2, S2 in or out once, W^2
+// twice, and the 4 updated ones out) take 162 us for 512 chains, 5.8 TB/s.  With three
+// launches of vector products before, 25 and 196 us.  77 tokens at B 2, H 8: 336 us,
+// against 2104 with launches for every token.
 #include "tnt_device.h"
 #include "tnt_kernels.h"
 
@@ -50,7 +63,7 @@ namespace {
 
 constexpr int STEP_THREADS = 256;
 // threads of a token launch: 512 at d = 128, where a slice's state, M and the weights
-// in flight would not fit the registers of 256
+// in flight take twice the registers (135 of them spill all the same)
 constexpr int step_threads(int d) { return d == 128 ? 512 : STEP_THREADS; }
 constexpr int STEP_MAX_D = 128, STEP_MAX_H = 512;
 constexpr int STEP_N = 16;  // tokens of one launch at most: the rows of an MFMA tile
@@ -116,6 +129,70 @@ __device__ __forceinline__ void group_sums(float (&x)[NU], int W) {
     for (int u = 0; u < NU; ++u) x[u] += __shfl_xor(x[u], 16, WAVE);
 }
 
+// The sums below are written as fused products one by one, so that both forms of a
+// step round alike (a token's results do not depend on the form that took it).
+__device__ __forceinline__ float dot4(const f4& a, const f4& b) {
+  return __builtin_fmaf(a[3], b[3], __builtin_fmaf(a[2], b[2], __builtin_fmaf(a[1], b[1], a[0] * b[0])));
+}
+// w <- keep w + s, s <- beta s - c v
+__device__ __forceinline__ void gated(f4& w, f4& s, float beta, float keep, float c, const f4& v) {
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    s[x] = __builtin_fmaf(-c, v[x], beta * s[x]);
+    w[x] = __builtin_fmaf(keep, w[x], s[x]);
+  }
+}
+
+// One token on a slice's state in registers (pieces tid + u NT of W1, S1 by rows and of
+// W2, S2 by rows of the slice's columns): the gated update, and a local memory's share of
+// W2_t s(W1_t x).  k, r, x: the token's rows; av, gv: s(z) and delta on the slice; zt:
+// HS floats of LDS, no two consecutive tokens' alike.
+template <int ACT, int D, int NT, int NU>
+__device__ __forceinline__ void slice_token(f4 (&w1)[NU], f4 (&s1)[NU], f4 (&w2)[NU], f4 (&s2)[NU], int HS,
+                                            bool global, float eta, float beta, float keep, const float* k,
+                                            const float* r, const float* x, const float* av, const float* gv,
+                                            float* zt, float* share) {
+  constexpr int g4 = D / 4;
+  const int tid = threadIdx.x, h4 = HS / 4, n4 = HS * g4;
+  const f4 kv = reinterpret_cast<const f4*>(k)[tid % g4];
+  const f4 a4 = reinterpret_cast<const f4*>(av)[tid % h4];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int jj = (tid + u * NT) / g4;
+    gated(w1[u], s1[u], beta, keep, eta * gv[jj < HS ? jj : 0], kv);
+  }
+  if (!global) {
+    const f4 xv = reinterpret_cast<const f4*>(x)[tid % g4];
+    float zp[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) zp[u] = dot4(w1[u], xv);
+    group_sums<NU>(zp, g4);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int e = tid + u * NT;
+      if (e < n4 && e % g4 == 0) zt[e / g4] = act_f<ACT>(zp[u]);
+    }
+    __syncthreads();  // (the other token's zt was last read before this barrier)
+  }
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int i = (tid + u * NT) / h4;
+    gated(w2[u], s2[u], beta, keep, eta * r[i < D ? i : 0], a4);
+  }
+  if (!global) {
+    const f4 zv = reinterpret_cast<const f4*>(zt)[tid % h4];
+    float y[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) y[u] = dot4(w2[u], zv);
+    group_sums<NU>(y, h4);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int e = tid + u * NT;
+      if (e < n4 && e % h4 == 0) share[e / h4] = y[u];
+    }
+  }
+}
+
 // 1 / ||k||^2 (0 for a zero key) of one LDS row, the same in every launch
 __device__ __forceinline__ float inv_norm2(const float* k, int d) {
   float s = 0.f;
@@ -124,9 +201,26 @@ __device__ __forceinline__ float inv_norm2(const float* k, int d) {
   return s > 0.f ? 1.0f / s : 0.f;
 }
 
+// One token by itself: the scratch of a (memory, chain), floats: s(z) [hid], s'(z)
+// [hid], x [d], then per slice the shares of W^2 s(z) [G][d] and of the retrieval [G][d]
+struct StepOne {
+  float *a, *sp, *x, *yp, *share;
+};
+__device__ __forceinline__ StepOne step_one(const StepArgs& a, int chain, int m) {
+  float* b = a.scratch + ((size_t)m * a.B * a.H + chain) * a.sc_stride;
+  StepOne s;
+  s.a = b;
+  s.sp = b + a.hid;
+  s.x = s.sp + a.hid;
+  s.yp = s.x + a.d;
+  s.share = s.yp + (size_t)a.G * a.d;
+  return s;
+}
+
 // the retrieval shares of a launch's tokens, per chain: [n][d] of the global memory
-// (if any), then [n][G][d] of every local memory
+// (if any), then [n][G][d] of every local memory; of one token by itself: [G][d] of each
 __device__ __forceinline__ float* step_share(const StepArgs& a, int chain, int m) {
+  if (a.one) return step_one(a, chain, m).share;
   float* b = a.scratch + (size_t)chain * a.M * a.sc_stride;
   const size_t nd = (size_t)a.n * a.d;
   if (a.has_global && m == 0) return b;
@@ -165,7 +259,7 @@ __global__ void __launch_bounds__(256) step_boundary_kernel(StepArgs a) {
 // Tokens t0 .. t0 + n - 1.  Every weight a workgroup reads is requested before the
 // first barrier (hid up to 256; the rest of a larger one in a second round).
 template <typename IO, int ACT, int D>
-__global__ void __launch_bounds__(step_threads(D)) step_tokens_kernel(StepArgs a) {
+__global__ void __launch_bounds__(step_threads(D), D == 64 ? 1 : 2) step_tokens_kernel(StepArgs a) {
   extern __shared__ __align__(16) float sm[];
   constexpr int d = D, NT = step_threads(D), NW = NT / WAVE;
   constexpr int g4 = D / 4;                    // 16-byte pieces of a row of W1, S1, M
@@ -304,13 +398,20 @@ __global__ void __launch_bounds__(step_threads(D)) step_tokens_kernel(StepArgs a
   auto y_tile = [&](int it, auto pieces, auto two) {
     constexpr int P = decltype(pieces)::value;  // pieces of a row of W^2 a round
     constexpr bool TWO = decltype(two)::value;
+    constexpr int S = P < 4 ? P : 4;  // pieces of a slice, summed slice by slice
     f4 y = zero4(), yq = zero4();
     for (int k0 = 0; k0 < hid; k0 += 16 * P) {
       if (it != w || k0) load_y(it, k0);
 #pragma unroll
-      for (int s = 0; s < P; ++s) {
-        row_piece(y, sa, Y.lh, k0 + 16 * s, by[s]);
-        if constexpr (TWO) row_piece(yq, saq, Y.lh, k0 + 16 * s, by[s]);
+      for (int s0 = 0; s0 < P; s0 += S) {
+        f4 yp = zero4(), yqp = zero4();
+#pragma unroll
+        for (int s = s0; s < s0 + S; ++s) {
+          row_piece(yp, sa, Y.lh, k0 + 16 * s, by[s]);
+          if constexpr (TWO) row_piece(yqp, saq, Y.lh, k0 + 16 * s, by[s]);
+        }
+        y += yp;
+        if constexpr (TWO) yq += yqp;
       }
     }
     const int i = it * 16 + lc;
@@ -346,8 +447,7 @@ __global__ void __launch_bounds__(step_threads(D)) step_tokens_kernel(StepArgs a
       static_assert(NT % g4 == 0, "one column of pieces per thread");
       float s[NM];
 #pragma unroll
-      for (int u = 0; u < NM; ++u)
-        s[u] = mq[u][0] * qv[0] + mq[u][1] * qv[1] + mq[u][2] * qv[2] + mq[u][3] * qv[3];
+      for (int u = 0; u < NM; ++u) s[u] = dot4(mq[u], qv);
       group_sums<NM>(s, g4);
 #pragma unroll
       for (int u = 0; u < NM; ++u) {
@@ -355,7 +455,7 @@ __global__ void __launch_bounds__(step_threads(D)) step_tokens_kernel(StepArgs a
         if (e < m4) {
           const int i = e / g4;
           const float ki = sk[t * Y.ld + i];
-          if (e % g4 == 0) sx[t * Y.ld + i] = s[u] + ki * c;
+          if (e % g4 == 0) sx[t * Y.ld + i] = __builtin_fmaf(ki, c, s[u]);
           const float kn = ki * ik;
 #pragma unroll
           for (int x = 0; x < 4; ++x) mq[u][x] = __builtin_fmaf(kn, kv[x], mq[u][x]);
@@ -381,51 +481,204 @@ __global__ void __launch_bounds__(step_threads(D)) step_tokens_kernel(StepArgs a
 
   // token by token: the gated update, and a local memory's share of W2_t s(W1_t x)
   float* const share = step_share(a, chain, m);
-  for (int t = 0; t < n; ++t) {
-    const float eta = sgt[t], beta = sgt[STEP_N + t], keep = 1.0f - sgt[2 * STEP_N + t];
-    const f4 kv = reinterpret_cast<const f4*>(sk + t * Y.ld)[tid % g4];
-    const f4 av = reinterpret_cast<const f4*>(sa + t * Y.lh + j0)[tid % h4];
-    float* const zt = sz + (t & 1) * HS;
+  for (int t = 0; t < n; ++t)
+    slice_token<ACT, D, NT, NU>(w1, s1, w2, s2, HS, global, sgt[t], sgt[STEP_N + t], 1.0f - sgt[2 * STEP_N + t],
+                                sk + t * Y.ld, sr + t * Y.ld, sx + t * Y.ld, sa + t * Y.lh + j0, sg + t * Y.ls,
+                                sz + (t & 1) * HS, share + ((size_t)t * G + g) * d);
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int jj = (tid + u * NT) / g4;
-      s1[u] = beta * s1[u] - (eta * sg[t * Y.ls + (jj < HS ? jj : 0)]) * kv;
-      w1[u] = keep * w1[u] + s1[u];
-    }
-    if (!global) {
-      const f4 xv = reinterpret_cast<const f4*>(sx + t * Y.ld)[tid % g4];
-      float zp[NU];
-#pragma unroll
-      for (int u = 0; u < NU; ++u)
-        zp[u] = w1[u][0] * xv[0] + w1[u][1] * xv[1] + w1[u][2] * xv[2] + w1[u][3] * xv[3];
-      group_sums<NU>(zp, g4);
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        const int e = tid + u * NT;
-        if (e < n4 && e % g4 == 0) zt[e / g4] = act_f<ACT>(zp[u]);
-      }
-      __syncthreads();  // (the other token's sz was last read before this barrier)
-    }
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int i = (tid + u * NT) / h4;
-      s2[u] = beta * s2[u] - (eta * sr[t * Y.ld + (i < d ? i : 0)]) * av;
-      w2[u] = keep * w2[u] + s2[u];
-    }
-    if (!global) {
-      const f4 zv = reinterpret_cast<const f4*>(zt)[tid % h4];
-      float y[NU];
-#pragma unroll
-      for (int u = 0; u < NU; ++u)
-        y[u] = w2[u][0] * zv[0] + w2[u][1] * zv[1] + w2[u][2] * zv[2] + w2[u][3] * zv[3];
-      group_sums<NU>(y, h4);
-#pragma unroll
-      for (int u = 0; u < NU; ++u) {
-        const int e = tid + u * NT;
-        if (e < n4 && e % h4 == 0) share[((size_t)t * G + g) * d + e / h4] = y[u];
-      }
+  for (int u = 0; u < NU; ++u) {
+    const int e = tid + u * NT;
+    if (e < n4) {
+      const size_t o2 = (size_t)(e / h4) * hid + 4 * (e % h4);
+      reinterpret_cast<f4*>(W1)[e] = w1[u];
+      reinterpret_cast<f4*>(S1)[e] = s1[u];
+      *reinterpret_cast<f4*>(W2 + o2) = w2[u];
+      *reinterpret_cast<f4*>(S2 + o2) = s2[u];
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// One token by itself, two launches before `out`: every weight of W^1 is read once and
+// of W^2 twice, whatever the number of slices, and a workgroup holds the registers of
+// one phase.  The products are the same MFMA tiles with one row that is not zero.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void row_piece1(f4& acc, const float* A, int k0, const f4& b) {
+  const int l = lane_id();
+  f4 x = *reinterpret_cast<const f4*>(A + k0 + 4 * (l >> 4));
+  if (l & 15) x = zero4();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r], b[r], acc, 0, 0, 0);
+}
+
+// entry: z = W^1 k of the slice's rows (and the global retrieval's W^1 q), the slice's
+// share of W^2 s(z) (and of W^2 s(W^1 q)); a local memory's query x, its rows dealt to
+// the slices
+template <typename IO, int ACT, int D>
+__global__ void __launch_bounds__(STEP_THREADS) step_entry_kernel(StepArgs a) {
+  __shared__ __align__(16) float sk[D], sq[D], sa[64], saq[64];
+  constexpr int d = D, g4 = D / 4, ND = D / 16, NW = STEP_THREADS / WAVE, TY = (ND + NW - 1) / NW;
+  const int g = blockIdx.x, chain = blockIdx.y, m = blockIdx.z;
+  const int hid = a.hid, HS = a.HS, G = a.G, j0 = g * HS;
+  const int tid = threadIdx.x, l = lane_id(), w = wave_id(), lg = l >> 4, lc = l & 15;
+  const bool global = a.has_global && m == 0;
+  const bool proj = !global && a.qk_proj;
+  const size_t hd = (size_t)hid * d;
+  const float* const base = a.state + ((size_t)m * a.B * a.H + chain) * a.mem_stride;
+  const float *Wh1 = base, *Wh2 = base + hd, *Mq = base + 6 * hd;
+  const StepOne sc = step_one(a, chain, m);
+  const size_t tok = ((size_t)chain * a.T + a.t0) * d;
+  const IO *q = (const IO*)a.q + tok, *k = (const IO*)a.k + tok;
+  for (int i = tid; i < d; i += STEP_THREADS) {
+    sk[i] = to_f(k[i]);
+    sq[i] = to_f(q[i]);
+  }
+  f4 bz[ND], by[TY][4];  // every weight of the workgroup, ahead of the first product
+  if (w < HS / 16)
+#pragma unroll
+    for (int s = 0; s < ND; ++s)
+      bz[s] = *reinterpret_cast<const f4*>(Wh1 + (size_t)(j0 + w * 16 + lc) * d + 16 * s + 4 * lg);
+#pragma unroll
+  for (int y = 0; y < TY; ++y)
+    if (w + NW * y < ND)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (16 * s < HS)
+          by[y][s] = *reinterpret_cast<const f4*>(Wh2 + (size_t)((w + NW * y) * 16 + lc) * hid + j0 + 16 * s + 4 * lg);
+  __syncthreads();
+  auto z_tile = [&](auto two) {
+    constexpr bool TWO = decltype(two)::value;
+    f4 z = zero4(), zq = zero4();
+#pragma unroll
+    for (int s = 0; s < ND; ++s) {
+      row_piece1(z, sk, 16 * s, bz[s]);
+      if constexpr (TWO) row_piece1(zq, sq, 16 * s, bz[s]);
+    }
+    if (lg == 0) {
+      const int j = w * 16 + lc;
+      const ActVals av = act_all<ACT>(z[0]);
+      sa[j] = av.s;
+      sc.a[j0 + j] = av.s;
+      sc.sp[j0 + j] = av.d1;
+      if constexpr (TWO) saq[j] = act_f<ACT>(zq[0]);
+    }
+  };
+  if (w < HS / 16) {
+    if (global)
+      z_tile(std::true_type{});
+    else
+      z_tile(std::false_type{});
+  }
+  __syncthreads();
+  auto y_tile = [&](int it, const f4(&b)[4], auto pieces, auto two) {
+    constexpr int P = decltype(pieces)::value;
+    constexpr bool TWO = decltype(two)::value;
+    f4 y = zero4(), yq = zero4();
+#pragma unroll
+    for (int s = 0; s < P; ++s) {
+      row_piece1(y, sa, 16 * s, b[s]);
+      if constexpr (TWO) row_piece1(yq, saq, 16 * s, b[s]);
+    }
+    if (lg == 0) {
+      sc.yp[(size_t)g * d + it * 16 + lc] = y[0];
+      if constexpr (TWO) sc.share[(size_t)g * d + it * 16 + lc] = yq[0];
+    }
+  };
+  auto y_rows = [&](auto pieces) {
+#pragma unroll
+    for (int y = 0; y < TY; ++y)
+      if (w + NW * y < ND) {
+        if (global)
+          y_tile(w + NW * y, by[y], pieces, std::true_type{});
+        else
+          y_tile(w + NW * y, by[y], pieces, std::false_type{});
+      }
+  };
+  switch (HS / 16) {
+    case 1: y_rows(std::integral_constant<int, 1>{}); break;
+    case 2: y_rows(std::integral_constant<int, 2>{}); break;
+    default: y_rows(std::integral_constant<int, 4>{}); break;
+  }
+  if (global) return;
+  if (!proj) {
+    for (int i = g * (d / G) + tid; i < (g + 1) * (d / G); i += STEP_THREADS) sc.x[i] = sq[i];
+    return;
+  }
+  const float ik = inv_norm2(sk, d);
+  float kq = 0.f;
+  for (int i = l; i < d; i += WAVE) kq = __builtin_fmaf(sk[i], sq[i], kq);
+  kq = wave_sum(kq);
+  const float c = kq * ik;
+  const f4 qv = reinterpret_cast<const f4*>(sq)[tid % g4];
+  const int e1 = (g + 1) * (d / G) * g4;
+  for (int e = g * (d / G) * g4 + tid; e - tid < e1; e += STEP_THREADS) {  // (whole groups of lanes)
+    float s[1] = {e < e1 ? dot4(reinterpret_cast<const f4*>(Mq)[e], qv) : 0.f};
+    group_sums<1>(s, g4);
+    if (e < e1 && e % g4 == 0) sc.x[e / g4] = __builtin_fmaf(sk[e / g4], c, s[0]);
+  }
+}
+
+// update: r, the slice's delta, the gated update and a local memory's retrieval share
+template <typename IO, int ACT, int D>
+__global__ void __launch_bounds__(step_threads(D)) step_update_kernel(StepArgs a) {
+  __shared__ __align__(16) float sk[D], sr[D], sx[D], sa[64], ssp[64], sg[64], sz[64];
+  constexpr int d = D, NT = step_threads(D), g4 = D / 4, ND = D / 16;
+  constexpr int NU = D <= 32 ? 2 : 16 * D / NT;
+  const int g = blockIdx.x, chain = blockIdx.y, m = blockIdx.z;
+  const int H = a.H, hid = a.hid, HS = a.HS, G = a.G, j0 = g * HS;
+  const int tid = threadIdx.x, l = lane_id(), w = wave_id(), lg = l >> 4, lc = l & 15;
+  const bool global = a.has_global && m == 0;
+  const size_t hd = (size_t)hid * d;
+  float* const base = a.state + ((size_t)m * a.B * H + chain) * a.mem_stride;
+  const float* Wh2 = base + hd;
+  float *W1 = base + 2 * hd + (size_t)j0 * d, *W2 = base + 3 * hd + j0;
+  float *S1 = base + 4 * hd + (size_t)j0 * d, *S2 = base + 5 * hd + j0;
+  const StepOne sc = step_one(a, chain, m);
+  const size_t tok = ((size_t)chain * a.T + a.t0) * d;
+  const size_t gi = ((size_t)m * a.B * H + chain) * a.T + a.t0;
+  const float rs = 2.0f / (float)d;
+  f4 bd[ND];  // the slice's W^2 columns
+  if (w < HS / 16)
+#pragma unroll
+    for (int s = 0; s < ND; ++s)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bd[s][r] = Wh2[(size_t)(16 * s + 4 * lg + r) * hid + j0 + w * 16 + lc];
+  const int h4 = HS / 4, n4 = HS * g4;
+  f4 w1[NU], s1[NU], w2[NU], s2[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int e = tid + u * NT;
+    w1[u] = s1[u] = w2[u] = s2[u] = zero4();
+    if (e < n4) {
+      const size_t o2 = (size_t)(e / h4) * hid + 4 * (e % h4);
+      w1[u] = reinterpret_cast<const f4*>(W1)[e];
+      s1[u] = reinterpret_cast<const f4*>(S1)[e];
+      w2[u] = *reinterpret_cast<const f4*>(W2 + o2);
+      s2[u] = *reinterpret_cast<const f4*>(S2 + o2);
+    }
+  }
+  const float eta = a.lr[gi], beta = a.mom[gi], keep = 1.0f - a.decay[gi];
+  if (tid < d) {
+    sk[tid] = to_f(((const IO*)a.k)[tok + tid]);
+    float y = 0.f;
+    for (int gg = 0; gg < G; ++gg) y += sc.yp[(size_t)gg * d + tid];
+    sr[tid] = rs * (y - to_f(((const IO*)a.v)[tok + tid]));
+    if (!global) sx[tid] = sc.x[tid];
+  }
+  if (tid < HS) {
+    sa[tid] = sc.a[j0 + tid];
+    ssp[tid] = sc.sp[j0 + tid];
+  }
+  __syncthreads();
+  if (w < HS / 16) {
+    f4 acc = zero4();
+#pragma unroll
+    for (int s = 0; s < ND; ++s) row_piece1(acc, sr, 16 * s, bd[s]);
+    if (lg == 0) sg[w * 16 + lc] = acc[0] * ssp[w * 16 + lc];
+  }
+  __syncthreads();
+  slice_token<ACT, D, NT, NU>(w1, s1, w2, s2, HS, global, eta, beta, keep, sk, sr, sx, sa, sg, sz,
+                              sc.share + (size_t)g * d);
 #pragma unroll
   for (int u = 0; u < NU; ++u) {
     const int e = tid + u * NT;
@@ -452,6 +705,8 @@ __global__ void __launch_bounds__(STEP_THREADS) step_out_kernel(StepArgs a) {
     for (int e = threadIdx.x; e < n * d; e += STEP_THREADS) {
       const int t = e / d, i = e - t * d;
       float acc = a.has_global ? step_share(a, chain, 0)[e] : 0.f;
+      if (a.one && a.has_global)
+        for (int gg = 1; gg < G; ++gg) acc += step_share(a, chain, 0)[(size_t)gg * d + e];
       for (int m = a.has_global; m < a.M; ++m) {
         const float* sh = step_share(a, chain, m) + (size_t)t * G * d + i;
         for (int gg = 0; gg < G; ++gg) acc += sh[(size_t)gg * d];
@@ -533,6 +788,32 @@ hipError_t launch_step_init(const StepArgs& a, hipStream_t st) {
   return launch_step_from_final(a, nullptr, st);
 }
 
+// Whether the next token goes by itself (three launches, weights read once or twice)
+// rather than with the others of its chunk (two, but every slice reads all of W^1 and W^2
+// and a CU holds one workgroup).  One token, us by itself / together:
+//   d 64, hid 256, global + one local: 1 chain 14.7 / 17.6, 32 chains 17.7 / 23.3, 128
+//   38.5 / 77; d 128, hid 512: 21.5 / 43, 44 / 122, 172 / 514; d 128, hid 128: 1 chain 21 /
+//   29; d 32, hid 512: 15.3 / 19.5
+//   d 64, hid 128: 1 chain 14.9 / 13.8, 32 15.8 / 15.4, 128 (512 workgroups) 24.7 / 33.7;
+//   d 32, hid 128: 15.2 / 12.2, 15.0 / 12.0, 15.9 / 16.2; d 16, hid 32: 1 to 256 chains
+//   (up to 512 workgroups) 15.3 / 12.0, 512 chains 14.7 / 14.7
+// so: from 64 KB a matrix or d 128 on; from 16 KB where there are more workgroups than
+// CUs; below that, four times as many.  Two
+// tokens: d 128, hid 512 42 / 46 (1 chain), 87 / 129, 344 / 537; d 64, hid 256 34 / 25 (32
+// chains, 256 workgroups), 77 / 84 (128, 1024); three at d 128, hid 512: 64 / 50, 131 /
+// 133, 517 / 550.
+static bool step_alone(const StepArgs& a) {
+  constexpr long cus = 256;  // of the whole card (a query costs the host more than it tells)
+  const long grid = (long)a.G * a.B * a.H * a.M;
+  const int hd = a.hid * a.d;
+  switch (a.n) {
+    case 1: return hd >= 16384 || a.d == 128 || (hd >= 4096 && grid > cus) || grid >= 4 * cus;
+    case 2: return hd >= 65536 || (hd >= 16384 && grid >= 4 * cus);
+    case 3: return hd >= 65536 && grid >= 2 * cus;
+    default: return false;
+  }
+}
+
 template <typename IO, int ACT, int D>
 static hipError_t step_run(StepArgs a, hipStream_t st) {
   const size_t lds = (size_t)step_lds(a.d, a.hid, a.HS).total * sizeof(float);
@@ -552,8 +833,16 @@ static hipError_t step_run(StepArgs a, hipStream_t st) {
       bound |= in == 0;
       a.n = (int)std::min<long long>(a.n, a.C[m] - in);
     }
+    a.one = step_alone(a) ? 1 : 0;
+    if (a.one) a.n = 1;
     if (bound) hipLaunchKernelGGL(step_boundary_kernel, dim3(16, BH, a.M), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(kern, dim3(a.G, BH, a.M), dim3(step_threads(D)), lds, st, a);
+    const dim3 grid(a.G, BH, a.M);
+    if (a.one) {
+      hipLaunchKernelGGL((step_entry_kernel<IO, ACT, D>), grid, dim3(STEP_THREADS), 0, st, a);
+      hipLaunchKernelGGL((step_update_kernel<IO, ACT, D>), grid, dim3(step_threads(D)), 0, st, a);
+    } else {
+      hipLaunchKernelGGL(kern, grid, dim3(step_threads(D)), lds, st, a);
+    }
     hipLaunchKernelGGL(step_out_kernel<IO>, dim3(BH, 1 + nloc), dim3(STEP_THREADS), 0, st, a);
   }
   return hipGetLastError();
