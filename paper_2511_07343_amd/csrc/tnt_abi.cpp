@@ -231,7 +231,10 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
   }
   for (int i = 0; i < c->n_local; ++i) {
     const Dims D = mem_dims(c, gsub0, i);
-    local_plan(D, &y.lplan[i], false);
+    // (the scratch serves the runtime-sized forward alone: chunks that the fixed-size one
+    // pads to 64 rows keep the area of their own padding, so that the smallest workspace,
+    // and with it what the no-allocation forward accepts, does not grow with the padding)
+    local_plan(dims_of(c, c->C_L[i], c->S_L[i]), &y.lplan[i], false);
     y.w_scr[i] = off; off += up((size_t)y.l_units[i] * y.lplan[i].elems * cts);
     const size_t fb = local_fwd_split_bytes(D, y.l_units[i]);
     y.w_fsplit[i] = fb ? off : SIZE_MAX;

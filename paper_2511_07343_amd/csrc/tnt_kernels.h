@@ -39,6 +39,7 @@ struct Dims {
 // array); filled by local_scratch_plan.
 struct LocalPlan {
   size_t elems;  // CT elements per unit
+  int rows;      // the padded chunk it is laid out for
   size_t Q, K, N, NT, X, KcT, KbT, R, RT, RcT, RbT, S, P;           // forward, small
   size_t Hk, HkT, Sp, D1T, H;                                      // forward, C x hid
   // backward extras

@@ -40,6 +40,7 @@ size_t local_plan(const Dims& D, LocalPlan* p, bool backward) {
     p->Rb = take(Cp * d);
   }
   p->elems = off;
+  p->rows = D.Cp;
   return off;
 }
 
@@ -266,6 +267,7 @@ static hipError_t launch_local_fwd_t(const LocalFwdArgs& a, int units, hipStream
 hipError_t launch_local_fwd(const LocalFwdArgs& a, int units, hipStream_t st) {
   hipError_t e = hipSuccess;
   if (!a.force_generic && launch_local_fwd_fast(a, units, st, &e)) return e;
+  if (a.plan.rows != a.D.Cp) return hipErrorInvalidValue;  // scratch of another chunk size
   e = a.D.bf16 ? launch_local_fwd_t<__bf16, __bf16>(a, units, st)
                : launch_local_fwd_t<float, float>(a, units, st);
   if (e != hipSuccess || !a.statesT) return e;

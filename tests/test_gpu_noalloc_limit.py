@@ -1,0 +1,29 @@
+"""tnt_mem_fwd_noalloc near the size of its workspace: chunks of 33 to 48 rows run on the
+64-row kernels, and need no larger workspace for it (the runtime-sized kernels took these
+configurations within the same 128 MiB).  Against tnt_mem_fwd within the bf16 bound."""
+import pytest
+import torch
+
+from paper_2511_07343_amd import tnt
+from paper_2511_07343_amd.inputs import ACT_SILU, BF16, make_inputs, small_config
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kw", [
+    dict(B=1, H=16, L=1056, C_G=1056, locals_=((33, 132),)),
+    dict(B=2, H=12, L=768, C_G=768, locals_=((48, 768),)),
+], ids=str)
+def test_noalloc_accepts(kw):
+    cfg = small_config(BF16, ACT_SILU, d=64, hid=256, name=str(kw), **kw)
+    print(f"\n[case] {cfg.name}", flush=True)
+    x = tnt.device_inputs(make_inputs(cfg, 603), cfg)
+    o = torch.empty_like(x["q"])
+    s = tnt.tnt_mem_fwd_noalloc(cfg, x["q"], x["k"], x["v"], x["lr"], x["mom"], x["decay"],
+                                x["W1"], x["W2"], o, None)
+    assert s == 0, tnt.strerror(s)
+    ref, _, _ = tnt.forward(cfg, x, save=False)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o.float()).all()
+    # one walk and the runtime-sized global kernels against two passes and fixed-size ones
+    assert (o.float() - ref.float()).abs().max() <= 2e-2 * ref.float().abs().max()
