@@ -256,11 +256,12 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
     y.w_fsplit[i] = off;
     off += up(local_fwd_split_bytes(D, y.l_units[i]));
   }
+  const int gpad = c->has_global ? global_blk_pad(dims_of(c, c->C_G, c->L)) : 0;
   // the fixed-size global kernels' chunk operands, padded to whole K slabs: where the
   // chunk is padded they lie past the smallest forward workspace, too
-  if (c->has_global && global_blk_pad(c->C_G) != c->C_G) {
+  if (c->has_global && gpad != c->C_G) {
     y.w_gop = off;
-    off += up((size_t)y.BH * (2 * (size_t)c->hid + 4 * (size_t)c->d) * global_blk_pad(c->C_G) * cts);
+    off += up((size_t)y.BH * (2 * (size_t)c->hid + 4 * (size_t)c->d) * gpad * cts);
     y.gop_late = true;
   }
   y.fwd_saved_bytes = off;
@@ -288,7 +289,7 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
     y.b_gscr = off;
     off += up(global_bwd_scratch_bytes(D, &y.b_gscr_f32));
     y.b_gpackA = off; off += up((size_t)y.BH * 8 * y.hd * cts);  // transposed and as they are
-    y.b_gop = off; off += up((size_t)y.BH * 5 * ((size_t)c->hid + c->d) * global_blk_pad(c->C_G) * cts);
+    y.b_gop = off; off += up((size_t)y.BH * 5 * ((size_t)c->hid + c->d) * gpad * cts);
   }
   for (int i = 0; i < c->n_local; ++i) {
     const Dims D = mem_dims(c, gsub0, i);

@@ -1011,6 +1011,10 @@ bool launch_global_bwd_blk(const GlobalArgs& a, int n, hipStream_t st, hipError_
          try_gbwd<64, 128>(a, n, st, err) || try_gbwd<32, 128>(a, n, st, err);
 }
 
-int global_blk_pad(int C) { return gpad(C); }
+int global_blk_pad(const Dims& D) {
+  const bool built = D.bf16 && ((D.d == 64 && (D.hid == 256 || D.hid == 128)) || (D.d == 128 && D.hid == 512) ||
+                                (D.d == 32 && D.hid == 128));
+  return built ? gpad(D.C) : D.C;
+}
 
 }  // namespace tnt

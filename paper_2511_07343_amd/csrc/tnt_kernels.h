@@ -233,7 +233,8 @@ hipError_t launch_reduce_global_init(const float* part, int B, int H, size_t hd,
                                      float* dW2, hipStream_t st);
 size_t global_bwd_scratch_bytes(const Dims& D, size_t* f32_off);
 int global_fwd_splits(const Dims& D);
-int global_blk_pad(int C);  // rows per chain of the fixed-size global kernels' chunk operands
+// rows per chain of the fixed-size global kernels' chunk operands (D.C where there are none)
+int global_blk_pad(const Dims& D);
 hipError_t launch_global_carry_reduce(const GlobalArgs& a, int n, int nsplit, hipStream_t st);
 hipError_t launch_gbwd_state_reduce(const GlobalArgs& a, int n, int nsplit, hipStream_t st);
 bool launch_global_fwd_blk(const GlobalArgs& a, int n, hipStream_t st, hipError_t* err);

@@ -7,7 +7,7 @@ import re
 import pytest
 
 from paper_2511_07343_amd import tnt
-from paper_2511_07343_amd.inputs import WORKLOADS, small_config
+from paper_2511_07343_amd.inputs import BF16, WORKLOADS, small_config
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -222,3 +222,15 @@ def test_global_intra_limits():
     # without a global memory the flag is ignored
     assert tnt.tnt_mem_saved_size(cfg.replace(has_global=0)) == \
         tnt.tnt_mem_saved_size(cfg.replace(has_global=0, global_intra=0))
+
+
+def test_workspace_of_unpadded_global_chunks():
+    """Only the head sizes with fixed-size global kernels reserve operands of padded chunks:
+    in fp32, and at other head sizes, a chunk of 130 tokens takes no more than 130/128 of
+    the operand room of one of 128."""
+    def sizes(C, **kw):
+        cfg = small_config(B=1, H=2, L=8 * C, C_G=C, locals_=(), **kw)
+        return [tnt.tnt_mem_workspace_size(cfg, k) / C for k in (tnt.TNT_WS_FWD_MIN, tnt.TNT_WS_BWD)]
+    for kw in (dict(d=16, hid=32), dict(d=64, hid=256), dict(d=16, hid=32, dtype=BF16)):
+        for a, b in zip(sizes(130, **kw), sizes(128, **kw)):
+            assert a <= 1.02 * b, (kw, a, b)
