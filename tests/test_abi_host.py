@@ -226,11 +226,12 @@ def test_global_intra_limits():
 
 def test_workspace_of_unpadded_global_chunks():
     """Only the head sizes with fixed-size global kernels reserve operands of padded chunks:
-    in fp32, and at other head sizes, a chunk of 130 tokens takes no more than 130/128 of
-    the operand room of one of 128."""
+    in fp32, and at other head sizes, a chunk of 130 tokens takes per token what one of 128
+    does (the forward), up to the scratch of a fifth tile of 32 rows (the backward, 6 %;
+    operands padded to 256 rows would add more than 15 %)."""
     def sizes(C, **kw):
         cfg = small_config(B=1, H=2, L=8 * C, C_G=C, locals_=(), **kw)
         return [tnt.tnt_mem_workspace_size(cfg, k) / C for k in (tnt.TNT_WS_FWD_MIN, tnt.TNT_WS_BWD)]
     for kw in (dict(d=16, hid=32), dict(d=64, hid=256), dict(d=16, hid=32, dtype=BF16)):
         for a, b in zip(sizes(130, **kw), sizes(128, **kw)):
-            assert a <= 1.02 * b, (kw, a, b)
+            assert a <= 1.07 * b, (kw, a, b)
