@@ -222,7 +222,7 @@ Layout layout_of(const tnt_config* c, int gsub0 = 0) {
     y.w_chunkc = off; off += up((size_t)y.BH * y.g_chunks * 4 * f);
     y.w_R = off; off += up((size_t)y.BH * c->C_G * c->d * f);
     const Dims D = dims_of(c, c->C_G, c->L);
-    // (the fixed-size kernels take at most one split per 1024 tokens)
+    // (the fixed-size kernels take at most one split per 256 tokens)
     const int ns = std::max({global_fwd_splits(D), global_bwd_splits(D), c->C_G / 256, 1});
     y.w_part = off; off += up((size_t)y.BH * ns * 4 * y.hd * f);
     // transposed state copies and the chunk operands of the fixed-size global kernels

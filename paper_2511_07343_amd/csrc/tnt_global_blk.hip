@@ -33,9 +33,16 @@ constexpr int GCARRY_KT = 128;
 // past the chunk, so every chunk length takes these kernels.
 __host__ __device__ inline int gpad(int C) { return (C + GCARRY_KT - 1) / GCARRY_KT * GCARRY_KT; }
 // tokens per split of the carry / state GEMMs: at most 1024 (fewer fp32 partials
-// written and read back than with short splits), whole slabs, the splits even
-inline int gtk_of(int C) {
+// written and read back than with short splits), whole slabs, the splits even.  A chunk
+// of a multiple of 256 tokens, not of 1024, is cut into splits of 256 where the long ones
+// would leave the state GEMM (2 `pieces` `chains` workgroups a split) under 128: forward and
+// backward of four chunks, d 64, hid 256, splits of 256 / long ones: 1 chain 357 / 404 us
+// (512 tokens), 370 / 462 (768), 413 / 500 (1536), 523 / 637 (3840); 8 chains 394 / 437, 409 /
+// 495, 456 / 534, 845 / 909; 32 chains 494 / 523 and 724 / 767 (64 workgroups), 1043 / 1017
+// (1280 tokens, 128), 2833 / 2598 (3840, 256).
+inline int gtk_of(int C, int chains, int pieces) {
   const int slabs = gpad(C) / GCARRY_KT, ns = (slabs + 7) / 8;
+  if (C % 256 == 0 && C % 1024 && 2 * pieces * chains * ns < 128) return 256;
   return (slabs + ns - 1) / ns * GCARRY_KT;
 }
 // rows (hidden units) of a state matrix that one workgroup of those GEMMs takes: all
@@ -934,9 +941,9 @@ static hipError_t gfwd_blk_chunk(const GlobalArgs& a, int n, hipStream_t st) {
     if (e != hipSuccess) return e;
     if (a.tile_recorded) *a.tile_recorded = 1;
   }
-  const int tk = gtk_of(C), ns = (gpad(C) + tk - 1) / tk;
-  const int sec = section_begin("global_carry", st);
   constexpr int MP = gpiece<D, H>();
+  const int tk = gtk_of(C, chains, H / MP), ns = (gpad(C) + tk - 1) / tk;
+  const int sec = section_begin("global_carry", st);
   constexpr size_t lc = lds_gemm_bytes<CT, MP, D, GCARRY_KT, 1>();
   auto k2 = gfwd_carry_kernel<CT, D, H>;
   set_lds_limit((const void*)k2);
@@ -972,9 +979,9 @@ static hipError_t gbwd_blk_chunk(const GlobalArgs& a, int n, hipStream_t st) {
     set_lds_limit((const void*)k1);
     hipLaunchKernelGGL(k1, dim3(gpad(C) / TT, chains), dim3(512), l1, st, a, n);
   }
-  const int tk = gtk_of(C), ns = (gpad(C) + tk - 1) / tk;
-  const int sec = section_begin("global_bwd_carry", st);
   constexpr int MP = gpiece<D, H>();
+  const int tk = gtk_of(C, chains, H / MP), ns = (gpad(C) + tk - 1) / tk;
+  const int sec = section_begin("global_bwd_carry", st);
   constexpr size_t ls = lds_gemm_bytes<CT, MP, D, GCARRY_KT, 1>();
   auto k2 = za ? gbwd_state_kernel<CT, D, H, true> : gbwd_state_kernel<CT, D, H, false>;
   set_lds_limit((const void*)k2);

@@ -47,6 +47,14 @@ def test_global_chunk_sizes(cfg):
     assert torch.equal(o, o2)
 
 
+@pytest.mark.parametrize("C", [512, 768])
+def test_whole_chunks_in_short_splits(C):
+    """Few chains: chunks of a multiple of 256 tokens go in splits of 256."""
+    cfg = cfg_of(64, 256, C, ACT_GELU, chunks=2)
+    inp = make_inputs(cfg, 513)
+    check(cfg, gpu_backward(cfg, inp), oracle_backward(cfg, inp))
+
+
 def test_long_chunk_in_uneven_splits():
     """1100 tokens a chunk: two splits of 640 and 512 padded tokens."""
     cfg = cfg_of(32, 128, 1100, ACT_SILU, chunks=2)

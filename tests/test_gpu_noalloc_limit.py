@@ -11,8 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kw", [
-    dict(B=1, H=16, L=1056, C_G=1056, locals_=((33, 132),)),
-    dict(B=2, H=12, L=768, C_G=768, locals_=((48, 768),)),
+    dict(B=1, H=16, L=1056, C_G=264, locals_=((33, 132),)),   # 126.4 MiB
+    dict(B=2, H=12, L=768, C_G=384, locals_=((48, 192),)),    # 127.6 MiB
 ], ids=str)
 def test_noalloc_accepts(kw):
     cfg = small_config(BF16, ACT_SILU, d=64, hid=256, name=str(kw), **kw)
