@@ -1320,7 +1320,7 @@ bool try_split(const LocalBwdArgs* a, const Dims& Dm, int units, void* ws, hipSt
   if (G > 1) P.groups = std::max(1, std::min(P.groups, (cus ? std::min(cus, WALK_CUS) : WALK_CUS) / G / std::max(1, a->walks)));
   constexpr SplitLayout Y = make_split_layout(CP, D, H);
   const int total = units * nch;
-  // When the walks leave half the CUs free and are long (32 chunks or more), the
+  // When the walk leaves half the CUs free and is long (32 chunks or more), the
   // chunks are cut in two: passes A and B take the upper chunks first, and the
   // lower chunks' pass A runs on the second stream beside the walk of the upper
   // ones (the walk reaches the lower chunks only after them).  Each part's pass A
@@ -1328,9 +1328,14 @@ bool try_split(const LocalBwdArgs* a, const Dims& Dm, int units, void* ws, hipSt
   // global chain after it, so with short walks the split only delays that chain.
   // The lower part is five eighths of the chunks: the walk of the upper three
   // eighths covers that part's pass A on half the chip (one half measured 0.04 ms
-  // slower at 32 chunks, three quarters 0.04 ms slower too).
+  // slower at 32 chunks, three quarters 0.04 ms slower too).  The sliced walk takes G
+  // CUs a unit; between 65 and 128 units, where it fills the chip, one part or two
+  // measured (us): 68 units, 16 rows, 32 / 256 chunks 1282 / 8424 against 1317 / 8633,
+  // 32 rows 1765 / 12247 against 1824 / 12430; 96 units, 32 chunks 1547 against 1588, 2132
+  // against 2225; 128 units within 0.5 % (only 4 rows at 68 units and 256 chunks gained
+  // from two: 7801 against 7991).
   const bool halves = a->aux && a->aux_mid && a->aux_done && a->pass_a_done && nch >= 32 &&
-                      2 * units <= device_cus();
+                      2 * G * units <= device_cus();
   const int nlo = halves ? nch * 5 / 8 : 0;
   P.n0 = nlo;
   P.nc = nch - nlo;
