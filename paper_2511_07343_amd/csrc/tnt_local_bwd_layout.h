@@ -20,7 +20,7 @@ enum BwdCT {
 };
 // fp32 buffers
 enum BwdF32 {
-  E_XK, E_HH, E_dOR, E_dZD1, E_Cbar, E_U, E_Kbar, E_Rbar, E_Xbar, E_T3, E_T4, E_T5, E_T6, E_Zkp,
+  E_XK, E_HH, E_dOR, E_dZD1, E_Cbar, E_Kbar, E_Rbar, E_Xbar, E_T3, E_T4, E_T5, E_T6, E_Zkp,
   E_Msym, E_PartA, E_PartE, BWD_F32_COUNT
 };
 
@@ -52,7 +52,7 @@ __host__ __device__ constexpr BwdLayout make_bwd_layout(int Cp, int d, int h) {
   }
   y->ct_elems = off;
   const size_t hp = (size_t)(h / 16 > d / 16 ? h / 16 : d / 16);
-  const size_t s_f[BWD_F32_COUNT] = {CC, CC, CC, CC, CC, CC, Cd, Cd, Cd, Cd, Cd, Cd, Cd, Ch,
+  const size_t s_f[BWD_F32_COUNT] = {CC, CC, CC, CC, CC, Cd, Cd, Cd, Cd, Cd, Cd, Cd, Ch,
                                      (size_t)d * d, hp * C, hp * C};
   off = 0;
   for (int i = 0; i < BWD_F32_COUNT; ++i) {

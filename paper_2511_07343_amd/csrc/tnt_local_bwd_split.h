@@ -15,7 +15,7 @@ struct SplitPtrs {
   float* brec_f;            // fp32 [units * nch][r.bf.n]
   float* dks;               // fp32 [units * nch][slices][Cp * d]  the walk's part of dk, per slice
   unsigned long long* xch;  // [groups][2][slices][Cp * d]  the slices' partial Rbar: value (low
-                            // half) and tag (high half); null for one slice
+                            // half) and tag (high half)
   int units;
   int n0, nc;               // passes A and B: the chunks n0 .. n0 + nc - 1 of every unit
   int groups;               // walk: groups of `slices` workgroups, unit u on group u % groups

@@ -51,6 +51,7 @@ constexpr int WAIT_ROUNDS = 1 << 25;  // a poll takes about a microsecond
 template <int D, int H, int CP>
 struct BWalk {
   static constexpr int HS = rec::walk_hs(H), G = rec::walk_slices(CP, H);
+  static_assert(G == 2, "two slices a unit: each has one other to wait for");
   static constexpr int NW = HS / 16, NT = NW * WAVE;
   static constexpr int DT = D / 16, TM = CP / 16;
   static constexpr int NCI = (CP + 31) / 32;  // K steps of a contraction over the chunk
@@ -154,7 +155,7 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
   const int h0 = sl * HS;                    // the slice's first hidden column
   const int pair = w / DT, strip = w % DT;   // column strip of T3, T4 (0) or T5, T6 (1)
   const float rscale = 2.0f / (float)D;
-  unsigned long long* const xg = G > 1 ? P.xch + (size_t)grp * 2 * G * CP * D : nullptr;
+  unsigned long long* const xg = P.xch + (size_t)grp * 2 * G * CP * D;
 
   f4 w1[DT], s1[DT], w2[DT], s2[DT];  // the adjoint: rows 16 dt + 4 g + r, column h0 + 16 w + lc
   // bf16 copies of the adjoint in LDS, [D][LH]
@@ -554,7 +555,7 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
         bqf[RL.bf.o[rec::gB] + CP * sl + tid] = -y;
       }
       const unsigned tag = tag0 + (unsigned)n + 1;
-      unsigned long long* const xb = G > 1 ? xg + (size_t)(turn & 1) * G * CP * D : nullptr;
+      unsigned long long* const xb = xg + (size_t)(turn & 1) * G * CP * D;
       float* const dvp = a.dv_part + (cbase + tok0) * D;
       // ---- the slice's part of Rbar
       if (pair == 1) {
@@ -581,20 +582,15 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
             for (int r = 0; r < 4; ++r) kr[it][r] -= po[r];
           }
         }
-        if constexpr (G > 1) {
 #pragma unroll
-          for (int it = 0; it < TM; ++it) {
-            unsigned long long* const p = xb + (uint32_t)(sl * CP * D + (16 * it + 4 * g) * D + 16 * strip + lc);
+        for (int it = 0; it < TM; ++it) {
+          unsigned long long* const p = xb + (uint32_t)(sl * CP * D + (16 * it + 4 * g) * D + 16 * strip + lc);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float v = kr[it][r];
-              __hip_atomic_store(p + r * D, ((unsigned long long)tag << 32) | __builtin_bit_cast(unsigned, v),
-                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+          for (int r = 0; r < 4; ++r) {
+            const float v = kr[it][r];
+            __hip_atomic_store(p + r * D, ((unsigned long long)tag << 32) | __builtin_bit_cast(unsigned, v),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
-        } else {
-#pragma unroll
-          for (int it = 0; it < TM; ++it) put_y(it, kr[it], dvp);
         }
       }
       // ---- the adjoint update's terms without Ykbar
@@ -637,53 +633,33 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
 #pragma unroll
         for (int c = 0; c < NCI; ++c) hkf[c] = gfrag<CP>(rc + RL.fc.o[rec::HkT], (hw + y.lc) * CP, 32 * c, y.g);
       }
-      // ---- Rbar of every slice (this one's from the registers: a workgroup never reads
-      // words that it may still be writing) -> Ykbar
-      if constexpr (G > 1) {
-        if (pair == 1) {
-          const Lane y;
-          // two slices: the order of the two terms does not matter; more: slice by slice
-          f4 sum[G > 2 ? TM : 1];
-          if constexpr (G > 2)
+      // ---- the other slice's part of Rbar added to this one's (from the registers: a
+      // workgroup never reads words that it may still be writing; two terms, so their order
+      // does not matter) -> Ykbar
+      if (pair == 1) {
+        const Lane y;
+        const unsigned long long* const p = xb + (uint32_t)((1 - sl) * CP * D + 4 * y.g * D + 16 * strip + y.lc);
 #pragma unroll
-            for (int it = 0; it < TM; ++it) sum[it] = zero4();
+        for (int it = 0; it < TM; ++it) {  // a tile at a time (the later ones have mostly arrived)
+          unsigned long long x[4];
+          bool all = false;  // of the wave
+          for (int round = lost ? WAIT_ROUNDS - 1 : 0; !all && round < WAIT_ROUNDS; ++round) {
+            bool ok = true;
 #pragma unroll
-          for (int gg = 0; gg < G; ++gg) {
-            if (gg == sl) {
-              if constexpr (G > 2)
+            for (int r = 0; r < 4; ++r)
+              x[r] = __hip_atomic_load(p + (16 * it + r) * D, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-                for (int it = 0; it < TM; ++it) sum[it] += kr[it];
-              continue;
-            }
-            const unsigned long long* const p = xb + (uint32_t)(gg * CP * D + 4 * y.g * D + 16 * strip + y.lc);
-#pragma unroll
-            for (int it = 0; it < TM; ++it) {  // a tile at a time (the later ones have mostly arrived)
-              unsigned long long x[4];
-              bool all = false;  // of the wave
-              for (int round = lost ? WAIT_ROUNDS - 1 : 0; !all && round < WAIT_ROUNDS; ++round) {
-                bool ok = true;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  x[r] = __hip_atomic_load(p + (16 * it + r) * D, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) ok = ok && (unsigned)(x[r] >> 32) == tag;
-                all = __builtin_amdgcn_readfirstlane(__all(ok)) != 0;
-                if (!all) __builtin_amdgcn_s_sleep(1);
-              }
-              lost = lost || !all;
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const float v = all ? __builtin_bit_cast(float, (unsigned)x[r]) : __builtin_nanf("");
-                if constexpr (G > 2)
-                  sum[it][r] += v;
-                else
-                  kr[it][r] += v;
-              }
-            }
+            for (int r = 0; r < 4; ++r) ok = ok && (unsigned)(x[r] >> 32) == tag;
+            all = __builtin_amdgcn_readfirstlane(__all(ok)) != 0;
+            if (!all) __builtin_amdgcn_s_sleep(1);
           }
+          lost = lost || !all;
 #pragma unroll
-          for (int it = 0; it < TM; ++it) put_y(it, G > 2 ? sum[G > 2 ? it : 0] : kr[it], dvp);
+          for (int r = 0; r < 4; ++r)
+            kr[it][r] += all ? __builtin_bit_cast(float, (unsigned)x[r]) : __builtin_nanf("");
         }
+#pragma unroll
+        for (int it = 0; it < TM; ++it) put_y(it, kr[it], dvp);
       }
       __syncthreads();  // Ykbar, K^T complete
 
