@@ -169,7 +169,12 @@ tnt_status tnt_mem_fwd(const tnt_config* cfg, const void* q, const void* k, cons
  *   saved : the buffer filled by tnt_mem_fwd on the same inputs (same
  *           configuration and kernel family; TNT_ERR_ARG otherwise), or NULL to
  *           recompute the states (then ws_bytes must cover TNT_WS_BWD_RECOMPUTE).
- * dq, dk, dv have the I/O dtype; the others are fp32 in the layouts above. */
+ * dq, dk, dv have the I/O dtype; the others are fp32 in the layouts above.
+ * Local memories with chunks of up to 32 tokens (bf16, d 64, hid 256) are walked
+ * back by pairs of workgroups that exchange a partial sum per chunk and wait for
+ * each other on the device.  Every wait is bounded (2^25 polls, tens of seconds):
+ * should the device stop running one of a pair for that long, the gradients of
+ * the call are NaN, with no error, since the call has long returned. */
 tnt_status tnt_mem_bwd(const tnt_config* cfg, const void* q, const void* k, const void* v,
                        const float* lr, const float* mom, const float* decay,
                        const float* W1_init, const float* W2_init, const void* dO,

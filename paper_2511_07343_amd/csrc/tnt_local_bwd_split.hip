@@ -208,6 +208,8 @@ local_bwd_ret_kernel(LocalBwdArgs a, SplitPtrs P) {
       unsigned long long* const xw = P.xch + (size_t)tl * NX;
       for (int e = threadIdx.x; e < NX; e += 512)
         __hip_atomic_store(xw + e, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tl == 0 && threadIdx.x < 2 * WALK_LANES)
+        __hip_atomic_store(P.tickets + threadIdx.x * TICKET_STRIDE, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     const int tok0 = s * Dm.S + n * C;
     const int l = lane_id_local();
@@ -1272,7 +1274,8 @@ size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 template <typename CT>
 size_t total_bytes(const SplitSizes& z) {
-  return up256(z.rec_ct * sizeof(CT)) + up256(z.rec_f * 4) + up256(z.dks * 4) + up256(z.xch * 8);
+  return up256(z.rec_ct * sizeof(CT)) + up256(z.rec_f * 4) + up256(z.dks * 4) + up256(z.xch * 8) +
+         (z.xch ? WALK_TICKETS * sizeof(unsigned) : 0);
 }
 
 template <typename CT>
@@ -1283,6 +1286,8 @@ SplitPtrs carve(void* ws, const SplitSizes& z, int units) {
   P.brec_f = (float*)p; p += up256(z.rec_f * 4);
   P.dks = (float*)p; p += up256(z.dks * 4);
   P.xch = z.xch ? (unsigned long long*)p : nullptr;
+  p += up256(z.xch * 8);
+  P.tickets = z.xch ? (unsigned*)p : nullptr;
   P.units = units;
   return P;
 }

@@ -25,15 +25,21 @@
 // fence, no flag, one trip.  Two buffers in turn: a slice that publishes a chunk has
 // received the others' chunk before it, which they sent after they had read the one
 // before that, the last in the same buffer.
-// Pass A clears the tags in every call.  The grid is never larger than the CUs
-// (groups of slices take several units in turn), the slices of a group are neighbours
-// in the dispatch order of one XCD, and the wait ends after WAIT_ROUNDS in any case
-// (the sums are NaN then).
+// Pass A clears the tags in every call.
+//
+// A workgroup learns its slice from a counter of the workgroups that have started (eight
+// counters, by residue of the block index; pass A clears them, too).  Those that have
+// started are therefore whole groups and at most one slice more per counter, in whatever
+// order the device starts them and whatever else runs there: a whole group waits for
+// nobody outside it, and the next workgroup to start on a place that it leaves completes
+// a pair.  The grid is never larger than the CUs (groups of slices take several units in
+// turn).  The wait ends after WAIT_ROUNDS in any case; the gradients are NaN then.
 //
 // Bound by latency (one memory round trip, four barriers and one exchange a chunk).
 // Chunks of up to 32 rows: 11.7 us a chunk at 16 rows (32 units of 512 chunks), where
-// the walk on one CU per unit with the adjoint in memory took 36.  At 64 rows the tiles
-// do not fit beside the adjoint in the registers, and that walk stays.
+// the walk on one CU per unit with the adjoint in memory took 36.  The 32-row instance
+// already spills 66 to 71 of its vector registers; at 64 rows the tiles do not fit beside
+// the adjoint at all, and that walk stays.
 #include "tnt_local_bwd_helpers.h"
 #include "tnt_local_bwd_split.h"
 #include "tnt_regtile.h"
@@ -139,6 +145,7 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
   constexpr rec::RecLayout RL = rec::make_rec_layout(CP, D, H);
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ __align__(16) float sC[CP], sB[CP];
+  __shared__ int role;
   __shared__ float sc3[4], dpart[3][NW], pC[2 * DT][CP], pB[2 * DT][CP];
   CT* const L = reinterpret_cast<CT*>(smem);
   CT *sPzT = L + B::PzT, *sQ1T = L + B::Q1T, *sK = L + B::K, *sR = L + B::R, *sYk = L + B::Yk,
@@ -146,9 +153,18 @@ __global__ void __launch_bounds__((BWalk<D, H, CP>::NT)) local_bwd_walk_kernel(L
      *sdOET = L + B::dOET, *sRT = L + B::RT,
      *sAdj = L + B::adj, *sGz = L + B::sG;
 
-  const int blk = (int)blockIdx.x / (8 * G), rem = (int)blockIdx.x % (8 * G);
-  const int sl = rem / 8, grp = blk * 8 + rem % 8;  // this workgroup's slice and group
-  if (grp >= P.groups) return;                      // (every slice of the group)
+  // this workgroup's group and slice, by the order in which those of its residue modulo
+  // WALK_LANES have started (one counter for all of them: 1135 us for 1120 at B 2, H 4, L 2048)
+  if (threadIdx.x == 0) {
+    const int lane8 = (int)blockIdx.x % WALK_LANES, part = P.n0 + P.nc == a.D.S / a.D.C ? 0 : 1;
+    role = (int)__hip_atomic_fetch_add(P.tickets + (part * WALK_LANES + lane8) * TICKET_STRIDE, 1u,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * WALK_LANES + lane8;
+  }
+  __syncthreads();
+  const int place = __builtin_amdgcn_readfirstlane(role);
+  const int blk = place / (WALK_LANES * G), rem = place % (WALK_LANES * G);
+  const int sl = rem / WALK_LANES, grp = blk * WALK_LANES + rem % WALK_LANES;
+  if (grp >= P.groups) return;  // (every slice of the group)
   const Dims Dm = a.D;
   const int C = Dm.C, nshard = Dm.L / Dm.S, nch = Dm.S / C;
   const int w = wave_id_uniform();
@@ -748,7 +764,7 @@ bool try_walk(const LocalBwdArgs& a, const SplitPtrs& P, hipStream_t st, hipErro
     return true;
   }
   set_lds_limit((const void*)kern);
-  const int grid = (P.groups + 7) / 8 * 8 * B::G;
+  const int grid = (P.groups + WALK_LANES - 1) / WALK_LANES * WALK_LANES * B::G;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(B::NT), lds, st, a, P);
   *err = hipGetLastError();
   return true;
