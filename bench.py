@@ -161,8 +161,9 @@ def launch_flops(cfg, name):
 TRAFFIC_FILE = {2: "hbm_traffic_pretrain_B4H8L8192.txt"}
 _COMMON = ["tnt_device.h", "tnt_kernels.h"]
 LAUNCH_SOURCES = {
-    "local_bwd": ["tnt_local_bwd_split.hip", "tnt_local_bwd_helpers.h", "tnt_local_common.h",
-                  "tnt_local_record.h"] + _COMMON,
+    "local_bwd": ["tnt_local_bwd_split.hip", "tnt_local_bwd_split.h", "tnt_local_bwd_walk.hip",
+                  "tnt_local_bwd_helpers.h", "tnt_local_bwd_layout.h", "tnt_regtile.h",
+                  "tnt_local_common.h", "tnt_local_record.h"] + _COMMON,
     "local_fwd": ["tnt_local_fwd_fast.hip", "tnt_local_walk.hip", "tnt_local_ret.hip", "tnt_regtile.h",
                   "tnt_local_common.h",
                   "tnt_local_record.h"] + _COMMON,

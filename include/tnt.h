@@ -106,11 +106,15 @@ typedef enum {
   TNT_WS_FWD = 0,          /* tnt_mem_fwd                                       */
   TNT_WS_BWD = 1,          /* tnt_mem_bwd given the forward's saved buffer     */
   TNT_WS_BWD_RECOMPUTE = 2,/* tnt_mem_bwd with saved == NULL                   */
-  TNT_WS_FWD_MIN = 3       /* the least tnt_mem_fwd accepts: with saved == NULL
-                              and less than TNT_WS_FWD, each local memory's
-                              forward runs as one walk per shard instead of the
-                              walk plus the chunk-parallel retrieval (same
-                              results to rounding, slower)                      */
+  TNT_WS_FWD_MIN = 3       /* enough for every tnt_mem_fwd, with or without a
+                              saved buffer, and what one with a saved buffer
+                              asks for.  A call with saved == NULL may accept
+                              less; below TNT_WS_FWD it runs each local memory's
+                              forward as one walk per shard instead of the walk
+                              plus the chunk-parallel retrieval, and below
+                              TNT_WS_FWD_MIN also the global memory's padded
+                              chunks on the runtime-sized kernels (same results
+                              to rounding, slower)                              */
 } tnt_ws_kind;
 
 /* Bytes of device workspace the call needs (0 if the config is invalid). */
@@ -155,9 +159,10 @@ size_t tnt_mem_saved_size(const tnt_config* cfg);
  *   saved       : may be NULL; else saved_bytes >= tnt_mem_saved_size(cfg)
  *                 (TNT_ERR_WORKSPACE otherwise) that receive the header and the
  *                 chunk-entry states for a later tnt_mem_bwd.
- *   workspace   : ws_bytes >= tnt_mem_workspace_size(cfg, TNT_WS_FWD_MIN); with
- *                 saved == NULL, ws_bytes >= tnt_mem_workspace_size(cfg, TNT_WS_FWD)
- *                 lets the local memories take the two-pass forward. */
+ *   workspace   : ws_bytes >= tnt_mem_workspace_size(cfg, TNT_WS_FWD_MIN) is
+ *                 enough; with saved == NULL, ws_bytes >=
+ *                 tnt_mem_workspace_size(cfg, TNT_WS_FWD) lets the local
+ *                 memories take the two-pass forward. */
 tnt_status tnt_mem_fwd(const tnt_config* cfg, const void* q, const void* k, const void* v,
                        const float* lr, const float* mom, const float* decay,
                        const float* W1_init, const float* W2_init, void* o,

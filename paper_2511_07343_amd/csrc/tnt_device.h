@@ -358,8 +358,8 @@ __device__ __forceinline__ void mma_run_(RowAcc<RB>& x, RowAcc<RB>& y, const EA*
   }
   apply(cur);
   // The reader may be in another block (after a loop, or after a product that a
-  // flag leaves out), where the compiler has been seen to leave out the wait states
-  // between a matrix product and the read of its result: wait here.
+  // flag leaves out).  The wait states between a matrix product and the read of its
+  // result pass here, once, ahead of any such branch.
   auto pin = [&] {
 #pragma unroll
     for (int r = 0; r < RB; ++r) {

@@ -19,7 +19,8 @@
 // y = W^2 s(z), the residual r, delta = (W^2^T r) s'(z), the global retrieval) is
 // independent from token to token until the next chunk boundary, and a slice's
 // running weights depend on r and its own rows only.  So up to STEP_N tokens that
-// no memory's chunk boundary divides take two launches:
+// no memory's chunk boundary divides, and that the scratch area has room for, take
+// two launches:
 //   tokens  one workgroup per (slice, chain, memory): y of every token over all
 //           hidden units (each slice forms it for itself: no exchange between
 //           workgroups), r, the slice's delta; then, token by token with the
@@ -46,9 +47,9 @@
 // cut of a sequence gives bitwise the same results.
 //
 // Bound by the launches' latency at few chains (entry, update and out: 14.7 us for one
-// chain at d 64, hid 256, global + one local) and by the state's bytes at many: its 14
-// hid d floats per (memory, chain) and token (W^1, W1, S1, W2, S2 in or out once, W^2
-// twice, and the 4 updated ones out) take 162 us for 512 chains, 5.8 TB/s.  With three
+// chain at d 64, hid 256, global + one local) and by the state's bytes at many: its 11
+// hid d floats per (memory, chain) and token (W^1, W1, S1, W2, S2 in once, W^2 twice, the
+// 4 updated ones out) take 162 us for 512 chains, 4.6 TB/s.  With three
 // launches of vector products before, 25 and 196 us.  77 tokens at B 2, H 8: 336 us,
 // against 2104 with launches for every token.
 #include "tnt_device.h"
