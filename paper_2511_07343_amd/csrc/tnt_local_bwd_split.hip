@@ -7,12 +7,13 @@
 // chunk that the backward needs into the chunk's forward record (see
 // tnt_local_record.h), so the reverse walk over a shard's chunks is split:
 //
-//   pass A  (all chunks of all units at once, a persistent grid) takes the
+//   pass A  (all chunks of all units at once, a workgroup each) takes the
 //           backward of the retrieval from dO and the forward record, writes
 //           the chunk's dq and its share of dk, and leaves a backward record:
 //           the dO operands the walk contracts, the retrieval's gate
 //           cotangents (cbar, dA, dE) and Xbar^T Q for the Q-K state adjoint;
-//   pass B  (one workgroup per unit, chunks in reverse) walks the carried
+//   pass B  (chunks in reverse; here one workgroup per unit, up to 32 rows in
+//           slices on two CUs, tnt_local_bwd_walk.hip) walks the carried
 //           adjoint back: T3..T6, D1bar / Gbar, Rbar (dv), Zkbar, the carried
 //           part of Kbar and the chunk-entry adjoint, four block barriers a chunk;
 //   scan    turns the per-chunk Xbar^T Q into the suffix sums the Q-K projection
