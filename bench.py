@@ -325,8 +325,9 @@ def decode_bench(args, cfg, x, dev):
     kt = tnt.tnt_timing_read()
     ms_call = 1e3 * (t1 - t0) / args.steps
     ev_ms = kt["step"][0] / kt["step"][1]
-    # per token and memory: read W^1, W^2, W1, W2, S1, S2, write W1, W2, S1, S2 (fp32)
-    alg = M * cfg.B * cfg.H * T * 10 * cfg.hid * cfg.d * 4
+    # per call and memory: read W^1, W^2, W1, W2, S1, S2, write W1, W2, S1, S2 (fp32); the
+    # tokens of a call between two chunk starts can share them
+    alg = M * cfg.B * cfg.H * 10 * cfg.hid * cfg.d * 4
     res = {
         "metric": f"step-wise forward tokens/s ({T} token(s) per chain per call)",
         "value": cfg.B * T * args.steps / (t1 - t0), "unit": "tokens/s", "n_gpus": 1,
