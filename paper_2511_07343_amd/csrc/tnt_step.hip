@@ -95,15 +95,30 @@ __host__ __device__ inline StepLds step_lds(int d, int hid, int HS) {
   return y;
 }
 
-// One 16-byte piece of a lane's row of B in the product acc(t, j) += sum_k A[t][k] B[j][k]
-// (16 rows t of A in LDS, 16 rows j of B, both contraction-contiguous): the piece at
-// contraction offset k0 + 4 (lane / 16) holds four consecutive k, one per MFMA step
-// (the steps sum the same k on both sides).
-__device__ __forceinline__ void row_piece(f4& acc, const float* A, int lda, int k0, const f4& b) {
-  const int l = lane_id();
-  const f4 x = *reinterpret_cast<const f4*>(A + (l & 15) * lda + k0 + 4 * (l >> 4));
+// Sum over P 16-byte pieces of a lane's row of B in the product (t, j) -> sum_k A[t][k]
+// B[j][k] (16 rows t of A in LDS, 16 rows j of B, both contraction-contiguous): the piece
+// at contraction offset k0 + 4 (lane / 16) holds four consecutive k, one per MFMA step (the
+// steps sum the same k on both sides).  ONE: the only row is 0, at A.  The pieces are added
+// as a tree: in one accumulator, where every step rounds the whole sum, fp32 outputs are
+// 2.0 to 2.4e-7 from 64 bits at d 64 and 128, and 1.4 to 1.7e-7 with the tree (as with lane
+// sums of vector products).  FINE, for d 16 and 32, halves the chains once more; at wider
+// d that costs up to 17 % (d 64, hid 256, 128 chains: 44.6 for 38.3 us) and gains 1 to 6 %.
+template <int P, bool ONE, bool FINE>
+__device__ __forceinline__ f4 row_sum(const float* A, int lda, int k0, const f4* b) {
+  if constexpr (P == 1) {
+    const int l = lane_id();
+    f4 x = *reinterpret_cast<const f4*>(A + (ONE ? 0 : (l & 15) * lda) + k0 + 4 * (l >> 4));
+    if (ONE && (l & 15)) x = zero4();
+    constexpr int CHAIN = FINE ? 2 : 4;  // steps in one accumulator
+    f4 p[4 / CHAIN];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r], b[r], acc, 0, 0, 0);
+    for (int r = 0; r < 4; ++r)
+      p[r / CHAIN] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r], b[0][r], r % CHAIN ? p[r / CHAIN] : zero4(), 0, 0, 0);
+    if constexpr (FINE) return p[0] + p[1];
+    return p[0];
+  } else {
+    return row_sum<P / 2, ONE, FINE>(A, lda, k0, b) + row_sum<P - P / 2, ONE, FINE>(A, lda, k0 + 16 * (P / 2), b + P / 2);
+  }
 }
 
 // Sums over groups of W consecutive lanes (4, 8, 16 or 32, aligned), every lane of a
@@ -139,7 +154,7 @@ __device__ __forceinline__ float dot4(const f4& a, const f4& b) {
 __device__ __forceinline__ void gated(f4& w, f4& s, float beta, float keep, float c, const f4& v) {
 #pragma unroll
   for (int x = 0; x < 4; ++x) {
-    s[x] = __builtin_fmaf(-c, v[x], beta * s[x]);
+    s[x] = __builtin_fmaf(beta, s[x], -(c * v[x]));  // (the larger product unrounded)
     w[x] = __builtin_fmaf(keep, w[x], s[x]);
   }
 }
@@ -267,6 +282,7 @@ __global__ void __launch_bounds__(step_threads(D), D == 64 ? 1 : 2) step_tokens_
   constexpr int NU = D <= 32 ? 2 : 16 * D / NT;  // pieces of each of the slice's arrays a thread holds
   constexpr int NM = (D * g4 + NT - 1) / NT;  // and of M
   constexpr int ND = D / 16;                   // tiles of d, pieces of a row of W^1
+  constexpr bool FINE = D <= 32;
   constexpr int GZ = D == 128 ? 2 : 4;         // row tiles of W^1 a wave requests at a time
   constexpr int GY = D == 128 ? 8 : 16;        // pieces of a row of W^2 likewise
   const int g = blockIdx.x, chain = blockIdx.y, m = blockIdx.z;
@@ -359,12 +375,9 @@ __global__ void __launch_bounds__(step_threads(D), D == 64 ? 1 : 2) step_tokens_
       for (int x = 0; x < GZ; ++x) {
         const int jt = w + NW * (x0 + x);
         if (jt >= hid / 16) continue;
-        f4 z = zero4(), zq = zero4();
-#pragma unroll
-        for (int s = 0; s < ND; ++s) {
-          row_piece(z, sk, Y.ld, 16 * s, bz[x][s]);
-          if constexpr (TWO) row_piece(zq, sq, Y.ld, 16 * s, bz[x][s]);
-        }
+        const f4 z = row_sum<ND, false, FINE>(sk, Y.ld, 0, bz[x]);
+        f4 zq = zero4();
+        if constexpr (TWO) zq = row_sum<ND, false, FINE>(sq, Y.ld, 0, bz[x]);
         const int j = jt * 16 + lc;
         const bool mine = j >= j0 && j < j0 + HS;
 #pragma unroll
@@ -405,14 +418,8 @@ __global__ void __launch_bounds__(step_threads(D), D == 64 ? 1 : 2) step_tokens_
       if (it != w || k0) load_y(it, k0);
 #pragma unroll
       for (int s0 = 0; s0 < P; s0 += S) {
-        f4 yp = zero4(), yqp = zero4();
-#pragma unroll
-        for (int s = s0; s < s0 + S; ++s) {
-          row_piece(yp, sa, Y.lh, k0 + 16 * s, by[s]);
-          if constexpr (TWO) row_piece(yqp, saq, Y.lh, k0 + 16 * s, by[s]);
-        }
-        y += yp;
-        if constexpr (TWO) yq += yqp;
+        y += row_sum<S, false, FINE>(sa, Y.lh, k0 + 16 * s0, by + s0);
+        if constexpr (TWO) yq += row_sum<S, false, FINE>(saq, Y.lh, k0 + 16 * s0, by + s0);
       }
     }
     const int i = it * 16 + lc;
@@ -469,9 +476,7 @@ __global__ void __launch_bounds__(step_threads(D), D == 64 ? 1 : 2) step_tokens_
   __syncthreads();
   // delta = (W^2^T r) s'(z) on the slice's columns (HS / 16 <= 4 tiles, one per wave)
   if (w < HS / 16) {
-    f4 acc = zero4();
-#pragma unroll
-    for (int s = 0; s < ND; ++s) row_piece(acc, sr, Y.ld, 16 * s, bd[s]);
+    const f4 acc = row_sum<ND, false, FINE>(sr, Y.ld, 0, bd);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int t = 4 * lg + r, j = w * 16 + lc;
@@ -504,14 +509,6 @@ __global__ void __launch_bounds__(step_threads(D), D == 64 ? 1 : 2) step_tokens_
 // of W^2 twice, whatever the number of slices, and a workgroup holds the registers of
 // one phase.  The products are the same MFMA tiles with one row that is not zero.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void row_piece1(f4& acc, const float* A, int k0, const f4& b) {
-  const int l = lane_id();
-  f4 x = *reinterpret_cast<const f4*>(A + k0 + 4 * (l >> 4));
-  if (l & 15) x = zero4();
-#pragma unroll
-  for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[r], b[r], acc, 0, 0, 0);
-}
-
 // entry: z = W^1 k of the slice's rows (and the global retrieval's W^1 q), the slice's
 // share of W^2 s(z) (and of W^2 s(W^1 q)); a local memory's query x, its rows dealt to
 // the slices
@@ -519,6 +516,7 @@ template <typename IO, int ACT, int D>
 __global__ void __launch_bounds__(STEP_THREADS) step_entry_kernel(StepArgs a) {
   __shared__ __align__(16) float sk[D], sq[D], sa[64], saq[64];
   constexpr int d = D, g4 = D / 4, ND = D / 16, NW = STEP_THREADS / WAVE, TY = (ND + NW - 1) / NW;
+  constexpr bool FINE = D <= 32;
   const int g = blockIdx.x, chain = blockIdx.y, m = blockIdx.z;
   const int hid = a.hid, HS = a.HS, G = a.G, j0 = g * HS;
   const int tid = threadIdx.x, l = lane_id(), w = wave_id(), lg = l >> 4, lc = l & 15;
@@ -549,12 +547,9 @@ __global__ void __launch_bounds__(STEP_THREADS) step_entry_kernel(StepArgs a) {
   __syncthreads();
   auto z_tile = [&](auto two) {
     constexpr bool TWO = decltype(two)::value;
-    f4 z = zero4(), zq = zero4();
-#pragma unroll
-    for (int s = 0; s < ND; ++s) {
-      row_piece1(z, sk, 16 * s, bz[s]);
-      if constexpr (TWO) row_piece1(zq, sq, 16 * s, bz[s]);
-    }
+    const f4 z = row_sum<ND, true, FINE>(sk, 0, 0, bz);
+    f4 zq = zero4();
+    if constexpr (TWO) zq = row_sum<ND, true, FINE>(sq, 0, 0, bz);
     if (lg == 0) {
       const int j = w * 16 + lc;
       const ActVals av = act_all<ACT>(z[0]);
@@ -574,12 +569,9 @@ __global__ void __launch_bounds__(STEP_THREADS) step_entry_kernel(StepArgs a) {
   auto y_tile = [&](int it, const f4(&b)[4], auto pieces, auto two) {
     constexpr int P = decltype(pieces)::value;
     constexpr bool TWO = decltype(two)::value;
-    f4 y = zero4(), yq = zero4();
-#pragma unroll
-    for (int s = 0; s < P; ++s) {
-      row_piece1(y, sa, 16 * s, b[s]);
-      if constexpr (TWO) row_piece1(yq, saq, 16 * s, b[s]);
-    }
+    const f4 y = row_sum<P, true, FINE>(sa, 0, 0, b);
+    f4 yq = zero4();
+    if constexpr (TWO) yq = row_sum<P, true, FINE>(saq, 0, 0, b);
     if (lg == 0) {
       sc.yp[(size_t)g * d + it * 16 + lc] = y[0];
       if constexpr (TWO) sc.share[(size_t)g * d + it * 16 + lc] = yq[0];
@@ -624,6 +616,7 @@ template <typename IO, int ACT, int D>
 __global__ void __launch_bounds__(step_threads(D)) step_update_kernel(StepArgs a) {
   __shared__ __align__(16) float sk[D], sr[D], sx[D], sa[64], ssp[64], sg[64], sz[64];
   constexpr int d = D, NT = step_threads(D), g4 = D / 4, ND = D / 16;
+  constexpr bool FINE = D <= 32;
   constexpr int NU = D <= 32 ? 2 : 16 * D / NT;
   const int g = blockIdx.x, chain = blockIdx.y, m = blockIdx.z;
   const int H = a.H, hid = a.hid, HS = a.HS, G = a.G, j0 = g * HS;
@@ -672,9 +665,7 @@ __global__ void __launch_bounds__(step_threads(D)) step_update_kernel(StepArgs a
   }
   __syncthreads();
   if (w < HS / 16) {
-    f4 acc = zero4();
-#pragma unroll
-    for (int s = 0; s < ND; ++s) row_piece1(acc, sr, 16 * s, bd[s]);
+    const f4 acc = row_sum<ND, true, FINE>(sr, 0, 0, bd);
     if (lg == 0) sg[w * 16 + lc] = acc[0] * ssp[w * 16 + lc];
   }
   __syncthreads();
