@@ -530,8 +530,8 @@ __device__ __forceinline__ void mma_pair_dots(f4 (&t0)[RBN], f4 (&t1)[RBN], cons
 // pass B on one CU per unit: the carried adjoint, walked back through a unit's
 // chunks with the adjoint in memory.  Chunks of more than 32 rows: there the sliced
 // walk (tnt_local_bwd_walk.hip) has to spill its 64-row tiles beside the
-// register-resident adjoint and takes 57 us a chunk on two CUs, this one 86 us on one
-// (128 units, workload of B 4, H 8, L 8192: step 4.62 ms here, 4.98 ms there).
+// register-resident adjoint and takes 57 us a chunk on two CUs, this one 88 us on one
+// (128 units, workload of B 4, H 8, L 8192: step 4.65 ms here, 4.98 ms there).
 // ===========================================================================
 template <typename IO, typename CT, int ACT, int D, int H, int CP, bool LO>
 __global__ void __launch_bounds__(512) local_bwd_chain_kernel(LocalBwdArgs a, SplitPtrs P) {

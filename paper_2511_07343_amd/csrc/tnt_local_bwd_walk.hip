@@ -36,7 +36,7 @@
 // turn).  The wait ends after WAIT_ROUNDS in any case; the gradients are NaN then.
 //
 // Bound by latency (one memory round trip, four barriers and one exchange a chunk).
-// Chunks of up to 32 rows: 11.7 us a chunk at 16 rows (32 units of 512 chunks), where
+// Chunks of up to 32 rows: 10.8 us a chunk at 16 rows (32 units of 512 chunks), where
 // the walk on one CU per unit with the adjoint in memory took 36.  The 32-row instance
 // already spills 66 to 71 of its vector registers; at 64 rows the tiles do not fit beside
 // the adjoint at all, and that walk stays.

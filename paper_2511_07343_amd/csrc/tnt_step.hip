@@ -50,7 +50,7 @@
 // chain at d 64, hid 256, global + one local) and by the state's bytes at many: its 11
 // hid d floats per (memory, chain) and token (W^1, W1, S1, W2, S2 in once, W^2 twice, the
 // 4 updated ones out) take 162 us for 512 chains, 4.6 TB/s.  With three
-// launches of vector products before, 25 and 196 us.  77 tokens at B 2, H 8: 336 us,
+// launches of vector products before, 25 and 196 us.  77 tokens at B 2, H 8: 347 us,
 // against 2104 with launches for every token.
 #include "tnt_device.h"
 #include "tnt_kernels.h"
